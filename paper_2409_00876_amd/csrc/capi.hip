@@ -739,12 +739,22 @@ namespace {
 // params.max_inflight_waves (automatic: see auto_inflight_waves) and by the
 // number of 64-term groups.  Large grids use 4-wave blocks; small caps use
 // one-wave blocks so the number of concurrent waves is exactly the cap.
-// Automatic cap: about n_nodes / 32 terms in flight (n_nodes / 2048 waves), so
-// a term shares an endpoint with another in-flight term with probability of
-// about 3% (the Hogwild sparsity assumption).  Small graphs are sensitive to
-// this: on a 2.6K-node graph one wave keeps the sampled path stress of the
-// sequential loop, two waves raise it by about 12%.
-uint64_t auto_inflight_waves(const pgsgd_graph* g) { return std::max<uint64_t>(1, g->n_nodes / 2048); }
+// Automatic cap.  One wave keeps the sampled path stress of the sequential loop
+// on a 2.6K-node graph and two waves raise it by 12%, but what counts there are
+// the XCDs: each works on its own L2's copy of the coordinates until the
+// launch ends.  On 51K nodes the stress is 1.0 / 1.23 / 1.33 / 1.45 of one
+// wave's on 1 / 2 / 4 / 8 XCDs, and then flat from 8 to 1,024 waves while the
+// time falls as 1 / waves (250 ms at 25 waves, 15 ms at 512).  So below `many`
+// nodes the cap is n_nodes / 2048 waves, one or two per XCD, whose runs repeat
+// to about 3e-4 of the coordinates (one wave: exactly) where more waves would
+// move the layout by 1e-3; from there on n_nodes / 64 waves up to 1,024, and
+// n_nodes / per_wave where that is more.
+constexpr uint32_t kManyWaveNodes = 32768;
+constexpr uint32_t kManyWaveNodesPlain = 16384;  // plain order: runs of 8 waves already differ by 6e-4 to 9e-4
+uint64_t auto_inflight_waves(const pgsgd_graph* g, uint32_t many, uint32_t per_wave) {
+  if (g->n_nodes < many) return std::max<uint64_t>(1, g->n_nodes / 2048);
+  return std::max<uint64_t>(g->n_nodes / per_wave, std::min<uint64_t>(g->n_nodes / 64, 1024));
+}
 
 pgsgd_status layout_grid(pgsgd_graph* g, const pgsgd_params* p, size_t lds, uint64_t n_groups, uint32_t* blocks,
                          uint32_t* threads) {
@@ -752,7 +762,8 @@ pgsgd_status layout_grid(pgsgd_graph* g, const pgsgd_params* p, size_t lds, uint
   pgsgd_status st = layout_blocks_per_cu(g, lds, &bpc);
   if (st) return st;
   uint64_t waves = (uint64_t)g->n_cu * bpc * 4;
-  const uint64_t cap = p->max_inflight_waves ? p->max_inflight_waves : auto_inflight_waves(g);
+  const uint64_t cap =
+      p->max_inflight_waves ? p->max_inflight_waves : auto_inflight_waves(g, kManyWaveNodesPlain, 2048);
   waves = std::min(waves, cap);
   waves = std::min(waves, std::max<uint64_t>(1, n_groups));
   if (waves >= 4ull * g->n_cu) {
@@ -1002,34 +1013,74 @@ pgsgd_status ensure_loss_tiles(pgsgd_graph* g, hipStream_t s) {
   return PGSGD_OK;
 }
 
+// Iterations of a layout by their launch shape: the first eighth, whose steps
+// are full corrections (mu = 1 for every pair), the rest of the iterations
+// with uniform partners, and the all-cooling ones (t >= n_iters / 2).
+enum LocalPhase : uint32_t { kPhaseEarly = 0, kPhaseMixed, kPhaseCooling, kPhases };
+
+LocalPhase local_phase(uint32_t iter, uint32_t n_iters) {
+  return iter >= n_iters / 2 ? kPhaseCooling : iter < n_iters / 8 ? kPhaseEarly : kPhaseMixed;
+}
+
 // Automatic wave cap of the windowed schedule (see kLocalNodesPerWave; the
-// all-cooling iterations use kLocalNodesPerWaveCooling).
-uint64_t auto_local_waves(const pgsgd_graph* g, bool cooling = false) {
+// all-cooling iterations use kLocalNodesPerWaveCooling).  A lost update of the
+// first iterations moves a node by a whole correction, and the next ones do
+// not bring the layout's place on the axes back: with 1,024 waves in them a
+// layout of 148K nodes lands 450 nt further along x than with 72 (6.5e-4 of
+// the coordinates, runs differ by 3.6e-4), with 512 or fewer it does not.
+// Graphs of a batch keep n_nodes / 2048 throughout: several of them share each
+// L2 and what one evicts of another's coordinates other XCDs then see, so a
+// graph's place depends on the pace of its neighbours (with the caps of a
+// single layout a batch took 174 ms instead of 1,080, but its 60K-node graph
+// lay 5e-3 from where it was, runs differing by 1e-3).
+uint64_t auto_local_waves(const pgsgd_graph* g, LocalPhase phase, bool batched) {
   const uint32_t sh = window_shift(g->S);
   const double nodes_w = std::min<double>((double)g->n_nodes,
                                           std::ldexp(1.0, (int)sh) * (double)g->n_nodes * g->n_paths / (double)g->S);
-  const uint64_t w = (uint64_t)(nodes_w / (double)(cooling ? kLocalNodesPerWaveCooling : kLocalNodesPerWave));
-  return std::max<uint64_t>(1, std::min(w, auto_inflight_waves(g)));
+  const uint64_t per = phase == kPhaseCooling ? kLocalNodesPerWaveCooling : kLocalNodesPerWave;
+  uint64_t w = (uint64_t)(nodes_w / (double)per);
+  w = std::min<uint64_t>(w, batched ? g->n_nodes / 2048
+                                    : auto_inflight_waves(g, kManyWaveNodes, kLocalNodesPerWavePlain));
+  if (phase == kPhaseEarly) w = std::min(w, std::max<uint64_t>(g->n_nodes / 2048, kLocalEarlyWaves));
+  return std::max<uint64_t>(1, w);
 }
 
-// Grid of k_layout_local: the in-flight wave cap (params.max_inflight_waves,
+// Grids of k_layout_local: the in-flight wave cap (params.max_inflight_waves,
 // automatic: auto_local_waves) and occupancy give the waves; 256-thread
 // blocks in a multiple of 8 (one share per XCD), or 64-thread blocks below 32
-// waves.  cooling: the grid of the iterations whose terms all have power-law
-// partners (t >= n_iters / 2).
-pgsgd_status local_grid(pgsgd_graph* g, const pgsgd_params* p, size_t lds, uint32_t* blocks, uint32_t* threads,
-                        bool cooling = false) {
+// waves.  Automatic caps of graphs of fewer than 65,536 nodes keep the
+// proportion between the XCDs that n_nodes / 2048 one-wave blocks have (21
+// blocks: three on XCDs 0..4, two on 5..7), so that the same XCDs end their
+// shares last: an XCD writes its copy of the coordinates back when it is
+// done, and the last one's stand.  With equal XCDs a layout of 44.5K nodes lay
+// 2e-3 to 3e-3 away (runs differ by 3e-4), with the proportion kept 6e-4.
+struct LocalGrids {
+  uint32_t blocks[kPhases], threads[kPhases];
+  uint32_t quota_hi[kPhases], quota_lo[kPhases], hi_xcds[kPhases];  // blocks of an XCD's share that take work
+};
+
+pgsgd_status local_grids(pgsgd_graph* g, const pgsgd_params* p, size_t lds, LocalGrids* out, bool batched = false) {
   int nb = 0;
   HIP_TRY(hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, layout_local_kernel(), 256, lds));
-  uint64_t waves = (uint64_t)g->n_cu * (uint64_t)std::max(nb, 1) * 4;
-  const uint64_t cap = p->max_inflight_waves ? p->max_inflight_waves : auto_local_waves(g, cooling);
-  waves = std::max<uint64_t>(1, std::min(waves, cap));
-  if (waves >= 4ull * kXcds) {
-    *threads = 256;
-    *blocks = (uint32_t)((waves / 4) / kXcds * kXcds);
-  } else {
-    *threads = 64;
-    *blocks = (uint32_t)waves;
+  const uint32_t base = g->n_nodes / 2048;
+  for (uint32_t ph = 0; ph < kPhases; ++ph) {
+    uint64_t waves = (uint64_t)g->n_cu * (uint64_t)std::max(nb, 1) * 4;
+    const uint64_t cap = p->max_inflight_waves ? p->max_inflight_waves : auto_local_waves(g, (LocalPhase)ph, batched);
+    waves = std::max<uint64_t>(1, std::min(waves, cap));
+    out->quota_hi[ph] = out->quota_lo[ph] = 0xFFFFFFFFu;
+    out->hi_xcds[ph] = kXcds;
+    const bool wide = waves >= 4ull * kXcds;
+    if (!p->max_inflight_waves && wide && base < 4 * kXcds) {
+      const uint32_t k = std::max<uint32_t>(1, (uint32_t)waves / (4 * base));  // 4-wave blocks for one of base
+      out->hi_xcds[ph] = base % kXcds;
+      out->quota_lo[ph] = base / kXcds * k;
+      out->quota_hi[ph] = out->quota_lo[ph] + k;
+      out->threads[ph] = 256;
+      out->blocks[ph] = kXcds * (base % kXcds ? out->quota_hi[ph] : out->quota_lo[ph]);
+      continue;
+    }
+    out->threads[ph] = wide ? 256 : 64;
+    out->blocks[ph] = (uint32_t)(wide ? (waves / 4) / kXcds * kXcds : waves);
   }
   return PGSGD_OK;
 }
@@ -1037,10 +1088,10 @@ pgsgd_status local_grid(pgsgd_graph* g, const pgsgd_params* p, size_t lds, uint3
 // Scratch, grid and launch arguments of the windowed schedule for graph g
 // (L: the sampling arguments of make_layout_launch).
 pgsgd_status local_plan(pgsgd_graph* g, const pgsgd_params* p, size_t lds, const LayoutLaunch& L, hipStream_t s,
-                        LocalLaunch* W, uint32_t* blocks, uint32_t* threads) {
+                        LocalLaunch* W, LocalGrids* grids, bool batched = false) {
   pgsgd_status st;
   if ((st = ensure_local(g, kLocalStreams, s))) return st;
-  if ((st = local_grid(g, p, lds, blocks, threads))) return st;
+  if ((st = local_grids(g, p, lds, grids, batched))) return st;
   *W = LocalLaunch{};
   W->L = L;
   W->n_win = g->loc_nwin;
@@ -1086,10 +1137,10 @@ ScratchCarve carve_scratch(uint32_t nwin, uint32_t runs, uint32_t xstride) {
 // iterations that read them.
 pgsgd_status local_plan_scratch(pgsgd_graph* g, const pgsgd_params* p, size_t lds, const LayoutLaunch& L,
                                 hipStream_t s, void* scratch, size_t scratch_bytes, LocalLaunch* W,
-                                uint32_t* blocks, uint32_t* threads) {
+                                LocalGrids* grids) {
   pgsgd_status st;
   if ((st = local_host_tables(g, kLocalStreams))) return st;
-  if ((st = local_grid(g, p, lds, blocks, threads))) return st;
+  if ((st = local_grids(g, p, lds, grids))) return st;
   const uint32_t nwin = (uint32_t)g->h_lwpath.size();
   const uint32_t runs = kXcds * kLocalStreams;
   const ScratchCarve c = carve_scratch(nwin, runs, g->h_loc_xstride);
@@ -1123,20 +1174,24 @@ pgsgd_status local_plan_scratch(pgsgd_graph* g, const pgsgd_params* p, size_t ld
 // The layout part of a windowed iteration whose counts and offsets are in W:
 // run counters cleared, layout kernel.  With e_mid set, an event is recorded
 // right before the layout kernel.
-hipError_t local_layout(const LocalLaunch& W, uint32_t blocks, uint32_t threads, hipStream_t s,
+hipError_t local_layout(const LocalLaunch& W, const LocalGrids& grids, LocalPhase phase, hipStream_t s,
                         hipEvent_t e_mid = nullptr) {
   hipError_t e = launch_fill_u32(reinterpret_cast<uint32_t*>(W.queue), 2ull * kXcds * W.streams * 16, 0u, s);
   if (!e && e_mid) e = hipEventRecord(e_mid, s);
-  if (!e) e = launch_layout_local(W, blocks, threads, s);
+  LocalLaunch Wp = W;
+  Wp.quota_hi = grids.quota_hi[phase];
+  Wp.quota_lo = grids.quota_lo[phase];
+  Wp.hi_xcds = grids.hi_xcds[phase];
+  if (!e) e = launch_layout_local(Wp, grids.blocks[phase], grids.threads[phase], s);
   return e;
 }
 
 // One windowed iteration (W.L.iter, cool_all and eta set) on one stream:
 // counts and offsets, then the layout part.
-hipError_t local_iteration(const LocalLaunch& W, uint32_t blocks, uint32_t threads, hipStream_t s,
+hipError_t local_iteration(const LocalLaunch& W, const LocalGrids& grids, LocalPhase phase, hipStream_t s,
                            hipEvent_t e_mid = nullptr) {
   hipError_t e = launch_local_count_scan(W, s);
-  if (!e) e = local_layout(W, blocks, threads, s, e_mid);
+  if (!e) e = local_layout(W, grids, phase, s, e_mid);
   return e;
 }
 
@@ -1187,14 +1242,13 @@ pgsgd_status layout_impl(pgsgd_graph* g, const pgsgd_params* p, float* coords, f
   const bool reuse = p->reuse_factor > 1 || p->step_reduction > 1;
   const bool windowed = resolve_schedule(p) == PGSGD_SCHEDULE_WINDOWED;
   if (tracing && !windowed) return fail(PGSGD_ERR_INVALID_ARG, "recording through the layout loop needs WINDOWED");
-  uint32_t blocks = 0, threads = 256, blocks_c = 0, threads_c = 256;
+  uint32_t blocks = 0, threads = 256;
   LocalLaunch W{};
+  LocalGrids grids{};
   if (windowed && scratch) {
-    if ((st = local_plan_scratch(g, p, lds, L, s, scratch, scratch_bytes, &W, &blocks, &threads))) return st;
-    if ((st = local_grid(g, p, lds, &blocks_c, &threads_c, true))) return st;
+    if ((st = local_plan_scratch(g, p, lds, L, s, scratch, scratch_bytes, &W, &grids))) return st;
   } else if (windowed) {
-    if ((st = local_plan(g, p, lds, L, s, &W, &blocks, &threads))) return st;
-    if ((st = local_grid(g, p, lds, &blocks_c, &threads_c, true))) return st;
+    if ((st = local_plan(g, p, lds, L, s, &W, &grids))) return st;
   } else {
     if ((st = layout_grid(g, p, lds, L.n_groups, &blocks, &threads))) return st;
     L.wave_stride = (uint64_t)blocks * (threads / 64);
@@ -1270,15 +1324,13 @@ pgsgd_status layout_impl(pgsgd_graph* g, const pgsgd_params* p, float* coords, f
       if (it + 1 < last) HIP_TRY(count_into(it + 1, k ^ 1u));
       LocalLaunch Wi = Wset[k];
       Wi.L = L;
-      HIP_TRY(local_layout(Wi, L.cool_all ? blocks_c : blocks, L.cool_all ? threads_c : threads, s,
-                           iter_ms ? ev[e0 + 1] : nullptr));
+      HIP_TRY(local_layout(Wi, grids, local_phase(it, p->n_iters), s, iter_ms ? ev[e0 + 1] : nullptr));
       HIP_TRY(hipEventRecord(g->ev_layout[k], s));
       set_used[k] = true;
       if (iter_ms) HIP_TRY(hipEventRecord(ev[e0 + 2], s));
     } else if (windowed) {
       W.L = L;
-      HIP_TRY(local_iteration(W, L.cool_all ? blocks_c : blocks, L.cool_all ? threads_c : threads, s,
-                              iter_ms ? ev[e0 + 1] : nullptr));
+      HIP_TRY(local_iteration(W, grids, local_phase(it, p->n_iters), s, iter_ms ? ev[e0 + 1] : nullptr));
       if (iter_ms) HIP_TRY(hipEventRecord(ev[e0 + 2], s));
     } else {
       if (iter_ms) HIP_TRY(hipEventRecord(ev[e0 + 1], s));
@@ -1918,7 +1970,7 @@ struct pgsgd_batch {
   bool windowed = false;
   std::vector<pgsgd_graph*> graphs;
   std::vector<LocalLaunch> wl;
-  std::vector<uint32_t> wblocks, wthreads, wblocks_c, wthreads_c;  // grids of mixed and all-cooling iterations
+  std::vector<LocalGrids> wgrids;
   std::vector<std::vector<float>> weta;
   std::vector<std::vector<uint32_t>> branch_graphs;
 
@@ -1999,17 +2051,13 @@ pgsgd_status batch_build_windowed(pgsgd_graph* const* graphs, uint32_t n, const 
     L.g_begin = 0;
     L.g_end = L.n_groups;
     LocalLaunch W;
-    uint32_t blk = 0, thr = 0, blk_c = 0, thr_c = 0;
-    if ((st = local_plan(g, &q, lds, L, cs, &W, &blk, &thr))) break;
-    if ((st = local_grid(g, &q, lds, &blk_c, &thr_c, true))) break;
+    LocalGrids grids;
+    if ((st = local_plan(g, &q, lds, L, cs, &W, &grids, true))) break;
     std::vector<float> eta;
     build_schedule(q.n_iters, eta_max_of(&q, g->d_max), q.eta_min, eta);
     b->graphs.push_back(g);
     b->wl.push_back(W);
-    b->wblocks.push_back(blk);
-    b->wthreads.push_back(thr);
-    b->wblocks_c.push_back(blk_c);
-    b->wthreads_c.push_back(thr_c);
+    b->wgrids.push_back(grids);
     b->weta.push_back(eta);
     b->coords.push_back(coords[k]);
     b->total_terms += L.n_terms;
@@ -2067,8 +2115,7 @@ pgsgd_status batch_build_windowed(pgsgd_graph* const* graphs, uint32_t n, const 
           W.L.iter = it;
           W.L.cool_all = it >= p->n_iters / 2 ? 1u : 0u;
           W.L.eta = b->weta[k][it];
-          e = local_iteration(W, W.L.cool_all ? b->wblocks_c[k] : b->wblocks[k],
-                              W.L.cool_all ? b->wthreads_c[k] : b->wthreads[k], bs[j]);
+          e = local_iteration(W, b->wgrids[k], local_phase(it, p->n_iters), bs[j]);
         }
         if (!e) e = launch_from_work(g->d_work, coords[k], g->n_nodes, g->d_inv, bs[j]);
       }
@@ -2391,8 +2438,7 @@ pgsgd_status autotune_windowed(pgsgd_graph* const* graphs, uint32_t n, const pgs
           W.L.cool_all = it >= p->n_iters / 2 ? 1u : 0u;
           W.L.eta = b->weta[k][std::min<uint32_t>(it, (uint32_t)b->weta[k].size() - 1)];
           if (!r)
-            r = local_iteration(W, W.L.cool_all ? b->wblocks_c[k] : b->wblocks[k],
-                                W.L.cool_all ? b->wthreads_c[k] : b->wthreads[k], bs[j]);
+            r = local_iteration(W, b->wgrids[k], W.L.cool_all ? kPhaseCooling : kPhaseMixed, bs[j]);
         }
       if (!r) r = hipEventRecord(join[j], bs[j]);
       if (!r) r = hipStreamWaitEvent(s, join[j], 0);

@@ -18,7 +18,7 @@ constexpr uint32_t kLocalMaxStreams = 16;
 constexpr uint32_t kLocalGrab = 4;          // items a wave takes from its run's counter at once
 // Automatic wave cap: waves <= nodes_w / 8, nodes_w ~ 2^shift * n_nodes *
 // n_paths / S the node ids a window spans (an XCD's in-flight terms then
-// number about as many as its window's node ids), never above the plain cap.
+// number about as many as its window's node ids), never above the whole-graph cap.
 // With the far-first update order of uniform-partner terms, layout quality on
 // locality-ordered graphs is flat up to this cap.
 constexpr uint64_t kLocalNodesPerWave = 8;
@@ -29,6 +29,11 @@ constexpr uint64_t kLocalNodesPerWave = 8;
 // same pairs of Eq. 2 at m = 3000: nodes_w / 8 left 5.3% more stress, nodes_w /
 // 32 2.6%, for 0.6 s more per layout of 3.5 s).
 constexpr uint64_t kLocalNodesPerWaveCooling = 32;
+// Both caps stay below n_nodes / 512 waves on graphs of more than 524K nodes
+// (1.8M nodes, 32 paths, 15 mixed iterations: 183 ms at 862 waves, 150 at
+// 2,048, 139 at 3,000, 142 at 4,096, the paired stress flat within 1%).
+constexpr uint32_t kLocalNodesPerWavePlain = 512;
+constexpr uint64_t kLocalEarlyWaves = 512;    // cap of the first eighth of the iterations below 1M nodes
 
 // log2 of the window length for S steps: 2^14, halved while there would be
 // fewer than 16 windows (not below 2^6), doubled while there would be more
@@ -64,6 +69,7 @@ struct LocalLaunch {
   uint32_t streams;        // concurrent window streams per XCD
   uint32_t xstride;        // row length of xitem
   uint32_t grab;           // items a wave takes from its stream's counter at once
+  uint32_t quota_hi, quota_lo, hi_xcds;  // blocks of XCDs [0, hi_xcds) and of the others (see LocalGrids)
   uint32_t* wcount;        // [n_win] histogram (zeroed by the scan for the next iteration)
   uint64_t* woff;          // [n_win + 1] first slot of every window (window-id order)
   const uint32_t* worder;  // [n_win] windows in region order

@@ -398,6 +398,7 @@ __device__ __forceinline__ void local_item_reuse(const LocalLaunch& P, const Lds
 
 __global__ __launch_bounds__(256) void k_layout_local(LocalLaunch P) {
   extern __shared__ __align__(16) char lds[];
+  if (blockIdx.x / kXcds >= (blockIdx.x % kXcds < P.hi_xcds ? P.quota_hi : P.quota_lo)) return;
   const LayoutLaunch& L = P.L;
   const LdsView V = lds_view(lds, L.path_slots, L.W);
   lds_fill(V, L.path_off, L.n_paths, L.path_slots, L.zipf, L.guide, L.W);
