@@ -640,14 +640,14 @@ def form_kernels() -> dict:
                 row("k_local_count + k_local_scan", f"chromosome iteration {it}", "term", T,
                     float(it_ms[0]) - float(mk_ms[0]), note_="the rest of the iteration: counting pass (one Philox "
                     "draw per term, ALU bound), scan, fill")
-    # sampled path stress (Eq. 2): two passes over m = 10 pairs per step
+    # sampled path stress (Eq. 2): one pass over m = 10 pairs per step
     P.layout(g, c)
     ms = ev_time(lambda: P.path_stress(g, c, 10, 7))
-    row("k_sps", "chromosome, m = 10", "pair", T, ms / 2, 48,
-        note_="uniform order, per pass: (coordinate copy, two passes, reductions) / 2")
+    row("k_sps", "chromosome, m = 10", "pair", T, ms, 48,
+        note_="uniform order: coordinate copy, the pass over the pairs, reduction")
     ms = ev_time(lambda: P.path_stress(g, c, 10, 7, pairs="uniform_windowed"))
-    row("k_sps_win", "chromosome, m = 10", "pair", T, ms / 2, 48,
-        note_="window-major order, per pass: (copy, segment count and scan, two passes, reductions) / 2")
+    row("k_sps_win", "chromosome, m = 10", "pair", T, ms, 48,
+        note_="window-major order: copy, segment count and scan, the pass over the pairs, reduction")
     del g, c
     torch.cuda.empty_cache()
 

@@ -402,16 +402,15 @@ typedef struct {
   double mean;       /* sampled path stress: mean of ((|v_i - v_j| - d)/d)^2 */
   double ci_lo;      /* mean - 1.96 sigma / sqrt(n) */
   double ci_hi;      /* mean + 1.96 sigma / sqrt(n) */
-  double stddev;     /* sigma from a second pass: sqrt(sum (s - mean)^2 / (n - 1)) */
-  double sum;        /* sum of the stress terms (pass 1) */
-  double sumsq_dev;  /* sum of squared deviations (pass 2) */
+  double stddev;     /* sigma: sqrt(sum (s - mean)^2 / (n - 1)) */
+  double sum;        /* sum of the stress terms */
+  double sumsq_dev;  /* sum of squared deviations from the mean */
   uint64_t n_valid;  /* pairs with d > 0 */
   uint64_t n_skipped;/* pairs with d = 0 (left out of the mean) */
 } pgsgd_stress_result;
 
 /*
- * Sampled path stress with its 95% confidence interval (Eq. 2; two passes, the
- * second for sigma).  Path p receives exactly pairs_per_step * |p| pairs; pair
+ * Sampled path stress with its 95% confidence interval (Eq. 2).  Path p receives exactly pairs_per_step * |p| pairs; pair
  * q of path p (q in [m*off[p], m*off[p+1])) draws Philox stream 1 at counter
  * q: i = start + floor(u64 * |p| / 2^64), j = start + floor(r2 * |p| / 2^32),
  * e_i = bit 0, e_j = bit 1 of r3.  All paths are pooled.  Stress terms are

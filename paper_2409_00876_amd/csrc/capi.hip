@@ -3,7 +3,7 @@
 // Responsibilities: graph validation (all on the host, before any device
 // work), packing of path steps into 16-byte records and their chunked upload
 // through pinned staging buffers, the learning-rate schedule and power-law
-// table, launch shapes, the two-pass sampled path stress, the differentiable
+// table, launch shapes, the sampled path stress, the differentiable
 // loss, and the batched form (HIP-graph capture and autotuning).
 #include <hip/hip_runtime.h>
 
@@ -178,7 +178,7 @@ struct pgsgd_graph {
   uint64_t* d_part_skip = nullptr;
   double* d_out_f = nullptr;    // [8]
   uint64_t* d_out_n = nullptr;  // [4]
-  double* d_mean = nullptr;     // [4]
+  SpsHostSums* h_sums = nullptr;  // pinned, on first use
   float2* d_work2 = nullptr;    // a second layout's working copy (pgsgd_path_stress_compare, on first use)
   size_t device_bytes = 0;
   std::unordered_map<void*, size_t> alloc_bytes;  // size of every lazily allocated buffer
@@ -224,7 +224,7 @@ struct pgsgd_graph {
     DeviceGuard g(device);
     (void)hipDeviceSynchronize();
     for (void* p : {(void*)d_rec, (void*)d_path_off, (void*)d_first, (void*)d_work, (void*)d_inv, (void*)d_zipf, (void*)d_guide, (void*)d_part_f,
-                    (void*)d_part_n, (void*)d_part_skip, (void*)d_out_f, (void*)d_out_n, (void*)d_mean, (void*)d_work2, (void*)d_lcount, (void*)d_loff, (void*)d_lxitem, (void*)d_lqueue, (void*)d_lorder,
+                    (void*)d_part_n, (void*)d_part_skip, (void*)d_out_f, (void*)d_out_n, (void*)d_work2, (void*)d_lcount, (void*)d_loff, (void*)d_lxitem, (void*)d_lqueue, (void*)d_lorder,
                     (void*)d_lsbeg, (void*)d_lwpath, (void*)d_lcount2, (void*)d_loff2, (void*)d_lxitem2,
                     (void*)d_lqueue2, (void*)d_tile_seg, (void*)d_tile_off, (void*)d_tile_base, (void*)d_tile_queue})
       if (p) (void)hipFree(p);
@@ -232,6 +232,7 @@ struct pgsgd_graph {
       for (void* p : {(void*)t->start, (void*)t->path, (void*)t->wseg, (void*)t->count, (void*)t->off,
                       (void*)t->sbeg, (void*)t->xitem, (void*)t->queue})
         if (p) (void)hipFree(p);
+    if (h_sums) (void)hipHostFree(h_sums);
     for (hipEvent_t e : {ev_start, ev_count[0], ev_count[1], ev_layout[0], ev_layout[1]})
       if (e) (void)hipEventDestroy(e);
     if (count_stream) (void)hipStreamDestroy(count_stream);
@@ -553,7 +554,7 @@ pgsgd_status pgsgd_graph_create_ex(uint32_t n_nodes, const uint32_t* node_len, u
   }
   // the buffers allocated below, checked against PGSGD_MAX_DEVICE_BYTES before any device work
   const uint64_t need = 16ull * std::max<uint64_t>(S, 1) + 8ull * (n_paths + 1) + 8ull * std::max(n_nodes, 1u) +
-                        16ull * std::max(n_nodes, 1u) + 40ull * kStressBlocks + 8 * 8 + 4 * 8 + 4 * 8 + 4ull * 65536 +
+                        16ull * std::max(n_nodes, 1u) + 40ull * kStressBlocks + 8 * 8 + 4 * 8 + 4ull * 65536 +
                         2ull * (kGuideSize + 1) + (perm.empty() ? 0 : 4ull * n_nodes);
   const uint64_t cap = device_byte_cap();
   if (cap && need > cap)
@@ -599,7 +600,6 @@ pgsgd_status pgsgd_graph_create_ex(uint32_t n_nodes, const uint32_t* node_len, u
   if ((st = dev_alloc(g, &g->d_part_skip, kStressBlocks))) return bail(st);
   if ((st = dev_alloc(g, &g->d_out_f, 8))) return bail(st);
   if ((st = dev_alloc(g, &g->d_out_n, 4))) return bail(st);
-  if ((st = dev_alloc(g, &g->d_mean, 4))) return bail(st);
   if ((st = dev_alloc(g, &g->d_zipf, 65536))) return bail(st);
   if ((st = dev_alloc(g, &g->d_guide, kGuideSize + 1))) return bail(st);
   if (!perm.empty() && (st = dev_alloc(g, &g->d_inv, n_nodes))) return bail(st);
@@ -1683,6 +1683,41 @@ pgsgd_status pgsgd_path_stress_outliers(pgsgd_graph* g, const float* coords, uin
 
 namespace {
 
+// A number as the unevaluated sum of two doubles (about 106 bits), for the
+// differences of the sums of squares.  A sum that is infinite or NaN is held
+// in hi alone.
+struct Twice {
+  double hi = 0.0, lo = 0.0;
+  static Twice of(double x, double y) {
+    const double s = x + y, b = s - x;
+    const double e = (x - (s - b)) + (y - b);
+    return std::isfinite(x) ? Twice{s, e} : Twice{x, 0.0};
+  }
+  Twice plus(const Twice& o) const {
+    const Twice t = of(hi, o.hi);
+    return of(t.hi, t.lo + (lo + o.lo));
+  }
+  Twice times(double x) const {
+    const double p = hi * x;
+    return of(p, std::fma(hi, x, -p) + lo * x);
+  }
+  Twice over(double x) const {
+    const double q = hi / x;
+    return of(q, (std::fma(-q, x, hi) + lo) / x);
+  }
+  double value() const { return hi + lo; }
+  // as a sum of squares: what rounds below 0 is 0
+  double square_sum() const { return value() < 0.0 ? 0.0 : value(); }
+};
+
+// sum (x - mean)^2 over n values from their sum and the sum of their squares
+double squares_about_mean(const Twice& sum, const Twice& squares, uint64_t n) {
+  if (!n) return 0.0;
+  if (!std::isfinite(sum.value())) return std::nan("");  // as inf - inf of its terms
+  const Twice mean = sum.over((double)n);
+  return squares.plus(sum.times(-mean.hi)).plus(sum.times(-mean.lo)).square_sum();
+}
+
 pgsgd_status path_stress_impl(pgsgd_graph* g, const float* coords, uint32_t m, uint64_t seed, uint32_t graph_id,
                               uint32_t pair_mode, double zipf_theta, uint32_t zipf_window, pgsgd_stress_result* out,
                               void* stream, const OutlierSink* sink, const float* coords_b,
@@ -1745,73 +1780,53 @@ pgsgd_status path_stress_impl(pgsgd_graph* g, const float* coords, uint32_t m, u
       return fail(PGSGD_ERR_UNSUPPORTED, "pairs_per_step %u too large for 32-bit segment counts", m);
     W = sps_win_launch(g, g->sps, P, kStreamSpsSlot, graph_id, 0);
   }
-  auto pass = [&](int k, const double* mean_dev, uint64_t* part_n, uint64_t* part_skip) -> hipError_t {
-    return windowed ? launch_sps_win_pass(W, k, mean_dev, g->d_part_f, part_n, part_skip, kStressBlocks, s)
-                    : launch_sps_pass(P, k, mode, mean_dev, g->d_part_f, part_n, part_skip, s);
-  };
-  auto reduce = [&](uint32_t part, double* out_f) -> hipError_t {  // sum of one of the three partial arrays
-    return launch_reduce_parts(g->d_part_f + (size_t)part * kStressBlocks, nullptr, nullptr, kStressBlocks, out_f,
-                               nullptr, nullptr, nullptr, nullptr, s);
-  };
+  if (!g->h_sums) HIP_TRY(hipHostMalloc((void**)&g->h_sums, sizeof(SpsHostSums), hipHostMallocDefault));
   HIP_TRY(launch_to_work(coords, g->d_work, g->n_nodes, g->d_inv, s));
   if (coords_b) HIP_TRY(launch_to_work(coords_b, g->d_work2, g->n_nodes, g->d_inv, s));
-  if (windowed) HIP_TRY(launch_sps_win_count_scan(W, s));
-  HIP_TRY(pass(1, nullptr, g->d_part_n, g->d_part_skip));
-  HIP_TRY(launch_reduce_parts(g->d_part_f, g->d_part_n, g->d_part_skip, kStressBlocks, g->d_out_f, g->d_out_n,
-                              g->d_mean, nullptr, nullptr, s));
-  double sum_b = 0.0;
-  if (coords_b) {  // pass 2 needs both means and the ratio: one round trip
-    HIP_TRY(reduce(1, g->d_out_f + 2));
-    double f0[3];
-    uint64_t n0;
-    HIP_TRY(hipMemcpyAsync(f0, g->d_out_f, sizeof(f0), hipMemcpyDeviceToHost, s));
-    HIP_TRY(hipMemcpyAsync(&n0, g->d_out_n, sizeof(n0), hipMemcpyDeviceToHost, s));
-    HIP_TRY(hipStreamSynchronize(s));
-    sum_b = f0[2];
-    const double mean3[3] = {n0 ? f0[0] / (double)n0 : 0.0, n0 ? sum_b / (double)n0 : 0.0,
-                             sum_b > 0.0 ? f0[0] / sum_b : 0.0};
-    HIP_TRY(hipMemcpyAsync(g->d_mean, mean3, sizeof(mean3), hipMemcpyHostToDevice, s));
-    HIP_TRY(hipStreamSynchronize(s));  // mean3 lives on this stack frame
+  uint32_t parts = 0;
+  if (windowed) {
+    HIP_TRY(launch_sps_win_count_scan(W, s));
+    HIP_TRY(launch_sps_win(W, g->d_part_f, g->d_part_n, g->d_part_skip, &parts, s));
+  } else {
+    HIP_TRY(launch_sps(P, mode, g->d_part_f, g->d_part_n, g->d_part_skip, &parts, s));
   }
-  HIP_TRY(pass(2, g->d_mean, nullptr, nullptr));
-  HIP_TRY(reduce(0, g->d_out_f + 1));
-  if (coords_b) {
-    HIP_TRY(reduce(1, g->d_out_f + 3));
-    HIP_TRY(reduce(2, g->d_out_f + 4));
-  }
-  double f[5];
-  uint64_t n[2];
-  HIP_TRY(hipMemcpyAsync(f, g->d_out_f, sizeof(f), hipMemcpyDeviceToHost, s));
-  HIP_TRY(hipMemcpyAsync(n, g->d_out_n, sizeof(n), hipMemcpyDeviceToHost, s));
+  HIP_TRY(launch_reduce_sps(P, g->d_part_f, g->d_part_n, g->d_part_skip, parts, g->h_sums, s));
   HIP_TRY(hipStreamSynchronize(s));
-  out->sum = f[0];
-  out->sumsq_dev = f[1];
-  out->n_valid = n[0];
-  out->n_skipped = n[1];
-  out->mean = n[0] ? f[0] / (double)n[0] : 0.0;
-  out->stddev = n[0] > 1 ? std::sqrt(f[1] / (double)(n[0] - 1)) : 0.0;
-  const double half = n[0] ? 1.96 * out->stddev / std::sqrt((double)n[0]) : 0.0;
+  const SpsHostSums& h = *g->h_sums;
+  const uint64_t nv = h.n[0];
+  const Twice a = Twice::of(h.hi[0], h.lo[0]), aa = Twice::of(h.hi[1], h.lo[1]);
+  auto sd = [&](double ss) { return nv > 1 ? std::sqrt(ss / (double)(nv - 1)) : 0.0; };
+  out->sum = a.value();
+  out->sumsq_dev = squares_about_mean(a, aa, nv);
+  out->n_valid = nv;
+  out->n_skipped = h.n[1];
+  out->mean = nv ? out->sum / (double)nv : 0.0;
+  out->stddev = sd(out->sumsq_dev);
+  const double half = nv ? 1.96 * out->stddev / std::sqrt((double)nv) : 0.0;
   out->ci_lo = out->mean - half;
   out->ci_hi = out->mean + half;
   if (cmp) {
-    const uint64_t nv = n[0];
+    const Twice b = Twice::of(h.hi[2], h.lo[2]), bb = Twice::of(h.hi[3], h.lo[3]), ab = Twice::of(h.hi[4], h.lo[4]);
+    const double sum_b = b.value();
     cmp->mean_a = out->mean;
     cmp->mean_b = nv ? sum_b / (double)nv : 0.0;
-    cmp->ratio = sum_b > 0.0 ? f[0] / sum_b : 0.0;
+    cmp->ratio = sum_b > 0.0 ? out->sum / sum_b : 0.0;
     cmp->sd_a = out->stddev;
-    cmp->sd_b = nv > 1 ? std::sqrt(f[3] / (double)(nv - 1)) : 0.0;
-    cmp->sd_diff = nv > 1 ? std::sqrt(f[4] / (double)(nv - 1)) : 0.0;
-    const double h = (nv && cmp->mean_b > 0.0) ? 1.96 * cmp->sd_diff / (std::sqrt((double)nv) * cmp->mean_b) : 0.0;
-    cmp->ratio_ci_lo = cmp->ratio - h;
-    cmp->ratio_ci_hi = cmp->ratio + h;
-    cmp->sum_a = f[0];
+    cmp->sd_b = sd(squares_about_mean(b, bb, nv));
+    // sum (a - R b)^2 = sum a^2 - 2 R sum a b + R^2 sum b^2
+    const double R = cmp->ratio;
+    const bool finite = std::isfinite(out->sum) && std::isfinite(sum_b);
+    cmp->sd_diff =
+        sd(finite ? aa.plus(ab.times(-2.0 * R)).plus(bb.times(R).times(R)).square_sum() : std::nan(""));
+    const double hw = (nv && cmp->mean_b > 0.0) ? 1.96 * cmp->sd_diff / (std::sqrt((double)nv) * cmp->mean_b) : 0.0;
+    cmp->ratio_ci_lo = cmp->ratio - hw;
+    cmp->ratio_ci_hi = cmp->ratio + hw;
+    cmp->sum_a = out->sum;
     cmp->sum_b = sum_b;
     cmp->n_valid = nv;
-    cmp->n_skipped = n[1];
+    cmp->n_skipped = h.n[1];
   }
-  if (sink) {
-    HIP_TRY(hipMemcpy(sink->n_host, P.out_count, sizeof(uint64_t), hipMemcpyDeviceToHost));
-  }
+  if (sink) *sink->n_host = h.outliers;
   return ok();
 }
 
@@ -1835,8 +1850,7 @@ pgsgd_status pgsgd_path_stress_exact(pgsgd_graph* g, const float* coords, double
   P.work = g->d_work;
   HIP_TRY(launch_to_work(coords, g->d_work, g->n_nodes, g->d_inv, s));
   HIP_TRY(launch_path_stress_exact(P, g->d_part_f, g->d_part_n, s));
-  HIP_TRY(launch_reduce_parts(g->d_part_f, g->d_part_n, nullptr, kStressBlocks, g->d_out_f, g->d_out_n, nullptr,
-                              nullptr, nullptr, s));
+  HIP_TRY(launch_reduce_parts(g->d_part_f, g->d_part_n, kStressBlocks, g->d_out_f, g->d_out_n, nullptr, nullptr, s));
   double f = 0.0;
   uint64_t n = 0;
   HIP_TRY(hipMemcpyAsync(&f, g->d_out_f, sizeof(f), hipMemcpyDeviceToHost, s));
@@ -1881,8 +1895,7 @@ pgsgd_status pgsgd_stress_forward(pgsgd_graph* g, const pgsgd_params* p, const f
   } else {
     HIP_TRY(launch_stress_fwd(P, g->d_part_f, g->d_part_n, s));
   }
-  HIP_TRY(launch_reduce_parts(g->d_part_f, g->d_part_n, nullptr, parts, nullptr, nullptr, nullptr, loss_dev,
-                              n_valid_dev, s));
+  HIP_TRY(launch_reduce_parts(g->d_part_f, g->d_part_n, parts, nullptr, nullptr, loss_dev, n_valid_dev, s));
   return ok();
 }
 

@@ -17,7 +17,7 @@ struct StressLaunch {
   const float* coords;
   const float2* work;      // interleaved copy of coords (sampled path stress only)
   const uint32_t* inv;     // renumbered graph: caller id of every device node id (else NULL)
-  const float2* work2;     // a second layout's interleaved copy: the SPS passes evaluate it on the same pairs
+  const float2* work2;     // a second layout's interleaved copy: the SPS evaluates it on the same pairs
   const uint64_t* path_off;
   const uint32_t* zipf;
   const uint16_t* guide;
@@ -32,7 +32,7 @@ struct StressLaunch {
   uint32_t word2;          // counter word 2
   uint32_t c3;
   uint32_t k0, k1;
-  // pass 1 of the sampled path stress, when out_count is set: pairs with stress
+  // the sampled path stress, when out_count is set: pairs with stress
   // above out_threshold are appended (i, j, e_i | e_j << 1, stress; the first
   // out_max kept) and counted in *out_count
   uint64_t* out_count;
@@ -44,17 +44,28 @@ struct StressLaunch {
   double* out_s;
 };
 
-// SPS: pass 1 writes per-block (sum, n_valid, n_skipped); pass 2 per-block sum
-// of squared deviations from mean_dev.  Final reductions write to out.
 constexpr uint32_t kStressBlocks = 2048;
 constexpr uint32_t kStressThreads = 256;
-hipError_t launch_sps_pass(const StressLaunch& P, int pass, int mode, const double* mean_dev, double* part_f,
-                           uint64_t* part_n, uint64_t* part_skip, hipStream_t s);
-// out_f[0] = sum of part_f; out_n[0..1] = sums of part_n / part_skip;
-// if mean_out: mean_out[0] = out_f[0] / out_n[0].
-hipError_t launch_reduce_parts(const double* part_f, const uint64_t* part_n, const uint64_t* part_skip,
-                               uint32_t n_parts, double* out_f, uint64_t* out_n, double* mean_out,
-                               float* loss_out, uint64_t* n_valid_out, hipStream_t s);
+// Grids of the sampled path stress, full occupancy each: 2 sums of two doubles
+// per block (one layout) or 5 (two layouts), within the 3 * kStressBlocks
+// doubles of partials that a graph holds.
+constexpr uint32_t kSpsBlocks = 1024, kSpsThreads = 512;
+constexpr uint32_t kSpsPairBlocks = 512, kSpsPairThreads = 1024;
+static_assert(4 * kSpsBlocks <= 3 * kStressBlocks && 10 * kSpsPairBlocks <= 3 * kStressBlocks, "partials");
+// The sums of one evaluation on the host: hi + lo of the sums of a, a^2 and, for
+// two layouts, b, b^2, a b; the valid and skipped pairs; the outliers found.
+struct SpsHostSums {
+  double hi[5], lo[5];
+  uint64_t n[2];
+  uint64_t outliers;
+};
+hipError_t launch_sps(const StressLaunch& P, int mode, double* part_f, uint64_t* part_n, uint64_t* part_skip,
+                      uint32_t* n_parts, hipStream_t s);
+hipError_t launch_reduce_sps(const StressLaunch& P, const double* part_f, const uint64_t* part_n,
+                             const uint64_t* part_skip, uint32_t n_parts, SpsHostSums* out, hipStream_t s);
+// out_f[0] = sum of part_f; out_n[0] = sum of part_n; loss_out[0] their ratio.
+hipError_t launch_reduce_parts(const double* part_f, const uint64_t* part_n, uint32_t n_parts, double* out_f,
+                               uint64_t* out_n, float* loss_out, uint64_t* n_valid_out, hipStream_t s);
 // Sampled path stress in window-major order: segments (the windows of
 // 2^win_shift steps cut at path boundaries, in step order) get the counts of
 // the plain pair draws that fall in them; each segment's slots draw their pair
@@ -77,9 +88,8 @@ struct SpsWinLaunch {
   uint64_t loss_pairs;        // the loss's window-major pairs (reading R22): the number of plain pairs; 0 = SPS
 };
 hipError_t launch_sps_win_count_scan(const SpsWinLaunch& W, hipStream_t s);
-// grid: blocks a multiple of kXcds
-hipError_t launch_sps_win_pass(const SpsWinLaunch& W, int pass, const double* mean_dev, double* part_f,
-                               uint64_t* part_n, uint64_t* part_skip, uint32_t blocks, hipStream_t s);
+hipError_t launch_sps_win(const SpsWinLaunch& W, double* part_f, uint64_t* part_n, uint64_t* part_skip,
+                          uint32_t* n_parts, hipStream_t s);
 // The loss (reading R22) over the segments' slots counted with loss_pairs:
 // forward per-block sums (grid: blocks a multiple of kXcds), and the adjoint
 // added into the planar gradient.

@@ -1,11 +1,13 @@
-// Stress kernels for gfx950: the sampled path stress of Eq. 2 (two passes for
-// the CI95), the differentiable loss and its adjoint, the initial layout and a
+// Stress kernels for gfx950: the sampled path stress of Eq. 2 with its CI95
+// (one pass), the differentiable loss and its adjoint, the initial layout and a
 // fused Adam step.
 //
 // Stress terms are evaluated in FP64 from the float32 coordinates with FMA
 // contraction off, so each term is the exactly rounded value of
 // ((|v_i - v_j| - d)/d)^2; block partials are FP64 and reduced in a fixed
 // order, so results are deterministic for a given launch shape.
+#include <algorithm>
+
 #include "device.h"
 #include "internal.h"
 #include "stress.h"
@@ -75,7 +77,7 @@ __device__ __forceinline__ double stress_work(const float2* __restrict__ W, uint
   return stress_xy(va.x, va.y, vb.x, vb.y, d);
 }
 
-// Pass 1 with outlier collection: a pair whose stress exceeds the threshold is
+// Outlier collection: a pair whose stress exceeds the threshold is
 // appended (slot from one atomic; the first out_max are kept).
 __device__ __forceinline__ void keep_outlier(const StressLaunch& P, uint64_t i, uint64_t j, uint32_t e, double st) {
   if (!P.out_count || !(st > P.out_threshold)) return;
@@ -88,47 +90,110 @@ __device__ __forceinline__ void keep_outlier(const StressLaunch& P, uint64_t i, 
   }
 }
 
-// A second layout (P.work2) on the same pair: pass 1 sums its stress into acc2;
-// pass 2 (mean_dev = mean_a, mean_b, R) sums (s_b - mean_b)^2 into acc2 and
-// (s_a - R s_b)^2 into acc3.
-__device__ __forceinline__ void paired_terms(const StressLaunch& P, int pass, const double* mean_dev, uint64_t a,
-                                             uint64_t b, double d, double st, double& acc2, double& acc3) {
+// A running sum with its rounding errors: hi is the plain FP64 sum, lo the sum
+// of what its additions rounded away (two-sum), so hi + lo carries about twice
+// FP64's digits.  hi is never renormalised, so infinities and NaN come out of
+// it as they would of the plain sum.
+struct Sum2 {
+  double hi = 0.0, lo = 0.0;
+  __device__ __forceinline__ void add(double x) {
 #pragma clang fp contract(off)
-  const double sb = stress_work(P.work2, a, b, d);
-  if (pass == 1) {
-    acc2 += sb;
-  } else {
-    acc2 += (sb - mean_dev[1]) * (sb - mean_dev[1]);
-    acc3 += (st - mean_dev[2] * sb) * (st - mean_dev[2] * sb);
+    const double s = hi + x, b = s - hi;
+    lo += (hi - (s - b)) + (x - b);
+    hi = s;
   }
-}
+  __device__ __forceinline__ void add_product(double x, double y) {
+#pragma clang fp contract(off)
+    const double p = x * y;
+    add(p);
+    lo += __builtin_fma(x, y, -p);
+  }
+  __device__ __forceinline__ void add(const Sum2& o) {
+    add(o.hi);
+    lo += o.lo;
+  }
+};
 
-// Per-block partial sums: part_f[blockIdx.x] = acc, and for a paired
-// evaluation part_f[gridDim.x + blockIdx.x] = acc2, part_f[2 gridDim.x + blockIdx.x] = acc3.
-__device__ __forceinline__ void write_parts(const StressLaunch& P, double acc, double acc2, double acc3, uint64_t nv,
-                                            uint64_t ns, double* red_f, uint64_t* red_n, double* part_f,
-                                            uint64_t* part_n, uint64_t* part_skip) {
-  acc = block_sum(acc, red_f);
-  if (P.work2) {
-    acc2 = block_sum(acc2, red_f);
-    acc3 = block_sum(acc3, red_f);
-  }
-  nv = block_sum(nv, red_n);
-  ns = block_sum(ns, red_n);
-  if (threadIdx.x == 0) {
-    part_f[blockIdx.x] = acc;
-    if (P.work2) {
-      part_f[gridDim.x + blockIdx.x] = acc2;
-      part_f[2 * gridDim.x + blockIdx.x] = acc3;
+// What one pass over the pairs leaves of the sampled path stress: the sums and
+// the sums of squares and products of the stress a of a layout and, kPair, of
+// the stress b of a second one on the same pairs.  The deviations about a mean
+// or a ratio, sum (a - mean)^2 and sum (a - R b)^2, follow from them on the
+// host; the sums carry enough digits for the cancellation (equal stresses give
+// 0), which a second pass over the pairs paid for before.
+constexpr size_t kSpsLds = (5 * 2 + 2) * 16 * 8;
+
+template <bool kPair>
+struct SpsAcc {
+  static constexpr uint32_t kSums = kPair ? 5 : 2;  // a, aa[, b, bb, ab]
+  Sum2 v[kSums];
+  uint64_t nv = 0, ns = 0;
+
+  __device__ __forceinline__ void take(const StressLaunch& P, uint64_t a, uint64_t b, double d, double st) {
+    ++nv;
+    v[0].add(st);
+    v[1].add_product(st, st);
+    if constexpr (kPair) {
+      const double sb = stress_work(P.work2, a, b, d);
+      v[2].add(sb);
+      v[3].add_product(sb, sb);
+      v[4].add_product(st, sb);
     }
-    if (part_n) part_n[blockIdx.x] = nv;
-    if (part_skip) part_skip[blockIdx.x] = ns;
   }
-}
+
+  // Block sums into column `block` of the rows (row q * 2 + {hi, lo}) of part_f
+  // and into the counts, by way of the block's dynamic LDS (kSpsLds bytes),
+  // whose tables are no longer read.
+  __device__ __forceinline__ void write(char* lds, uint32_t block, uint32_t stride, double* __restrict__ part_f,
+                                        uint64_t* __restrict__ part_n, uint64_t* __restrict__ part_skip) {
+    double(*red)[2][16] = reinterpret_cast<double(*)[2][16]>(lds);  // [kSums]
+    uint64_t(*red_n)[16] = reinterpret_cast<uint64_t(*)[16]>(lds + kSums * 2 * 16 * 8);
+    __syncthreads();
+    const uint32_t lane = threadIdx.x & 63u, w = threadIdx.x >> 6, nw = blockDim.x >> 6;
+#pragma unroll
+    for (uint32_t q = 0; q < kSums; ++q) {
+#pragma unroll
+      for (int o = 32; o > 0; o >>= 1) {
+        Sum2 x;
+        x.hi = __shfl_xor(v[q].hi, o, 64);
+        x.lo = __shfl_xor(v[q].lo, o, 64);
+        v[q].add(x);
+      }
+      if (lane == 0) {
+        red[q][0][w] = v[q].hi;
+        red[q][1][w] = v[q].lo;
+      }
+    }
+    nv = wave_sum(nv);
+    ns = wave_sum(ns);
+    if (lane == 0) {
+      red_n[0][w] = nv;
+      red_n[1][w] = ns;
+    }
+    __syncthreads();
+    if (threadIdx.x < kSums) {
+      Sum2 t;
+      for (uint32_t k = 0; k < nw; ++k) {
+        t.add(red[threadIdx.x][0][k]);
+        t.lo += red[threadIdx.x][1][k];
+      }
+      part_f[(size_t)(2 * threadIdx.x) * stride + block] = t.hi;
+      part_f[(size_t)(2 * threadIdx.x + 1) * stride + block] = t.lo;
+    } else if (threadIdx.x - kSums < 2) {
+      uint64_t t = 0;
+      for (uint32_t k = 0; k < nw; ++k) t += red_n[threadIdx.x - kSums][k];
+      (threadIdx.x == kSums ? part_n : part_skip)[block] = t;
+    }
+  }
+};
 
 // ---------------------------------------------------------------------------
-// Sampled path stress: thread-strided over steps s; step s owns pairs
-// q = m*s .. m*s+m-1, which all belong to the path of s.
+// Sampled path stress; step s owns pairs q = m*s .. m*s+m-1, which all belong
+// to the path of s.  A thread takes `per` consecutive pairs of a step: per = m
+// on graphs with a step for every thread of the chip, fewer on smaller ones,
+// whose few steps would otherwise leave it idle while each thread waits for
+// one pair's memory after another (14K steps, m = 100: a call took 198 us with
+// 57 busy blocks and a second pass, 43 us with chunks of 3 pairs and one pass;
+// 1.04e6 steps in 16 paths, m = 10, two layouts: 3.9 and 1.9 ms).
 // ---------------------------------------------------------------------------
 __device__ __forceinline__ void fill_loss_lds(char* lds, const StressLaunch& P, uint64_t*& off, uint32_t*& zipf,
                                               uint16_t*& guide);
@@ -136,15 +201,15 @@ __device__ __forceinline__ void fill_loss_lds(char* lds, const StressLaunch& P, 
 // mode 0: uniform partner in the path (Eq. 2); mode 1: the power-law partner
 // of the layout's cooling phase (same draw words; no partner in a single-step
 // path: the pair is skipped).
-__global__ __launch_bounds__(256) void k_sps(StressLaunch P, int pass, int mode, const double* __restrict__ mean_dev,
-                                             double* __restrict__ part_f, uint64_t* __restrict__ part_n,
-                                             uint64_t* __restrict__ part_skip) {
+template <bool kPair>
+__global__ __launch_bounds__(kPair ? 1024 : 512) void k_sps(StressLaunch P, int mode, uint32_t per, uint32_t chunks,
+                                                            double* __restrict__ part_f,
+                                                            uint64_t* __restrict__ part_n,
+                                                            uint64_t* __restrict__ part_skip) {
   extern __shared__ __align__(16) char lds[];
   uint64_t* off;
   uint32_t* zipf;
   uint16_t* guide;
-  __shared__ double red_f[16];
-  __shared__ uint64_t red_n[16];
   if (mode == 1) {
     fill_loss_lds(lds, P, off, zipf, guide);
   } else {
@@ -154,21 +219,23 @@ __global__ __launch_bounds__(256) void k_sps(StressLaunch P, int pass, int mode,
     fill_offsets(off, P);
   }
   __syncthreads();
-  const double mean = pass == 2 ? mean_dev[0] : 0.0;
-  double acc = 0.0, acc2 = 0.0, acc3 = 0.0;
-  uint64_t nv = 0, ns = 0;
+  SpsAcc<kPair> acc;
   const uint64_t stride = (uint64_t)gridDim.x * blockDim.x;
-  for (uint64_t s = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; s < P.S; s += stride) {
+  const uint64_t total = P.S * chunks;  // at most the threads of the grid when chunks > 1
+  for (uint64_t u = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; u < total; u += stride) {
+    const uint32_t chunk = chunks > 1 ? (uint32_t)u / (uint32_t)P.S : 0u;
+    const uint64_t s = u - (uint64_t)chunk * P.S;
     const uint32_t p = find_path(off, P.path_top, s);
     const uint64_t start = off[p], len = off[p + 1] - start;
-    for (uint32_t k = 0; k < P.m; ++k) {
+    const uint32_t k_end = min(P.m, (chunk + 1) * per);
+    for (uint32_t k = chunk * per; k < k_end; ++k) {
       const uint64_t q = (uint64_t)P.m * s + k;
       const Rand4 r = philox10((uint32_t)q, (uint32_t)(q >> 32), 0u, P.c3, P.k0, P.k1);
       const uint64_t i = start + mulhi64((uint64_t)r.r0 | ((uint64_t)r.r1 << 32), len);
       uint64_t j;
       if (mode == 1) {
         if (!partner_power_law(i, start, len, r.r2, r.r3, zipf, guide, P.W, j)) {
-          ++ns;
+          ++acc.ns;
           continue;
         }
       } else {
@@ -177,22 +244,15 @@ __global__ __launch_bounds__(256) void k_sps(StressLaunch P, int pass, int mode,
       uint64_t a, b;
       double d;
       if (!pair_terms(P.rec, i, j, r.r3 & 1u, (r.r3 >> 1) & 1u, a, b, d)) {
-        ++ns;
+        ++acc.ns;
         continue;
       }
       const double st = stress_work(P.work, a, b, d);
-      if (pass == 1) {
-        acc += st;
-        ++nv;
-        keep_outlier(P, i, j, r.r3 & 3u, st);
-      } else {
-#pragma clang fp contract(off)
-        acc += (st - mean) * (st - mean);
-      }
-      if (P.work2) paired_terms(P, pass, mean_dev, a, b, d, st, acc2, acc3);
+      keep_outlier(P, i, j, r.r3 & 3u, st);
+      acc.take(P, a, b, d, st);
     }
   }
-  write_parts(P, acc, acc2, acc3, nv, ns, red_f, red_n, part_f, part_n, part_skip);
+  acc.write(lds, blockIdx.x, gridDim.x, part_f, part_n, part_skip);
 }
 
 // ---------------------------------------------------------------------------
@@ -322,25 +382,23 @@ __global__ __launch_bounds__(1024) void k_sps_win_scan(SpsWinLaunch W) {
   if (threadIdx.x < 2 * kXcds) W.queue[(size_t)threadIdx.x * 16] = 0;
 }
 
-// One pass: the waves of XCD x take the items of run x from its counter,
+// The waves of XCD x take the items of run x from its counter,
 // kSpsGrab at a time; every wave leaves once the counter has passed the run's
 // last item.
-__global__ __launch_bounds__(256) void k_sps_win(SpsWinLaunch W, int pass, const double* __restrict__ mean_dev,
-                                                 double* __restrict__ part_f, uint64_t* __restrict__ part_n,
-                                                 uint64_t* __restrict__ part_skip) {
-  __shared__ double red_f[16];
-  __shared__ uint64_t red_n[16];
+template <bool kPair>
+__global__ __launch_bounds__(kPair ? 1024 : 512) void k_sps_win(SpsWinLaunch W, double* __restrict__ part_f,
+                                                                uint64_t* __restrict__ part_n,
+                                                                uint64_t* __restrict__ part_skip) {
+  extern __shared__ __align__(16) char lds[];
   const StressLaunch& P = W.P;
-  const double mean = pass == 2 ? mean_dev[0] : 0.0;
   const uint32_t lane = threadIdx.x & 63u;
   const uint32_t x = blockIdx.x % kXcds;
   const uint32_t gb = uload(W.sbeg + x);
   const uint32_t nq = uload(W.sbeg + x + 1) - gb;
   const uint64_t* __restrict__ xi = W.xitem + (size_t)x * W.xstride;
   const uint64_t n_items = uniform_u64(uload(xi + nq));
-  unsigned long long* ctr = reinterpret_cast<unsigned long long*>(W.queue + ((size_t)(pass - 1) * kXcds + x) * 16);
-  double acc = 0.0, acc2 = 0.0, acc3 = 0.0;
-  uint64_t nv = 0, ns = 0;
+  unsigned long long* ctr = reinterpret_cast<unsigned long long*>(W.queue + (size_t)x * 16);
+  SpsAcc<kPair> acc;
   uint32_t q = 0;
   for (uint64_t m = 0, m_end = 0;; ++m) {
     if (m >= m_end) {
@@ -367,22 +425,15 @@ __global__ __launch_bounds__(256) void k_sps_win(SpsWinLaunch W, int pass, const
       uint64_t a, b;
       double d;
       if (!pair_terms(P.rec, i, j, r.r3 & 1u, (r.r3 >> 1) & 1u, a, b, d)) {
-        ++ns;
+        ++acc.ns;
       } else {
         const double st = stress_work(P.work, a, b, d);
-        if (pass == 1) {
-          acc += st;
-          ++nv;
-          keep_outlier(P, i, j, r.r3 & 3u, st);
-        } else {
-#pragma clang fp contract(off)
-          acc += (st - mean) * (st - mean);
-        }
-        if (P.work2) paired_terms(P, pass, mean_dev, a, b, d, st, acc2, acc3);
+        keep_outlier(P, i, j, r.r3 & 3u, st);
+        acc.take(P, a, b, d, st);
       }
     }
   }
-  write_parts(P, acc, acc2, acc3, nv, ns, red_f, red_n, part_f, part_n, part_skip);
+  acc.write(lds, blockIdx.x, gridDim.x, part_f, part_n, part_skip);
 }
 
 // ---------------------------------------------------------------------------
@@ -438,31 +489,62 @@ __global__ __launch_bounds__(256) void k_path_stress_exact(StressLaunch P, doubl
   }
 }
 
+// One block sums the partials of `sums` Sum2 rows and the two counts in a fixed
+// order and writes hi, lo of every sum and the counts (and the outlier counter,
+// if there is one) to `out`, host memory that the device can write.
+__global__ __launch_bounds__(1024) void k_reduce_sps(const double* __restrict__ part_f,
+                                                     const uint64_t* __restrict__ part_n,
+                                                     const uint64_t* __restrict__ part_skip, uint32_t n_parts,
+                                                     uint32_t sums, const uint64_t* __restrict__ out_count,
+                                                     SpsHostSums* out) {
+  const uint32_t lane = threadIdx.x & 63u, w = threadIdx.x >> 6;  // one wave per row
+  if (w < sums) {
+    Sum2 t;
+    for (uint32_t k = lane; k < n_parts; k += 64) {
+      Sum2 x;
+      x.hi = part_f[(size_t)(2 * w) * n_parts + k];
+      x.lo = part_f[(size_t)(2 * w + 1) * n_parts + k];
+      t.add(x);
+    }
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) {
+      Sum2 x;
+      x.hi = __shfl_xor(t.hi, o, 64);
+      x.lo = __shfl_xor(t.lo, o, 64);
+      t.add(x);
+    }
+    if (lane == 0) {
+      out->hi[w] = t.hi;
+      out->lo[w] = t.lo;
+    }
+  } else if (w < sums + 2) {
+    const uint64_t* part = w == sums ? part_n : part_skip;
+    uint64_t t = 0;
+    for (uint32_t k = lane; k < n_parts; k += 64) t += part[k];
+    t = wave_sum(t);
+    if (lane == 0) out->n[w - sums] = t;
+  }
+  if (threadIdx.x == 0) out->outliers = out_count ? *out_count : 0;
+}
+
 // One block sums the partials in a fixed order.
 __global__ __launch_bounds__(1024) void k_reduce_parts(const double* __restrict__ part_f,
-                                                       const uint64_t* __restrict__ part_n,
-                                                       const uint64_t* __restrict__ part_skip, uint32_t n_parts,
-                                                       double* out_f, uint64_t* out_n, double* mean_out,
-                                                       float* loss_out, uint64_t* n_valid_out) {
+                                                       const uint64_t* __restrict__ part_n, uint32_t n_parts,
+                                                       double* out_f, uint64_t* out_n, float* loss_out,
+                                                       uint64_t* n_valid_out) {
   __shared__ double red_f[16];
   __shared__ uint64_t red_n[16];
   double f = 0.0;
-  uint64_t n = 0, sk = 0;
+  uint64_t n = 0;
   for (uint32_t k = threadIdx.x; k < n_parts; k += blockDim.x) {
     f += part_f[k];
-    if (part_n) n += part_n[k];
-    if (part_skip) sk += part_skip[k];
+    n += part_n[k];
   }
   f = block_sum(f, red_f);
   n = block_sum(n, red_n);
-  sk = block_sum(sk, red_n);
   if (threadIdx.x == 0) {
     if (out_f) out_f[0] = f;
-    if (out_n) {
-      if (part_n) out_n[0] = n;
-      if (part_skip) out_n[1] = sk;
-    }
-    if (mean_out) mean_out[0] = n ? f / (double)n : 0.0;
+    if (out_n) out_n[0] = n;
     if (loss_out) loss_out[0] = n ? (float)(f / (double)n) : 0.0f;
     if (n_valid_out) n_valid_out[0] = n;
   }
@@ -880,11 +962,35 @@ static uint32_t grid_for(uint64_t n, uint32_t cap) {
   return (uint32_t)(b < 1 ? 1 : (b > cap ? cap : b));
 }
 
-hipError_t launch_sps_pass(const StressLaunch& P, int pass, int mode, const double* mean_dev, double* part_f,
-                           uint64_t* part_n, uint64_t* part_skip, hipStream_t s) {
-  const size_t lds = mode == 1 ? loss_lds_bytes(P) : (size_t)P.path_slots * 8;
-  hipLaunchKernelGGL(k_sps, dim3(kStressBlocks), dim3(kStressThreads), lds, s, P, pass, mode, mean_dev, part_f,
-                     part_n, part_skip);
+// Chunks of a step's m pairs so that a small graph still has a pair for every
+// thread of the grid: as many as it takes, no more threads than the grid has.
+static uint32_t sps_chunks(uint64_t S, uint32_t m, uint64_t threads) {
+  if (S >= threads) return 1;
+  return (uint32_t)std::max<uint64_t>(1, std::min<uint64_t>(m, threads / S));
+}
+
+hipError_t launch_sps(const StressLaunch& P, int mode, double* part_f, uint64_t* part_n, uint64_t* part_skip,
+                      uint32_t* n_parts, hipStream_t s) {
+  const size_t lds = std::max(kSpsLds, mode == 1 ? loss_lds_bytes(P) : (size_t)P.path_slots * 8);
+  const uint32_t threads = P.work2 ? kSpsPairThreads : kSpsThreads;
+  const uint32_t cap = P.work2 ? kSpsPairBlocks : kSpsBlocks;
+  const uint32_t want = sps_chunks(P.S, P.m, (uint64_t)cap * threads);
+  const uint32_t per = (P.m + want - 1) / want, chunks = (P.m + per - 1) / per;
+  const uint64_t blocks = (P.S * chunks + threads - 1) / threads;
+  *n_parts = (uint32_t)std::min<uint64_t>(cap, std::max<uint64_t>(1, blocks));
+  if (P.work2)
+    hipLaunchKernelGGL(k_sps<true>, dim3(*n_parts), dim3(threads), lds, s, P, mode, per, chunks, part_f, part_n,
+                       part_skip);
+  else
+    hipLaunchKernelGGL(k_sps<false>, dim3(*n_parts), dim3(threads), lds, s, P, mode, per, chunks, part_f, part_n,
+                       part_skip);
+  return hipGetLastError();
+}
+
+hipError_t launch_reduce_sps(const StressLaunch& P, const double* part_f, const uint64_t* part_n,
+                             const uint64_t* part_skip, uint32_t n_parts, SpsHostSums* out, hipStream_t s) {
+  hipLaunchKernelGGL(k_reduce_sps, dim3(1), dim3(1024), 0, s, part_f, part_n, part_skip, n_parts, P.work2 ? 5u : 2u,
+                     P.out_count, out);
   return hipGetLastError();
 }
 
@@ -897,10 +1003,13 @@ hipError_t launch_sps_win_count_scan(const SpsWinLaunch& W, hipStream_t s) {
   return hipGetLastError();
 }
 
-hipError_t launch_sps_win_pass(const SpsWinLaunch& W, int pass, const double* mean_dev, double* part_f,
-                               uint64_t* part_n, uint64_t* part_skip, uint32_t blocks, hipStream_t s) {
-  hipLaunchKernelGGL(k_sps_win, dim3(blocks), dim3(kStressThreads), 0, s, W, pass, mean_dev, part_f, part_n,
-                     part_skip);
+hipError_t launch_sps_win(const SpsWinLaunch& W, double* part_f, uint64_t* part_n, uint64_t* part_skip,
+                          uint32_t* n_parts, hipStream_t s) {
+  *n_parts = W.P.work2 ? kSpsPairBlocks : kSpsBlocks;
+  if (W.P.work2)
+    hipLaunchKernelGGL(k_sps_win<true>, dim3(*n_parts), dim3(kSpsPairThreads), kSpsLds, s, W, part_f, part_n, part_skip);
+  else
+    hipLaunchKernelGGL(k_sps_win<false>, dim3(*n_parts), dim3(kSpsThreads), kSpsLds, s, W, part_f, part_n, part_skip);
   return hipGetLastError();
 }
 
@@ -910,11 +1019,10 @@ hipError_t launch_path_stress_exact(const StressLaunch& P, double* part_f, uint6
   return hipGetLastError();
 }
 
-hipError_t launch_reduce_parts(const double* part_f, const uint64_t* part_n, const uint64_t* part_skip,
-                               uint32_t n_parts, double* out_f, uint64_t* out_n, double* mean_out,
-                               float* loss_out, uint64_t* n_valid_out, hipStream_t s) {
-  hipLaunchKernelGGL(k_reduce_parts, dim3(1), dim3(1024), 0, s, part_f, part_n, part_skip, n_parts, out_f, out_n,
-                     mean_out, loss_out, n_valid_out);
+hipError_t launch_reduce_parts(const double* part_f, const uint64_t* part_n, uint32_t n_parts, double* out_f,
+                               uint64_t* out_n, float* loss_out, uint64_t* n_valid_out, hipStream_t s) {
+  hipLaunchKernelGGL(k_reduce_parts, dim3(1), dim3(1024), 0, s, part_f, part_n, n_parts, out_f, out_n, loss_out,
+                     n_valid_out);
   return hipGetLastError();
 }
 

@@ -9,12 +9,52 @@ from test_gpu_parity import P, _compare_windowed  # noqa: F401 (P: the package f
 pytestmark = pytest.mark.gpu
 
 
-# 33K, 45K and 65.5K nodes: the automatic grids whose XCDs have equal (16 and 32 waves at n_nodes / 2048) and
-# unequal (21) numbers of blocks; every slot of an early, a mixed and a cooling iteration is processed once
-@pytest.mark.parametrize("backbone,paths", [(28000, 4), (38000, 4), (55500, 4)])
+# 33K, 44K and 65K nodes: the automatic grids whose XCDs have equal (16 waves at n_nodes / 2048) and
+# unequal (21 and 31) numbers of blocks; every slot of an early, a mixed and a cooling iteration is processed once
+@pytest.mark.parametrize("backbone,paths", [(28300, 4), (38000, 4), (55500, 4)])
 def test_windowed_sampling_in_the_automatic_grids(P, backbone, paths):  # noqa: F811
     sg = synth.generate(backbone, 0.2, paths, 17)
     og, g = O.Graph.from_synth(sg), P.Graph.from_synth(sg)
     assert g.n_nodes >= 32768
     for it in (0, 9, 20):
         _compare_windowed(P, g, og, it, 0, 10 * og.S)
+
+
+# few steps with many pairs each (split between threads, the last chunk of a step shorter), one pair a step, and more
+# steps than threads; the deviations about the mean to the sums' bar (FP64 terms in another order)
+@pytest.mark.parametrize("backbone,paths,m", [(2, 1, 1), (2, 1, 977), (40, 3, 1000), (700, 3, 257), (3000, 4, 63),
+                                              (250000, 3, 2)])
+@pytest.mark.parametrize("pairs", ["uniform", "power_law", "uniform_windowed"])
+def test_sps_in_one_pass_at_its_split_sizes(P, backbone, paths, m, pairs):  # noqa: F811
+    import torch
+    sg = synth.generate(backbone, 0.2, paths, 5)
+    og, g = O.Graph.from_synth(sg), P.Graph.from_synth(sg)
+    rng = np.random.default_rng(backbone)
+    c = (O.init_coords(og) + rng.normal(scale=4.0, size=4 * sg.n_nodes)).astype(np.float32)
+    a, b = P.path_stress(g, torch.from_numpy(c).cuda(), m, 3, pairs=pairs), O.sampled_path_stress(og, c, m, 3,
+                                                                                                pairs=pairs)
+    assert (a["n_valid"], a["n_skipped"]) == (b["n_valid"], b["n_skipped"])
+    for k in ("sum", "sumsq_dev", "mean", "stddev"):
+        assert abs(a[k] - b[k]) <= 1e-9 * abs(b[k]), (k, a[k], b[k])
+
+
+@pytest.mark.parametrize("pairs", ["uniform", "power_law", "uniform_windowed"])
+def test_sps_deviations_cancel_exactly(P, pairs):  # noqa: F811
+    # a straight path laid out at three times its length: every stress is exactly 4, so its sum is exact, its
+    # deviations from the mean are 0, and so are those of two equal layouts from their ratio 1
+    import torch
+    sg = synth.linear_path(5000)
+    g = P.Graph.from_synth(sg)
+    x = np.cumsum(np.concatenate([[0], sg.node_len.astype(np.int64)]))
+    c = np.zeros((2, sg.n_nodes, 2), np.float32)
+    c[0, :, 0], c[0, :, 1] = 3 * x[:-1], 3 * x[1:]
+    t = torch.from_numpy(c.reshape(-1)).cuda()
+    r = P.path_stress(g, t, 20, 3, pairs=pairs)
+    assert r["sum"] == 4.0 * r["n_valid"] and r["sumsq_dev"] == 0.0 and r["ci_lo"] == r["ci_hi"] == 4.0
+    noisy = t + 5 * torch.randn(t.numel(), generator=torch.Generator().manual_seed(1)).cuda()
+    q = P.path_stress_compare(g, noisy, noisy.clone(), 20, pairs=pairs)
+    assert q["ratio"] == 1.0 and q["sd_diff"] == 0.0 and q["sd_a"] == q["sd_b"] > 0
+    inf = t.clone()
+    inf[7] = float("inf")
+    r = P.path_stress(g, inf, 20, 3, pairs=pairs)  # as the plain FP64 sums: inf, and no deviation from it
+    assert r["sum"] == r["mean"] == float("inf") and np.isnan(r["stddev"])
