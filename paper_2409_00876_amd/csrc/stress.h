@@ -123,7 +123,11 @@ constexpr size_t kTileStaticLds = 9 * 1024;   // static LDS of k_loss_tile (a ti
 // out[g] = the lowest device node id over the steps [start[g], start[g + 1])
 hipError_t launch_segment_min_node(const StepRec* rec, const uint64_t* start, uint32_t nseg, uint32_t* out,
                                    hipStream_t s);
-hipError_t launch_path_stress_exact(const StressLaunch& P, double* part_f, uint64_t* part_n, hipStream_t s);
+// max_path_steps, d_max: the graph's longest path in steps and in nucleotides
+hipError_t launch_path_stress_exact(const StressLaunch& P, uint64_t max_path_steps, int64_t d_max, double* part_f,
+                                    uint64_t* part_n, hipStream_t s);
+// Static LDS of k_path_stress_exact, rounded up.
+constexpr size_t kExactStaticLds = 25 * 1024;
 hipError_t launch_stress_fwd(const StressLaunch& P, double* part_f, uint64_t* part_n, hipStream_t s);
 hipError_t launch_stress_bwd(const StressLaunch& P, const float* grad_out, const uint64_t* n_valid, float* grad,
                              hipStream_t s);

@@ -439,47 +439,134 @@ __global__ __launch_bounds__(kPair ? 1024 : 512) void k_sps_win(SpsWinLaunch W, 
 // ---------------------------------------------------------------------------
 // Path stress, Eq. 1: for every path and every step pair i < j of it, the mean
 // of the stress over the endpoint combinations with d > 0; averaged over all
-// pairs.  Thread-strided over rows i; a row visits j = i+1 .. end of the path.
-// O(sum |p|^2) work: for small graphs and for validating the sampled metric.
+// pairs.  O(sum |p|^2) work: for small graphs and for validating the sampled
+// metric; bound by the FP64 units.
+//
+// A unit of work is kExactRows rows i (one per thread) against kExactCols
+// columns j, whose endpoint positions and coordinates the block stages in LDS
+// as doubles and every wave reads as broadcasts; the units of all rows together
+// tile the triangles, so no thread carries a long row to its end alone.  Only
+// the pair (i, i + 1) can have d = 0 (node lengths are at least 1) and takes
+// the general way; all others have d >= 1 and take exact_stress, whose square
+// root and quotient are the compiler's own sequences without their scaling for
+// arguments near the ends of FP64's range, which float32 coordinates and
+// lengths below 2^63 cannot reach: the same rounding, fewer instructions.  A
+// sum that is not finite (infinite or NaN coordinates) is taken again the
+// general way.  1.3e9 pairs: 19.3 ms with one row per thread and the
+// compiler's sequences, now 5.6 ms (four combinations a pair: 9.4e11 a second).
 // part_f: per-block sum of the pair means; part_n: per-block pair count.
 // ---------------------------------------------------------------------------
-__global__ __launch_bounds__(256) void k_path_stress_exact(StressLaunch P, double* __restrict__ part_f,
-                                                           uint64_t* __restrict__ part_n) {
+constexpr uint32_t kExactRows = 256, kExactCols = 512;
+
+// ((|v| - d) / d)^2 for v = (dx, dy), |dx|, |dy| 0 or in [2^-150, 2^130], 1 <= d < 2^63, each operation rounded
+// as by sqrt and /: Goldschmidt's iteration for the root and Newton's for the reciprocal, each with a last step on
+// the residual (Markstein, IBM J. Res. Dev. 34, 1990).  NaN where |v| is infinite.
+__device__ __forceinline__ double exact_stress(double dx, double dy, double d) {
+#pragma clang fp contract(off)
+  const double x = dx * dx + dy * dy;
+  const double y = __builtin_amdgcn_rsq(__builtin_fmax(x, 0x1p-1000));  // x = 0 gives 0 below
+  double g = x * y, h = 0.5 * y;
+  const double r = __builtin_fma(-h, g, 0.5);
+  g = __builtin_fma(g, r, g);
+  h = __builtin_fma(h, r, h);
+  g = __builtin_fma(__builtin_fma(-g, g, x), h, g);
+  g = __builtin_fma(__builtin_fma(-g, g, x), h, g);
+  double c = __builtin_amdgcn_rcp(d);
+  c = __builtin_fma(c, __builtin_fma(-d, c, 1.0), c);
+  c = __builtin_fma(c, __builtin_fma(-d, c, 1.0), c);
+  const double n = g - d;
+  const double q = n * c;
+  const double e = __builtin_fma(__builtin_fma(-d, q, n), c, q);
+  return e * e;
+}
+
+// Pos: double (differences of positions below 2^53 are exact: one instruction instead of six), or int64_t.
+template <typename Pos>
+__global__ __launch_bounds__(kExactRows) void k_path_stress_exact(StressLaunch P, uint32_t col_chunks,
+                                                                  double* __restrict__ part_f,
+                                                                  uint64_t* __restrict__ part_n) {
   extern __shared__ __align__(16) char lds[];
   uint64_t* off = reinterpret_cast<uint64_t*>(lds);
   __shared__ double red_f[16];
   __shared__ uint64_t red_n[16];
+  __shared__ Pos s_pos[kExactCols][2];
+  __shared__ double s_xy[kExactCols][4];
   fill_offsets(off, P);
   __syncthreads();
   // both endpoints of a node are 16 contiguous bytes of the interleaved copy
   const float4* __restrict__ W4 = reinterpret_cast<const float4*>(P.work);
   double acc = 0.0;
   uint64_t np = 0;
-  const uint64_t stride = (uint64_t)gridDim.x * blockDim.x;
-  for (uint64_t i = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; i < P.S; i += stride) {
-    const uint32_t p = find_path(off, P.path_top, i);
-    const uint64_t end = off[p + 1];
+  const uint64_t units = (P.S + kExactRows - 1) / kExactRows * col_chunks;
+  for (uint64_t u = blockIdx.x; u < units; u += gridDim.x) {
+    const uint64_t r0 = u / col_chunks * kExactRows;
+    const uint64_t j0 = r0 + (u % col_chunks) * kExactCols;
+    const uint64_t last = min(r0 + kExactRows, P.S) - 1;
+    const uint64_t j1 = min(j0 + kExactCols, off[find_path(off, P.path_top, last) + 1]);
+    if (j0 >= j1) continue;  // the same for the whole block
+    const uint32_t n = (uint32_t)(j1 - j0);
+    __syncthreads();  // the columns of the unit before are no longer read
+    for (uint32_t c = threadIdx.x; c < n; c += kExactRows) {
+      const StepRec sj = load_rec(P.rec, j0 + c);
+      const float4 v = W4[sj.node_rev & kNodeMask];
+      s_pos[c][0] = (Pos)endpoint_pos(sj, 0);
+      s_pos[c][1] = (Pos)endpoint_pos(sj, 1);
+      s_xy[c][0] = v.x;
+      s_xy[c][1] = v.y;
+      s_xy[c][2] = v.z;
+      s_xy[c][3] = v.w;
+    }
+    __syncthreads();
+    const uint64_t i = r0 + threadIdx.x;
+    if (i >= P.S) continue;
+    const uint64_t end = min(off[find_path(off, P.path_top, i) + 1], j1);
     const StepRec si = load_rec(P.rec, i);
     const float4 ci = W4[si.node_rev & kNodeMask];
-    for (uint64_t j = i + 1; j < end; ++j) {
-      const StepRec sj = load_rec(P.rec, j);
-      const float4 cj = W4[sj.node_rev & kNodeMask];
-      double sum = 0.0;
+    const Pos p0 = (Pos)endpoint_pos(si, 0), p1 = (Pos)endpoint_pos(si, 1);
+    const double x0 = ci.x, y0 = ci.y, x1 = ci.z, y1 = ci.w;
+    // the mean over the combinations with d > 0
+    auto general = [&](uint32_t c, double& sum) -> bool {
       uint32_t nv = 0;
+      sum = 0.0;
       for (uint32_t e = 0; e < 4; ++e) {
-        const uint32_t ei = e & 1u, ej = e >> 1;
-        const int64_t dd = endpoint_pos(si, ei) - endpoint_pos(sj, ej);
+        const Pos dd = ((e & 1u) ? p1 : p0) - s_pos[c][e >> 1];
         if (dd == 0) continue;
-        sum += stress_xy(ei ? ci.z : ci.x, ei ? ci.w : ci.y, ej ? cj.z : cj.x, ej ? cj.w : cj.y,
-                         (double)(dd < 0 ? -dd : dd));
+        sum += stress_xy((e & 1u) ? ci.z : ci.x, (e & 1u) ? ci.w : ci.y, (float)s_xy[c][(e >> 1) * 2],
+                         (float)s_xy[c][(e >> 1) * 2 + 1], (double)(dd < 0 ? -dd : dd));
         ++nv;
       }
-      if (nv) {
+      sum = nv ? sum / (double)nv : 0.0;
+      return nv != 0;
+    };
+    if (i + 1 >= j0 && i + 1 < end) {
+      double sum;
+      np += general((uint32_t)(i + 1 - j0), sum);
+      acc += sum;
+    }
+    const uint32_t lo = (uint32_t)(i + 2 > j0 ? min(i + 2 - j0, (uint64_t)n) : 0);
+    const uint32_t hi = end > j0 ? (uint32_t)(end - j0) : 0u;
+    if (lo >= hi) continue;
+    double unit = 0.0;
+    for (uint32_t c = lo; c < hi; ++c) {
 #pragma clang fp contract(off)
-        acc += sum / (double)nv;
-        ++np;
+      const Pos q0 = s_pos[c][0], q1 = s_pos[c][1];
+      const double u0 = s_xy[c][0], v0 = s_xy[c][1], u1 = s_xy[c][2], v1 = s_xy[c][3];
+      double sum = exact_stress(x0 - u0, y0 - v0, (double)(q0 - p0));
+      sum += exact_stress(x1 - u0, y1 - v0, (double)(q0 - p1));
+      sum += exact_stress(x0 - u1, y0 - v1, (double)(q1 - p0));
+      sum += exact_stress(x1 - u1, y1 - v1, (double)(q1 - p1));
+      unit += sum * 0.25;
+    }
+    if (!(unit - unit == 0.0)) {
+      unit = 0.0;
+      for (uint32_t c = lo; c < hi; ++c) {
+        double sum;
+        general(c, sum);
+        unit += sum;
       }
     }
+    acc += unit;
+    np += hi - lo;
   }
   acc = block_sum(acc, red_f);
   np = block_sum(np, red_n);
@@ -1013,9 +1100,17 @@ hipError_t launch_sps_win(const SpsWinLaunch& W, double* part_f, uint64_t* part_
   return hipGetLastError();
 }
 
-hipError_t launch_path_stress_exact(const StressLaunch& P, double* part_f, uint64_t* part_n, hipStream_t s) {
-  hipLaunchKernelGGL(k_path_stress_exact, dim3(kStressBlocks), dim3(kStressThreads), (size_t)P.path_slots * 8, s, P,
-                     part_f, part_n);
+hipError_t launch_path_stress_exact(const StressLaunch& P, uint64_t max_path_steps, int64_t d_max, double* part_f,
+                                    uint64_t* part_n, hipStream_t s) {
+  const uint32_t chunks = (uint32_t)((max_path_steps + kExactRows + kExactCols - 1) / kExactCols);
+  const size_t lds = (size_t)P.path_slots * 8;
+  // any line up to 2^53 is exact; 2^40 leaves genomes a factor of 100 and lets a path of 256 long nodes cross it
+  if (d_max < (1ll << 40))
+    hipLaunchKernelGGL(k_path_stress_exact<double>, dim3(kStressBlocks), dim3(kExactRows), lds, s, P, chunks, part_f,
+                       part_n);
+  else
+    hipLaunchKernelGGL(k_path_stress_exact<int64_t>, dim3(kStressBlocks), dim3(kExactRows), lds, s, P, chunks,
+                       part_f, part_n);
   return hipGetLastError();
 }
 

@@ -58,3 +58,25 @@ def test_sps_deviations_cancel_exactly(P, pairs):  # noqa: F811
     inf[7] = float("inf")
     r = P.path_stress(g, inf, 20, 3, pairs=pairs)  # as the plain FP64 sums: inf, and no deviation from it
     assert r["sum"] == r["mean"] == float("inf") and np.isnan(r["stddev"])
+
+
+# one column, one row tile and its neighbours, a chunk of columns and its neighbours, several row tiles; with
+# the long nodes the paths of 256 steps and more pass 2^40 nucleotides (the integer variant)
+@pytest.mark.parametrize("steps", [1, 2, 3, 255, 256, 257, 511, 512, 513, 514, 1300])
+@pytest.mark.parametrize("length", [9, 4_000_000_000])
+def test_exact_path_stress_at_the_edges_of_its_tiles(P, steps, length):  # noqa: F811
+    import torch
+    rng = np.random.default_rng(steps)
+    n = 700
+    paths = [steps, 5, 0, steps // 2 + 1]
+    off = np.cumsum([0] + paths).astype(np.uint64)
+    node_len = rng.integers(max(1, length - 8), length + 1, size=n).astype(np.uint32)
+    node = rng.integers(0, n, size=int(off[-1])).astype(np.uint32)
+    node |= np.where(rng.random(node.size) < 0.3, np.uint32(synth.REV_BIT), np.uint32(0)).astype(np.uint32)
+    sg = synth.SynthGraph(node_len, off, node, {}, "tiles")
+    og, g = O.Graph.from_synth(sg), P.Graph.from_synth(sg)
+    c = rng.normal(scale=50.0, size=4 * n).astype(np.float32)
+    mean, pairs = P.path_stress_exact(g, torch.from_numpy(c).cuda())
+    ref = O.path_stress_exact(og, c)
+    assert pairs == ref[1]
+    assert abs(mean - ref[0]) <= 1e-9 * abs(ref[0])
