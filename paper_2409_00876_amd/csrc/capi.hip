@@ -196,6 +196,8 @@ struct pgsgd_graph {
   uint32_t* d_lorder = nullptr;
   uint32_t* d_lsbeg = nullptr;
   uint32_t* d_lwpath = nullptr;
+  OrderedTerm* d_ordered = nullptr;  // terms of one ordered iteration
+  uint64_t ordered_cap = 0;          // its terms
   // window-major segment tables of the sampled path stress (R21) and of the
   // loss (R22), and the loss adjoint's tiles (allocated on first use)
   SegTables sps, loss;
@@ -226,7 +228,7 @@ struct pgsgd_graph {
     for (void* p : {(void*)d_rec, (void*)d_path_off, (void*)d_first, (void*)d_work, (void*)d_inv, (void*)d_zipf, (void*)d_guide, (void*)d_part_f,
                     (void*)d_part_n, (void*)d_part_skip, (void*)d_out_f, (void*)d_out_n, (void*)d_work2, (void*)d_lcount, (void*)d_loff, (void*)d_lxitem, (void*)d_lqueue, (void*)d_lorder,
                     (void*)d_lsbeg, (void*)d_lwpath, (void*)d_lcount2, (void*)d_loff2, (void*)d_lxitem2,
-                    (void*)d_lqueue2, (void*)d_tile_seg, (void*)d_tile_off, (void*)d_tile_base, (void*)d_tile_queue})
+                    (void*)d_lqueue2, (void*)d_ordered, (void*)d_tile_seg, (void*)d_tile_off, (void*)d_tile_base, (void*)d_tile_queue})
       if (p) (void)hipFree(p);
     for (SegTables* t : {&sps, &loss})
       for (void* p : {(void*)t->start, (void*)t->path, (void*)t->wseg, (void*)t->count, (void*)t->off,
@@ -1085,6 +1087,43 @@ pgsgd_status local_grids(pgsgd_graph* g, const pgsgd_params* p, size_t lds, Loca
   return PGSGD_OK;
 }
 
+// Whether a phase's iterations take the ordered form: one wave.  (Several
+// one-wave blocks, one per XCD, gain as much and each applies its terms as
+// before, but which of the XCDs ends last, and so whose coordinates stand,
+// follows from their pace: layouts of 9K and 13K nodes lay 2e-3 from where
+// they were, runs differing by 5e-5 to 5e-4.)
+bool ordered_phase(const LocalGrids& grids, uint32_t phase) {
+  return grids.threads[phase] == 64 && grids.blocks[phase] == 1;
+}
+
+// Terms of the ordered form's list for the plan W, or 0 when no phase takes it:
+// never with data reuse (its terms meet in registers), and not beyond
+// kOrderedMaxBytes.
+uint64_t ordered_terms(const LocalLaunch& W, const LocalGrids& grids) {
+  bool any = false;
+  for (uint32_t ph = 0; ph < kPhases; ++ph) any = any || ordered_phase(grids, ph);
+  const uint64_t terms = 64 * ordered_items(W.L.n_terms, W.n_win);
+  return any && W.L.drf <= 1 && W.streams == 1 && terms * sizeof(OrderedTerm) <= kOrderedMaxBytes ? terms : 0;
+}
+
+// The graph's list for the plan W, grown when needed.  Without the memory for
+// it the layout runs k_layout_local, which gives the same coordinates.  Only
+// the calls that run at once use it: a batch holds lists of its own.
+OrderedTerm* ordered_list(pgsgd_graph* g, const LocalLaunch& W, const LocalGrids& grids) {
+  const uint64_t terms = ordered_terms(W, grids);
+  if (!terms) return nullptr;
+  if (g->ordered_cap < terms) {
+    free_set(g, {(void**)&g->d_ordered});
+    g->ordered_cap = 0;
+    if (dev_alloc(g, &g->d_ordered, terms) != PGSGD_OK) {
+      clear_error();
+      return nullptr;
+    }
+    g->ordered_cap = terms;
+  }
+  return g->d_ordered;
+}
+
 // Scratch, grid and launch arguments of the windowed schedule for graph g
 // (L: the sampling arguments of make_layout_launch).
 pgsgd_status local_plan(pgsgd_graph* g, const pgsgd_params* p, size_t lds, const LayoutLaunch& L, hipStream_t s,
@@ -1107,6 +1146,7 @@ pgsgd_status local_plan(pgsgd_graph* g, const pgsgd_params* p, size_t lds, const
   W->wpath = g->d_lwpath;
   W->streams = kLocalStreams;
   W->grab = kLocalGrab;
+  W->list = batched ? nullptr : ordered_list(g, *W, *grids);
   return PGSGD_OK;
 }
 
@@ -1176,6 +1216,10 @@ pgsgd_status local_plan_scratch(pgsgd_graph* g, const pgsgd_params* p, size_t ld
 // right before the layout kernel.
 hipError_t local_layout(const LocalLaunch& W, const LocalGrids& grids, LocalPhase phase, hipStream_t s,
                         hipEvent_t e_mid = nullptr) {
+  if (W.list && ordered_phase(grids, phase) && !W.L.trace_f && !W.L.apply_mask) {
+    const hipError_t e = e_mid ? hipEventRecord(e_mid, s) : hipSuccess;
+    return e ? e : launch_layout_ordered(W, s);
+  }
   hipError_t e = launch_fill_u32(reinterpret_cast<uint32_t*>(W.queue), 2ull * kXcds * W.streams * 16, 0u, s);
   if (!e && e_mid) e = hipEventRecord(e_mid, s);
   LocalLaunch Wp = W;
@@ -1984,6 +2028,7 @@ struct pgsgd_batch {
   std::vector<pgsgd_graph*> graphs;
   std::vector<LocalLaunch> wl;
   std::vector<LocalGrids> wgrids;
+  std::vector<OrderedTerm*> lists;
   std::vector<std::vector<float>> weta;
   std::vector<std::vector<uint32_t>> branch_graphs;
 
@@ -1995,6 +2040,7 @@ struct pgsgd_batch {
     for (void* p : {(void*)d_graphs, (void*)d_seg_off, (void*)d_path_blob, (void*)d_eta, (void*)d_zipf,
                     (void*)d_guide})
       if (p) (void)hipFree(p);
+    for (OrderedTerm* l : lists) (void)hipFree(l);
   }
 };
 
@@ -2066,6 +2112,15 @@ pgsgd_status batch_build_windowed(pgsgd_graph* const* graphs, uint32_t n, const 
     LocalLaunch W;
     LocalGrids grids;
     if ((st = local_plan(g, &q, lds, L, cs, &W, &grids, true))) break;
+    // a list per graph: graphs of different branches apply theirs at the same time
+    if (const uint64_t terms = ordered_terms(W, grids)) {
+      if (hipMalloc((void**)&W.list, terms * sizeof(OrderedTerm)) == hipSuccess) {
+        b->lists.push_back(W.list);
+      } else {
+        (void)hipGetLastError();
+        W.list = nullptr;
+      }
+    }
     std::vector<float> eta;
     build_schedule(q.n_iters, eta_max_of(&q, g->d_max), q.eta_min, eta);
     b->graphs.push_back(g);

@@ -183,12 +183,15 @@ __device__ __forceinline__ bool resolve_term(const StepRec* __restrict__ rec, co
 // r (a - b); a moves by -disp and b by +disp.  Returns false (disp unset)
 // when the points coincide.  FP32 throughout.  Every layout kernel (plain,
 // window-major, data reuse, batched, the parity hook) takes its updates from
-// this one function.
+// this one function; the ordered one writes out the fused operations that the
+// compiler makes of it and of the moves around it.
+__device__ __forceinline__ float step_length(float d, float eta) { return fminf(eta / (d * d), 1.0f); }
+
 __device__ __forceinline__ bool clamped_step(float2 pa, float2 pb, float d, float eta, float2& disp) {
   const float dx = pa.x - pb.x, dy = pa.y - pb.y;
   const float mag = sqrtf(dx * dx + dy * dy);
   if (mag == 0.0f) return false;
-  const float mu = fminf(eta / (d * d), 1.0f);
+  const float mu = step_length(d, eta);
   const float r = mu * (mag - d) / (2.0f * mag);
   disp = make_float2(r * dx, r * dy);
   return true;

@@ -58,6 +58,22 @@ inline uint32_t loss_shift(uint64_t S) {
   return sh;
 }
 
+// One term of the ordered form: the two endpoints, their reference distance and
+// the step length of the iteration; a = kNoTerm where the slot has no update.
+struct alignas(16) OrderedTerm {
+  uint32_t a, b;
+  float d, mu;
+};
+constexpr uint32_t kNoTerm = 0xFFFFFFFFu;
+// The ordered form of a windowed iteration that one wave runs: the terms of all
+// slots first (any order, the whole chip), then one wave applies them in the
+// order in which it would have drawn them.  list: 64 * ordered_items(T, n_win)
+// terms.
+constexpr uint32_t kOrderedChunk = 32;        // items a block stages at a time (two buffers)
+constexpr uint32_t kOrderedLdsNodes = 4096;   // coordinates are held in LDS up to this many nodes
+constexpr uint64_t kOrderedMaxBytes = 64u << 20;
+inline uint64_t ordered_items(uint64_t n_terms, uint32_t n_win) { return n_terms / 64 + n_win; }
+
 // Processing order: kXcds * streams runs of windows; run sigma = x * streams +
 // r is stream r of XCD x and holds the windows starting in piece sigma of
 // every path (paths cut into kXcds * streams equal pieces), in id order.
@@ -76,10 +92,13 @@ struct LocalLaunch {
   const uint32_t* sbeg;    // [kXcds * streams + 1] first position in worder of every run
   const uint32_t* wpath;   // [n_win] path holding the whole window, or bit 31 set if it spans paths
   uint64_t* xitem;         // [kXcds * streams][xstride] prefix of 64-slot groups over the windows of each run
+  OrderedTerm* list;       // the ordered form's terms (see launch_layout_ordered), or NULL
   uint64_t* queue;         // [kXcds * streams * 16] item counters, one per run on its own 128-byte line
 };
 
 hipError_t launch_local_count_scan(const LocalLaunch& P, hipStream_t s);
+// Terms of every item into P.list, then their application by one wave.
+hipError_t launch_layout_ordered(const LocalLaunch& P, hipStream_t s);
 hipError_t launch_layout_local(const LocalLaunch& P, uint32_t blocks, uint32_t threads, hipStream_t s);
 const void* layout_local_kernel();
 

@@ -26,6 +26,8 @@
 //   k_local_count  plain draw i_t, window histogram (LDS, then global)
 //   k_local_scan   window offsets, per-run group prefixes; clears the histogram
 //   k_layout_local slot draw, sample, gather, update
+#include <algorithm>
+
 #include "device.h"
 #include "local.h"
 
@@ -174,11 +176,12 @@ __device__ __forceinline__ void local_item(const LocalLaunch& P, const LdsView& 
   else apply_update_far_first(L.work, a, b, d, L.eta);
 }
 
-// The draws of item m of a run in an all-cooling iteration (no loads beyond
-// the run's metadata, read at wave-uniform addresses, and the LDS tables):
-// the lane's term, or flags bit 3 when the lane has no slot or no partner;
-// slot = the lane's global slot, ~0 when it has none.
-__device__ __forceinline__ Term cooling_draw(const LocalLaunch& P, const LdsView& V, uint32_t wb, uint32_t nq,
+// The draws of item m of a run (kCooling: in an all-cooling iteration; no loads
+// beyond the run's metadata, read at wave-uniform addresses, and the LDS
+// tables): the lane's term, or flags bit 3 when the lane has no slot or no
+// partner; slot = the lane's global slot, ~0 when it has none.
+template <bool kCooling>
+__device__ __forceinline__ Term item_draw(const LocalLaunch& P, const LdsView& V, uint32_t wb, uint32_t nq,
                                              const uint64_t* __restrict__ xi, uint64_t m, uint32_t& q,
                                              uint64_t& slot) {
   const LayoutLaunch& L = P.L;
@@ -191,6 +194,8 @@ __device__ __forceinline__ Term cooling_draw(const LocalLaunch& P, const LdsView
   const uint64_t s = wbeg + k;
   const uint32_t slot_c3 = (kStreamWindow << 24) | (L.c3 & 0xFFFFFFu);
   const Rand4 r = philox10((uint32_t)s, (uint32_t)(s >> 32), L.iter, slot_c3, L.k0, L.k1);
+  const uint32_t lead = uniform_u32(r.r3);  // lane 0: slot 64 * group, always inside the window
+  const bool cooling = kCooling || ((lead >> 3) & 1u);
   Term T;
   T.j = 0;
   slot = ~0ull;
@@ -207,8 +212,10 @@ __device__ __forceinline__ Term cooling_draw(const LocalLaunch& P, const LdsView
   const uint32_t p = (wp >> 31) ? find_path(V.off, L.path_top, T.i) : wp;
   const uint64_t start = V.off[p];
   const uint64_t len = V.off[p + 1] - start;
-  const bool ok = partner_power_law(T.i, start, len, r.r2, r.r3, V.zipf, V.guide, L.W, T.j);
-  T.flags = (r.r3 & 3u) | 4u | ((ok ? 0u : 1u) << 3);
+  bool ok = true;
+  if (cooling) ok = partner_power_law(T.i, start, len, r.r2, r.r3, V.zipf, V.guide, L.W, T.j);
+  else T.j = start + mulhi32(r.r2, (uint32_t)len);
+  T.flags = (r.r3 & 3u) | ((cooling ? 1u : 0u) << 2) | ((ok ? 0u : 1u) << 3);
   return T;
 }
 
@@ -242,7 +249,7 @@ __device__ __forceinline__ void local_run_cooling(const LocalLaunch& P, const Ld
   uint64_t slot;
   if (L.trace_f) {  // parity hook: the drawn terms of the slots [t_begin, t_end), nothing applied
     for (;;) {
-      Term T = cooling_draw(P, V, wb, nq, xi, m, q, slot);
+      Term T = item_draw<true>(P, V, wb, nq, xi, m, q, slot);
       if (slot >= L.t_begin && slot < L.t_end) {
         if (!(T.flags & 8u)) {
           uint64_t a, b;
@@ -257,7 +264,7 @@ __device__ __forceinline__ void local_run_cooling(const LocalLaunch& P, const Ld
       if (++m >= m_end && !grab(m, m_end)) return;
     }
   }
-  Term cur = cooling_draw(P, V, wb, nq, xi, m, q, slot);
+  Term cur = item_draw<true>(P, V, wb, nq, xi, m, q, slot);
   for (;;) {
     // the next item's index first: a grab waits for its atomic before this item's loads are issued
     uint64_t mn = m + 1, mn_end = m_end;
@@ -270,7 +277,7 @@ __device__ __forceinline__ void local_run_cooling(const LocalLaunch& P, const Ld
     }
     Term nxt;
     nxt.flags = 8u;
-    if (more) nxt = cooling_draw(P, V, wb, nq, xi, mn, q, slot);
+    if (more) nxt = item_draw<true>(P, V, wb, nq, xi, mn, q, slot);
     if (live) {
       const uint32_t ei = cur.flags & 1u, ej = (cur.flags >> 1) & 1u;
       const uint64_t a = 2ull * (si.node_rev & kNodeMask) + ei;
@@ -282,6 +289,162 @@ __device__ __forceinline__ void local_run_cooling(const LocalLaunch& P, const Ld
     cur = nxt;
     m = mn;
     m_end = mn_end;
+  }
+}
+
+// ---------------------------------------------------------------------------
+// The ordered form.  A graph of a few thousand nodes runs one wave, so its
+// iteration is one serial chain of items.  In k_layout_local the chain holds
+// everything an item does (run metadata, Philox, power-law search, step
+// records, two coordinate round trips: 1.38 us); only the coordinates depend
+// on the items before.  So k_ordered_terms draws and resolves the terms of all
+// items with the whole chip, and the first wave of k_layout_ordered applies
+// them item after item while its other waves stage the next ones in LDS, with
+// the same loads, arithmetic and stores per item as local_item: the same
+// coordinates bit for bit.  kLds: the coordinates live in LDS for the
+// iteration.  2.7K nodes, 14.4K steps (67.6K items a layout): 93.5 ms with
+// k_layout_local, 13.9 in LDS; 7K nodes, one wave: 300 and 73 ms in the L2.
+//
+// Lanes of an item that store to one endpoint: a global store leaves the value
+// of the lane highest in the order of quads 0, 4, 8, 12, 1, 5, ... (measured
+// for all pairs of lanes), an LDS store that of the highest lane, so for kLds
+// the terms are listed in that order of lanes.
+// ---------------------------------------------------------------------------
+__device__ __forceinline__ uint32_t store_rank(uint32_t lane) {
+  return ((lane >> 2) & 3u) << 4 | (lane >> 4) << 2 | (lane & 3u);
+}
+
+template <bool kLds>
+__global__ __launch_bounds__(256) void k_ordered_terms(LocalLaunch P) {
+  extern __shared__ __align__(16) char lds[];
+  const LayoutLaunch& L = P.L;
+  const LdsView V = lds_view(lds, L.path_slots, L.W);
+  lds_fill(V, L.path_off, L.n_paths, L.path_slots, L.zipf, L.guide, L.W);
+  __syncthreads();
+  const uint32_t lane = threadIdx.x & 63u;
+  const uint64_t waves = (uint64_t)gridDim.x * (blockDim.x >> 6);
+  uint64_t item = (uint64_t)blockIdx.x * (blockDim.x >> 6) + uniform_u32(threadIdx.x >> 6);
+  uint64_t base = 0;
+  for (uint32_t run = 0; run < kXcds * P.streams; ++run) {
+    const uint32_t wb = uniform_u32(uload(P.sbeg + run));
+    const uint32_t nq = uniform_u32(uload(P.sbeg + run + 1)) - wb;
+    const uint64_t* __restrict__ xi = P.xitem + (size_t)run * P.xstride;
+    const uint64_t n_items = uniform_u64(uload(xi + nq));
+    for (; item < base + n_items; item += waves) {
+      const uint64_t m = item - base;
+      uint32_t q = 0;  // the last window of the run with xi[q] <= m
+      for (uint32_t hi = nq; hi - q > 1;) {
+        const uint32_t mid = uniform_u32(q + ((hi - q) >> 1));
+        if (uniform_u64(uload(xi + mid)) <= m) q = mid;
+        else hi = mid;
+      }
+      uint64_t slot;
+      const Term T = L.cool_all ? item_draw<true>(P, V, wb, nq, xi, m, q, slot)
+                                : item_draw<false>(P, V, wb, nq, xi, m, q, slot);
+      OrderedTerm o{kNoTerm, 0, 0.0f, 0.0f};
+      if (!(T.flags & 8u)) {
+        uint64_t a, b;
+        float d;
+        if (resolve_term(L.rec, T, a, b, d)) o = OrderedTerm{(uint32_t)a, (uint32_t)b, d, step_length(d, L.eta)};
+      }
+      P.list[item * 64 + (kLds ? store_rank(lane) : lane)] = o;
+    }
+    base += n_items;
+  }
+}
+
+// mu (mag - d) / (2 mag), mag = sqrt(mag2), each operation correctly rounded as
+// by sqrtf and /.  The chain of these operations and the LDS round trip bound
+// k_layout_ordered (0.24 us an item with the compiler's sequences and a wait
+// for the stores, 0.19 so).  The reciprocal square root y serves both: y mag2 with one correction by the residual is the root,
+// and y / 2, Newton's step, two corrections by the residual the quotient
+// (Markstein, IBM J. Res. Dev. 34, 1990).  Items with a live lane outside the
+// ranges in which no intermediate result leaves FP32's normal numbers take the
+// compiler's sequences; a lane with mag2 = 0 has no step.
+__device__ __forceinline__ float step_ratio(float mag2, float d, float mu, bool live) {
+#pragma clang fp contract(off)
+  const float y = __builtin_amdgcn_rsqf(mag2);
+  const float g = mag2 * y;
+  float h = 0.5f * y;
+  const float mag = __builtin_fmaf(__builtin_fmaf(-g, g, mag2), h, g);
+  const float n = mu * (mag - d), den = mag + mag;
+  h = __builtin_fmaf(h, __builtin_fmaf(-den, h, 1.0f), h);
+  float q = n * h;
+  q = __builtin_fmaf(__builtin_fmaf(-den, q, n), h, q);
+  q = __builtin_fmaf(__builtin_fmaf(-den, q, n), h, q);
+  // exponents by the bits: mag2 in [2^-96, 2^96), |n| in [2^-60, 2^60)
+  const bool inside = __float_as_uint(mag2) - 0x0F800000u < 0x60000000u &&
+                      (__float_as_uint(n) & 0x7FFFFFFFu) - 0x21800000u < 0x3C000000u;
+  if (__builtin_amdgcn_ballot_w64(live && mag2 != 0.0f && !inside)) {
+    const float root = sqrtf(mag2);
+    q = mu * (root - d) / (2.0f * root);
+  }
+  return q;
+}
+
+template <bool kLds>
+__global__ __launch_bounds__(256) void k_layout_ordered(LocalLaunch P) {
+  extern __shared__ __align__(16) char lds[];
+  constexpr uint32_t kChunk = kOrderedChunk * 64;  // terms
+  OrderedTerm* buf = reinterpret_cast<OrderedTerm*>(lds);  // [2][kChunk]
+  float2* __restrict__ W = P.L.work;
+  float2* C = kLds ? reinterpret_cast<float2*>(lds + 2 * kChunk * sizeof(OrderedTerm)) : W;
+  if (kLds)
+    for (uint32_t k = threadIdx.x; k < 2 * P.L.n_nodes; k += blockDim.x) C[k] = W[k];
+  const uint32_t lane = threadIdx.x & 63u;
+  const bool applies = uniform_u32(threadIdx.x >> 6) == 0;
+  uint64_t base = 0;
+  for (uint32_t run = 0; run < kXcds * P.streams; ++run) {
+    const uint32_t wb = uniform_u32(uload(P.sbeg + run));
+    const uint32_t nq = uniform_u32(uload(P.sbeg + run + 1)) - wb;
+    const uint64_t n_items = uniform_u64(uload(P.xitem + (size_t)run * P.xstride + nq));
+    const OrderedTerm* __restrict__ list = P.list + base * 64;
+    base += n_items;
+    const uint64_t chunks = (n_items + kOrderedChunk - 1) / kOrderedChunk;
+    // chunk c is staged in buffer c & 1 while chunk c - 1 is applied
+    for (uint64_t c = 0; c <= chunks; ++c) {
+      if (applies) {
+        if (c > 0) {
+          const OrderedTerm* now = buf + ((c - 1) & 1) * kChunk;
+          const uint32_t items = (uint32_t)min((uint64_t)kOrderedChunk, n_items - (c - 1) * kOrderedChunk);
+          OrderedTerm t = now[lane];
+          bool live = t.a != kNoTerm;
+          uint32_t a = live ? t.a : 0, b = live ? t.b : 0;
+          float2 pa = C[a], pb = C[b];
+          for (uint32_t k = 1; k <= items; ++k) {
+            OrderedTerm next = now[min(k, items - 1) * 64 + lane];
+            // clamped_step and its moves, with the same fused operations
+            const float dx = pa.x - pb.x, dy = pa.y - pb.y;
+            const float mag2 = __builtin_fmaf(dx, dx, dy * dy);
+            const float r = step_ratio(mag2, t.d, t.mu, live);
+            // the next item's words are here before this item's stores are issued (no instruction is emitted), so
+            // nothing waits for the stores
+            asm volatile("" : "+v"(next.a), "+v"(next.b), "+v"(next.d), "+v"(next.mu));
+            const bool next_live = next.a != kNoTerm;
+            const uint32_t next_a = next_live ? next.a : 0, next_b = next_live ? next.b : 0;
+            if (live && mag2 != 0.0f) {
+              C[a] = make_float2(__builtin_fmaf(-dx, r, pa.x), __builtin_fmaf(-dy, r, pa.y));
+              C[b] = make_float2(__builtin_fmaf(dx, r, pb.x), __builtin_fmaf(dy, r, pb.y));
+            }
+            pa = C[next_a];
+            pb = C[next_b];
+            t = next;
+            live = next_live;
+            a = next_a;
+            b = next_b;
+          }
+        }
+      } else if (c < chunks) {
+        const uint64_t k0 = c * kChunk, k1 = min(n_items * 64, k0 + kChunk);
+        OrderedTerm* to = buf + (c & 1) * kChunk;
+        for (uint64_t k = k0 + threadIdx.x - 64; k < k1; k += blockDim.x - 64) to[k - k0] = list[k];
+      }
+      __syncthreads();
+    }
+  }
+  if (kLds) {
+    __syncthreads();
+    for (uint32_t k = threadIdx.x; k < 2 * P.L.n_nodes; k += blockDim.x) W[k] = C[k];
   }
 }
 
@@ -445,6 +608,23 @@ hipError_t launch_local_count_scan(const LocalLaunch& P, hipStream_t s) {
   if (e) return e;
   hipLaunchKernelGGL(k_local_scan, dim3(1), dim3(1024), 0, s, P);
   return hipGetLastError();
+}
+
+template <bool kLds>
+static hipError_t launch_ordered(const LocalLaunch& P, hipStream_t s) {
+  const uint64_t items = ordered_items(P.L.n_terms, P.n_win);
+  hipLaunchKernelGGL(k_ordered_terms<kLds>, dim3((uint32_t)std::min<uint64_t>(1024, (items + 3) / 4)), dim3(256),
+                     layout_lds_bytes(P.L.path_slots, P.L.W), s, P);
+  const hipError_t e = hipGetLastError();
+  if (e) return e;
+  const size_t stage = (size_t)2 * kOrderedChunk * 64 * sizeof(OrderedTerm);
+  hipLaunchKernelGGL(k_layout_ordered<kLds>, dim3(1), dim3(256),
+                     stage + (kLds ? 2 * P.L.n_nodes * sizeof(float2) : 0), s, P);
+  return hipGetLastError();
+}
+
+hipError_t launch_layout_ordered(const LocalLaunch& P, hipStream_t s) {
+  return P.L.n_nodes <= kOrderedLdsNodes ? launch_ordered<true>(P, s) : launch_ordered<false>(P, s);
 }
 
 hipError_t launch_layout_local(const LocalLaunch& P, uint32_t blocks, uint32_t threads, hipStream_t s) {

@@ -193,7 +193,7 @@ struct SpsAcc {
 // whose few steps would otherwise leave it idle while each thread waits for
 // one pair's memory after another (14K steps, m = 100: a call took 198 us with
 // 57 busy blocks and a second pass, 43 us with chunks of 3 pairs and one pass;
-// 1.04e6 steps in 16 paths, m = 10, two layouts: 3.9 and 1.9 ms).
+// 2.9e6 steps in 16 paths, m = 10, two layouts: 3.9 and 1.9 ms).
 // ---------------------------------------------------------------------------
 __device__ __forceinline__ void fill_loss_lds(char* lds, const StressLaunch& P, uint64_t*& off, uint32_t*& zipf,
                                               uint16_t*& guide);

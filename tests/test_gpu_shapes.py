@@ -80,3 +80,44 @@ def test_exact_path_stress_at_the_edges_of_its_tiles(P, steps, length):  # noqa:
     ref = O.path_stress_exact(og, c)
     assert pairs == ref[1]
     assert abs(mean - ref[0]) <= 1e-9 * abs(ref[0])
+
+
+# the ordered form of one-wave layouts against k_layout_local (which layout_noalloc keeps), bit for bit: a single item,
+# a chunk of items and its neighbours, the last size with the coordinates in LDS and the first in memory, many short
+# paths, iteration ranges and parameters
+@pytest.mark.parametrize("backbone,paths,nodes,kw", [
+    (2, 1, 0, {}), (7, 1, 0, {}), (200, 1, 0, {}), (211, 1, 0, {}), (300, 3, 0, {"terms_per_step": 1}),
+    (1000, 40, 0, {"n_iters": 6}), (3448, 4, 4095, {"n_iters": 4}),
+    (3448, 4, 4096, {"n_iters": 4, "max_inflight_waves": 1}), (3448, 4, 4097, {"n_iters": 4, "max_inflight_waves": 1}),
+    (9000, 4, 0, {"n_iters": 4, "max_inflight_waves": 1}), (500, 5, 0, {"first_iter": 13, "last_iter": 17}),
+    (500, 5, 0, {"zipf_window": 7, "zipf_theta": 0.5, "eta_min": 1e-9, "eta_max": 1e30, "graph_id": 3})])
+def test_ordered_layout_equals_the_window_kernel(P, backbone, paths, nodes, kw):  # noqa: F811
+    import torch
+    sg = synth.generate(backbone, 0.2, paths, 23)
+    if nodes:  # nodes that no path visits
+        sg.node_len = np.concatenate([sg.node_len, np.ones(nodes - sg.n_nodes, np.uint32)])
+    g = P.Graph.from_synth(sg)
+    a, b = g.new_coords(), g.new_coords()
+    for f, c in ((P.layout, a), (P.layout_noalloc, b)):
+        P.init_coords(g, c)
+        f(g, c, **kw)
+    torch.cuda.synchronize()
+    assert torch.equal(a, b)
+
+
+@pytest.mark.parametrize("span", [40, 60, 70])
+def test_ordered_layout_with_coincident_and_distant_points(P, span):  # noqa: F811
+    # the ranges of the update's short sequences: equal points, distances below 2^-48 and above 2^48; with the widest
+    # span squares overflow and both forms end with the same infinities and NaN
+    import torch
+    sg = synth.generate(300, 0.2, 4, 3)
+    g = P.Graph.from_synth(sg)
+    rng = np.random.default_rng(8)
+    c = (rng.normal(size=4 * g.n_nodes) * 2.0 ** rng.integers(-span, span, size=4 * g.n_nodes)).astype(np.float32)
+    c[rng.random(c.size) < 0.3] = 0.0
+    a, b = torch.from_numpy(c).cuda(), torch.from_numpy(c).cuda()
+    P.layout(g, a, n_iters=8)
+    P.layout_noalloc(g, b, n_iters=8)
+    torch.cuda.synchronize()
+    assert bool(((a == b) | (a.isnan() & b.isnan())).all())
+    assert span > 60 or bool(torch.isfinite(a).all())
