@@ -145,7 +145,7 @@ struct SegTables {
   uint32_t shift = 0, nseg = 0, xstride = 0;
   uint64_t* start = nullptr;   // [nseg + 1]
   uint32_t* path = nullptr;    // [nseg]
-  uint32_t* wseg = nullptr;    // [n_win + 1] first segment of every window
+  uint32_t* extra = nullptr;   // [n_paths] a path's first segment less the window it starts in
   uint32_t* count = nullptr;   // [nseg] histogram
   uint64_t* off = nullptr;     // [nseg + 1] first slot of every segment
   uint32_t* sbeg = nullptr;    // [kXcds + 1]
@@ -231,7 +231,7 @@ struct pgsgd_graph {
                     (void*)d_lqueue2, (void*)d_ordered, (void*)d_tile_seg, (void*)d_tile_off, (void*)d_tile_base, (void*)d_tile_queue})
       if (p) (void)hipFree(p);
     for (SegTables* t : {&sps, &loss})
-      for (void* p : {(void*)t->start, (void*)t->path, (void*)t->wseg, (void*)t->count, (void*)t->off,
+      for (void* p : {(void*)t->start, (void*)t->path, (void*)t->extra, (void*)t->count, (void*)t->off,
                       (void*)t->sbeg, (void*)t->xitem, (void*)t->queue})
         if (p) (void)hipFree(p);
     if (h_sums) (void)hipHostFree(h_sums);
@@ -900,10 +900,9 @@ pgsgd_status ensure_count_stream(pgsgd_graph* g) {
 pgsgd_status ensure_seg_tables(pgsgd_graph* g, SegTables& T, uint32_t shift, hipStream_t s) {
   if (T.start && T.shift == shift) return PGSGD_OK;
   HIP_TRY(hipStreamSynchronize(s));
-  const auto set = {(void**)&T.start, (void**)&T.path, (void**)&T.wseg, (void**)&T.count, (void**)&T.off,
+  const auto set = {(void**)&T.start, (void**)&T.path, (void**)&T.extra, (void**)&T.count, (void**)&T.off,
                     (void**)&T.sbeg, (void**)&T.xitem, (void**)&T.queue};
   free_set(g, set);
-  const uint64_t nwin = (g->S + (1ull << shift) - 1) >> shift;
   std::vector<uint64_t> start;
   std::vector<uint32_t> path;
   for (uint32_t p = 0; p < g->n_paths; ++p)
@@ -916,10 +915,10 @@ pgsgd_status ensure_seg_tables(pgsgd_graph* g, SegTables& T, uint32_t shift, hip
   start.push_back(g->S);
   const uint64_t nseg = path.size();
   if (nseg >= (1ull << 31)) return fail(PGSGD_ERR_UNSUPPORTED, "too many segments");
-  std::vector<uint32_t> wseg(nwin + 1), sbeg(kXcds + 1);
-  for (uint64_t w = 0, k = 0; w <= nwin; ++w) {  // first segment starting at or after the window's start
-    while (k < nseg && start[k] < (w << shift)) ++k;
-    wseg[w] = (uint32_t)(w == nwin ? nseg : k);
+  std::vector<uint32_t> extra(g->n_paths), sbeg(kXcds + 1);
+  for (uint32_t p = 0, k = 0; p < g->n_paths; ++p) {  // k: first segment starting at or after the path's start
+    while (k < nseg && start[k] < g->h_path_off[p]) ++k;
+    extra[p] = k - (uint32_t)(g->h_path_off[p] >> shift);
   }
   for (uint32_t x = 0, k = 0; x <= kXcds; ++x) {  // first segment starting at or after x * S / 8
     while (k < nseg && (unsigned __int128)start[k] * kXcds < (unsigned __int128)x * g->S) ++k;
@@ -934,7 +933,7 @@ pgsgd_status ensure_seg_tables(pgsgd_graph* g, SegTables& T, uint32_t shift, hip
     pgsgd_status e;
     if ((e = dev_alloc(g, &T.start, nseg + 1))) return e;
     if ((e = dev_alloc(g, &T.path, nseg))) return e;
-    if ((e = dev_alloc(g, &T.wseg, nwin + 1))) return e;
+    if ((e = dev_alloc(g, &T.extra, g->n_paths))) return e;
     if ((e = dev_alloc(g, &T.count, nseg))) return e;
     if ((e = dev_alloc(g, &T.off, nseg + 1))) return e;
     if ((e = dev_alloc(g, &T.sbeg, kXcds + 1))) return e;
@@ -942,7 +941,7 @@ pgsgd_status ensure_seg_tables(pgsgd_graph* g, SegTables& T, uint32_t shift, hip
     if ((e = dev_alloc(g, &T.queue, (size_t)2 * kXcds * 16))) return e;
     HIP_TRY(hipMemcpy(T.start, start.data(), sizeof(uint64_t) * (nseg + 1), hipMemcpyHostToDevice));
     HIP_TRY(hipMemcpy(T.path, path.data(), sizeof(uint32_t) * nseg, hipMemcpyHostToDevice));
-    HIP_TRY(hipMemcpy(T.wseg, wseg.data(), sizeof(uint32_t) * (nwin + 1), hipMemcpyHostToDevice));
+    HIP_TRY(hipMemcpy(T.extra, extra.data(), sizeof(uint32_t) * g->n_paths, hipMemcpyHostToDevice));
     HIP_TRY(hipMemcpy(T.sbeg, sbeg.data(), sizeof(uint32_t) * (kXcds + 1), hipMemcpyHostToDevice));
     HIP_TRY(launch_fill_u32(T.count, nseg, 0u, s));  // the histogram must start at zero
     return PGSGD_OK;
@@ -1624,10 +1623,10 @@ SpsWinLaunch sps_win_launch(const pgsgd_graph* g, const SegTables& T, const Stre
   W.win_shift = T.shift;
   W.n_seg = T.nseg;
   W.xstride = T.xstride;
-  W.count_blocks = (uint32_t)g->n_cu * 2;
+  W.count_blocks = (uint32_t)g->n_cu * (((size_t)g->path_slots * 8 + (size_t)T.nseg * 4) * 2 <= g->lds_limit ? 2 : 1);
   W.seg_start = T.start;
   W.seg_path = T.path;
-  W.wseg = T.wseg;
+  W.path_extra = T.extra;
   W.count = T.count;
   W.seg_off = T.off;
   W.sbeg = T.sbeg;
@@ -1657,7 +1656,7 @@ pgsgd_status loss_win_prepare(pgsgd_graph* g, const pgsgd_params* p, const Stres
       key.c3 == P.c3 && key.k0 == P.k0 && key.k1 == P.k1)
     return PGSGD_OK;
   key.tables = nullptr;
-  HIP_TRY(launch_sps_win_count_scan(*W, s));
+  HIP_TRY(launch_sps_win_count_scan(*W, !offsets_only, s));
   key.tables = g->loss.start;
   key.n_pairs = n_pairs;
   key.word2 = P.word2;
@@ -1665,6 +1664,21 @@ pgsgd_status loss_win_prepare(pgsgd_graph* g, const pgsgd_params* p, const Stres
   key.k0 = P.k0;
   key.k1 = P.k1;
   return PGSGD_OK;
+}
+
+// The tiles of one pass and its grid.  The tile's coordinates are staged where
+// their LDS fits and there are enough pairs to use them: staging reads the
+// 512 lines of 4,096 nodes once, not staging two scattered lines a pair.
+TileLaunch loss_tile_launch(const pgsgd_graph* g, const pgsgd_params* p, uint64_t n_pairs, bool grad,
+                            uint32_t* blocks) {
+  TileLaunch T{g->d_tile_seg, g->d_tile_off, g->d_tile_base, g->n_tiles, 1, false, g->d_tile_queue};
+  T.stage = loss_tile_lds_bytes(p->zipf_window, grad, true) + kTileStaticLds <= g->lds_limit &&
+            n_pairs >= 512ull * std::max(1u, g->n_tiles);
+  const uint32_t per_cu = grad && T.stage ? 1 : 2;  // blocks that a CU's LDS and waves hold
+  const uint32_t cap = per_cu * (uint32_t)g->n_cu;
+  T.split = loss_tile_split(g->n_tiles, cap, n_pairs, grad);
+  *blocks = (uint32_t)std::max<uint64_t>(1, std::min<uint64_t>((uint64_t)g->n_tiles * T.split, cap));
+  return T;
 }
 
 }  // namespace
@@ -1829,7 +1843,7 @@ pgsgd_status path_stress_impl(pgsgd_graph* g, const float* coords, uint32_t m, u
   if (coords_b) HIP_TRY(launch_to_work(coords_b, g->d_work2, g->n_nodes, g->d_inv, s));
   uint32_t parts = 0;
   if (windowed) {
-    HIP_TRY(launch_sps_win_count_scan(W, s));
+    HIP_TRY(launch_sps_win_count_scan(W, true, s));
     HIP_TRY(launch_sps_win(W, g->d_part_f, g->d_part_n, g->d_part_skip, &parts, s));
   } else {
     HIP_TRY(launch_sps(P, mode, g->d_part_f, g->d_part_n, g->d_part_skip, &parts, s));
@@ -1921,22 +1935,23 @@ pgsgd_status pgsgd_stress_forward(pgsgd_graph* g, const pgsgd_params* p, const f
   P.word2 = step;
   P.count = g->S ? n_pairs : 0;
   P.work = g->d_work;
-  if (P.count) HIP_TRY(launch_to_work(coords, g->d_work, g->n_nodes, g->d_inv, s));
+  auto copy_in = [&](uint32_t* zero) { return launch_to_work(coords, g->d_work, g->n_nodes, g->d_inv, s, zero); };
   uint32_t parts = kStressBlocks;
   if (P.count && resolve_schedule(p) == PGSGD_SCHEDULE_WINDOWED) {
     SpsWinLaunch W;
-    const bool tiles = loss_tile_lds_bytes(p->zipf_window, true) + kTileStaticLds <= g->lds_limit;
+    const bool tiles = loss_tile_lds_bytes(p->zipf_window, true, false) + kTileStaticLds <= g->lds_limit;
     if ((st = loss_win_prepare(g, p, P, n_pairs, s, &W, tiles))) return st;
     if (tiles) {
       if ((st = ensure_loss_tiles(g, s))) return st;
-      parts = std::max<uint32_t>(1, std::min<uint32_t>(g->n_tiles, 2u * (uint32_t)g->n_cu));
-      HIP_TRY(launch_fill_u32(g->d_tile_queue, 1, 0u, s));
-      const TileLaunch T{g->d_tile_seg, g->d_tile_off, g->d_tile_base, g->n_tiles, g->d_tile_queue};
+      HIP_TRY(copy_in(g->d_tile_queue));
+      const TileLaunch T = loss_tile_launch(g, p, n_pairs, false, &parts);
       HIP_TRY(launch_loss_tile_fwd(W, T, g->d_part_f, g->d_part_n, parts, s));
     } else {
+      HIP_TRY(copy_in(nullptr));
       HIP_TRY(launch_loss_win_fwd(W, g->d_part_f, g->d_part_n, kStressBlocks, s));
     }
   } else {
+    if (P.count) HIP_TRY(copy_in(nullptr));
     HIP_TRY(launch_stress_fwd(P, g->d_part_f, g->d_part_n, s));
   }
   HIP_TRY(launch_reduce_parts(g->d_part_f, g->d_part_n, parts, nullptr, nullptr, loss_dev, n_valid_dev, s));
@@ -1962,24 +1977,26 @@ pgsgd_status pgsgd_stress_backward(pgsgd_graph* g, const pgsgd_params* p, const 
   P.word2 = step;
   P.count = n_pairs;
   P.work = g->d_work;
-  HIP_TRY(launch_to_work(coords, g->d_work, g->n_nodes, g->d_inv, s));
+  auto copy_in = [&](uint32_t* zero) { return launch_to_work(coords, g->d_work, g->n_nodes, g->d_inv, s, zero); };
   if (resolve_schedule(p) == PGSGD_SCHEDULE_WINDOWED) {
     SpsWinLaunch W;
     // by tiles when their LDS image fits a block (it does for every window W up to ~10^4)
-    const bool tiles = loss_tile_lds_bytes(p->zipf_window, true) + kTileStaticLds <= g->lds_limit;
+    const bool tiles = loss_tile_lds_bytes(p->zipf_window, true, false) + kTileStaticLds <= g->lds_limit;
     if ((st = loss_win_prepare(g, p, P, n_pairs, s, &W, tiles))) return st;
     if (tiles) {
       if ((st = ensure_loss_tiles(g, s))) return st;
+      HIP_TRY(copy_in(g->d_tile_queue));
       if (g->n_tiles) {
-        HIP_TRY(launch_fill_u32(g->d_tile_queue, 1, 0u, s));
-        const TileLaunch T{g->d_tile_seg, g->d_tile_off, g->d_tile_base, g->n_tiles, g->d_tile_queue};
-        const uint32_t blocks = std::min<uint32_t>(g->n_tiles, 2u * (uint32_t)g->n_cu);
+        uint32_t blocks = 0;
+        const TileLaunch T = loss_tile_launch(g, p, n_pairs, true, &blocks);
         HIP_TRY(launch_loss_tile_bwd(W, T, grad_out_dev, n_valid_dev, grad_coords, blocks, s));
       }
     } else {
+      HIP_TRY(copy_in(nullptr));
       HIP_TRY(launch_loss_win_bwd(W, grad_out_dev, n_valid_dev, grad_coords, kStressBlocks, s));
     }
   } else {
+    HIP_TRY(copy_in(nullptr));
     HIP_TRY(launch_stress_bwd(P, grad_out_dev, n_valid_dev, grad_coords, s));
   }
   return ok();

@@ -5,6 +5,8 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <algorithm>
+
 #include "internal.h"
 
 namespace pgsgd {
@@ -79,7 +81,7 @@ struct SpsWinLaunch {
   uint32_t count_blocks;
   const uint64_t* seg_start;  // [n_seg + 1], seg_start[n_seg] = S
   const uint32_t* seg_path;   // [n_seg]
-  const uint32_t* wseg;       // [n_win + 1] first segment of every window
+  const uint32_t* path_extra; // [n_paths] a path's first segment less the window it starts in
   uint32_t* count;            // [n_seg] histogram (zeroed again by the scan)
   uint64_t* seg_off;          // [n_seg + 1] first slot of every segment
   const uint32_t* sbeg;       // [kXcds + 1] first segment of every run
@@ -87,7 +89,8 @@ struct SpsWinLaunch {
   uint64_t* queue;            // [2][kXcds][16] item counters of the two passes (zeroed by the scan)
   uint64_t loss_pairs;        // the loss's window-major pairs (reading R22): the number of plain pairs; 0 = SPS
 };
-hipError_t launch_sps_win_count_scan(const SpsWinLaunch& W, hipStream_t s);
+// runs: also the runs' item prefixes and counters, which the passes by tiles do not read
+hipError_t launch_sps_win_count_scan(const SpsWinLaunch& W, bool runs, hipStream_t s);
 hipError_t launch_sps_win(const SpsWinLaunch& W, double* part_f, uint64_t* part_n, uint64_t* part_skip,
                           uint32_t* n_parts, hipStream_t s);
 // The loss (reading R22) over the segments' slots counted with loss_pairs:
@@ -104,22 +107,36 @@ hipError_t launch_loss_win_bwd(const SpsWinLaunch& W, const float* grad_out, con
 // entry; other endpoints are added directly.  The pairs are the window-major
 // loss pairs of W, the same slots as launch_loss_win_bwd.
 constexpr uint32_t kTileNodes = 2048;
-constexpr uint32_t kTileMaxSeg = 256;
-constexpr uint32_t kTileThreads = 512;
+constexpr uint32_t kTileMaxSeg = 256;    // a segment's number in its tile is a byte of k_loss_tile's guide
+constexpr uint32_t kTileGuide = 1024;
+constexpr uint32_t kTileThreads = 1024;
 struct TileLaunch {
   const uint32_t* seg;
   const uint32_t* off;
   const uint32_t* base;
   uint32_t n_tiles;
+  uint32_t split;  // parts of a tile's pairs, a unit of work each
+  bool stage;      // the tile's coordinates in LDS
   uint32_t* queue;
 };
+// Parts of a tile.  A gradient unit zeroes and flushes the tile's whole image,
+// so its tiles stay whole while they fill the blocks; below that (and always
+// in the forward pass, which has no image) a tile is cut until the blocks have
+// `rounds` units each, with at least one pair for every thread.
+inline uint32_t loss_tile_split(uint32_t n_tiles, uint32_t blocks, uint64_t n_pairs, bool grad) {
+  const uint64_t rounds = grad ? 1 : 4;
+  const uint64_t want = (rounds * blocks + n_tiles - 1) / std::max(1u, n_tiles);
+  const uint64_t room = n_pairs / ((uint64_t)kTileThreads * std::max(1u, n_tiles));
+  if (grad && n_tiles >= blocks) return 1;
+  return (uint32_t)std::max<uint64_t>(1, std::min(want, room));
+}
 hipError_t launch_loss_tile_bwd(const SpsWinLaunch& W, const TileLaunch& T, const float* grad_out,
                                 const uint64_t* n_valid, float* grad, uint32_t blocks, hipStream_t s);
 // The forward pass over the same tiles: per-block sums into part_f / part_n[0 .. blocks).
 hipError_t launch_loss_tile_fwd(const SpsWinLaunch& W, const TileLaunch& T, double* part_f, uint64_t* part_n,
                                 uint32_t blocks, hipStream_t s);
-size_t loss_tile_lds_bytes(uint32_t W, bool grad);  // dynamic LDS of k_loss_tile
-constexpr size_t kTileStaticLds = 9 * 1024;   // static LDS of k_loss_tile (a tile's segment table), rounded up
+size_t loss_tile_lds_bytes(uint32_t W, bool grad, bool stage);  // dynamic LDS of k_loss_tile
+constexpr size_t kTileStaticLds = 12 * 1024;  // static LDS of k_loss_tile (a tile's segment table), rounded up
 // out[g] = the lowest device node id over the steps [start[g], start[g + 1])
 hipError_t launch_segment_min_node(const StepRec* rec, const uint64_t* start, uint32_t nseg, uint32_t* out,
                                    hipStream_t s);

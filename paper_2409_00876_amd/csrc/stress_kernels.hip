@@ -61,20 +61,61 @@ __device__ __forceinline__ double stress_xy(float xa, float ya, float xb, float 
   return e * e;
 }
 
-// v_a - v_b from the interleaved copy in FP64; returns |v_a - v_b|.
-__device__ __forceinline__ double delta_work(const float2* __restrict__ W, uint64_t a, uint64_t b, double& dx,
-                                             double& dy) {
+// sqrt(x) for x = 0 or in [2^-300, 2^260], and n / d for quotients well inside
+// FP64's range (float32 coordinates and lengths below 2^63 cannot leave
+// either), correctly rounded as by sqrt and /: the compiler's own sequences
+// without their scaling, Goldschmidt's iteration for the root and Newton's for
+// the reciprocal, each with a last step on the residual (Markstein, IBM J. Res.
+// Dev. 34, 1990).  NaN where an argument is infinite.
+__device__ __forceinline__ double root64(double x) {
+  const double y = __builtin_amdgcn_rsq(__builtin_fmax(x, 0x1p-1000));  // x = 0 gives 0 below
+  double g = x * y, h = 0.5 * y;
+  const double r = __builtin_fma(-h, g, 0.5);
+  g = __builtin_fma(g, r, g);
+  h = __builtin_fma(h, r, h);
+  g = __builtin_fma(__builtin_fma(-g, g, x), h, g);
+  return __builtin_fma(__builtin_fma(-g, g, x), h, g);
+}
+
+__device__ __forceinline__ double quotient64(double n, double d) {
 #pragma clang fp contract(off)
-  const float2 va = W[a], vb = W[b];
+  double c = __builtin_amdgcn_rcp(d);
+  c = __builtin_fma(c, __builtin_fma(-d, c, 1.0), c);
+  c = __builtin_fma(c, __builtin_fma(-d, c, 1.0), c);
+  const double q = n * c;
+  return __builtin_fma(__builtin_fma(-d, q, n), c, q);
+}
+
+// ((|v| - d) / d)^2 for v = (dx, dy) and 1 <= d < 2^63; NaN where |v| is infinite.
+__device__ __forceinline__ double exact_stress(double dx, double dy, double d) {
+#pragma clang fp contract(off)
+  const double e = quotient64(root64(dx * dx + dy * dy) - d, d);
+  return e * e;
+}
+
+// stress_xy by the short sequences, taken again the general way where it is not finite.
+__device__ __forceinline__ double pair_stress(float2 va, float2 vb, double d) {
+  const double st = exact_stress((double)va.x - (double)vb.x, (double)va.y - (double)vb.y, d);
+  return st - st == 0.0 ? st : stress_xy(va.x, va.y, vb.x, vb.y, d);
+}
+
+// v_a - v_b in FP64; returns |v_a - v_b|.
+__device__ __forceinline__ double delta_xy(float2 va, float2 vb, double& dx, double& dy) {
+#pragma clang fp contract(off)
   dx = (double)va.x - (double)vb.x;
   dy = (double)va.y - (double)vb.y;
-  return sqrt(dx * dx + dy * dy);
+  return root64(dx * dx + dy * dy);
+}
+
+// scale (mag - d) / d^2 / mag, the factor of (dx, dy) in a pair's gradient.
+__device__ __forceinline__ double gradient_factor(double scale, double mag, double d) {
+#pragma clang fp contract(off)
+  return quotient64(quotient64(scale * (mag - d), d * d), mag);
 }
 
 // The stress of endpoints a and b of the interleaved copy (W[e] = (x, y) of endpoint e).
 __device__ __forceinline__ double stress_work(const float2* __restrict__ W, uint64_t a, uint64_t b, double d) {
-  const float2 va = W[a], vb = W[b];
-  return stress_xy(va.x, va.y, vb.x, vb.y, d);
+  return pair_stress(W[a], W[b], d);
 }
 
 // Outlier collection: a pair whose stress exceeds the threshold is
@@ -290,7 +331,10 @@ __device__ __forceinline__ uint64_t uniform_u64(uint64_t v) {
 // The segment histogram: step s owns the plain pairs q = m*s .. m*s+m-1 (all
 // of the path of s); each draws its i as k_sps does and counts its segment.
 // With loss_pairs set, the loss's plain pairs q < loss_pairs are counted
-// instead.
+// instead.  The segments start at the window starts and the path starts, so
+// step i of path p lies in segment (i >> win_shift) + path_extra[p], the path
+// starts inside windows up to that of p (a search of the window's segments,
+// with three random loads, bound the count of 1e7 loss pairs: 70 us, now 41).
 __global__ __launch_bounds__(1024) void k_sps_win_count(SpsWinLaunch W) {
   extern __shared__ __align__(16) char lds[];
   const StressLaunch& P = W.P;
@@ -304,31 +348,19 @@ __global__ __launch_bounds__(1024) void k_sps_win_count(SpsWinLaunch W) {
   for (uint64_t q = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; q < W.loss_pairs; q += stride) {
     const Rand4 r = philox10((uint32_t)q, (uint32_t)(q >> 32), P.word2, P.c3, P.k0, P.k1);
     const uint64_t i = mulhi64((uint64_t)r.r0 | ((uint64_t)r.r1 << 32), P.S);
-    const uint32_t w = (uint32_t)(i >> W.win_shift);
-    uint32_t lo = W.wseg[w], hi = W.wseg[w + 1];
-    while (hi - lo > 1) {
-      const uint32_t mid = lo + ((hi - lo) >> 1);
-      if (W.seg_start[mid] <= i) lo = mid;
-      else hi = mid;
-    }
-    atomicAdd(&hist[lo], 1u);
+    const uint32_t p = find_path(off, P.path_top, i);
+    atomicAdd(&hist[W.path_extra[p] + (uint32_t)(i >> W.win_shift)], 1u);
   }
   const uint64_t sps_steps = W.loss_pairs ? 0 : P.S;
   for (uint64_t s = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; s < sps_steps; s += stride) {
     const uint32_t p = find_path(off, P.path_top, s);
     const uint64_t start = off[p], len = off[p + 1] - start;
+    const uint32_t extra = W.path_extra[p];
     for (uint32_t k = 0; k < P.m; ++k) {
       const uint64_t q = (uint64_t)P.m * s + k;
       const Rand4 r = philox10((uint32_t)q, (uint32_t)(q >> 32), 0u, P.c3, P.k0, P.k1);
       const uint64_t i = start + mulhi64((uint64_t)r.r0 | ((uint64_t)r.r1 << 32), len);
-      const uint32_t w = (uint32_t)(i >> W.win_shift);
-      uint32_t lo = W.wseg[w], hi = W.wseg[w + 1];  // the segments of window w: the last with start <= i
-      while (hi - lo > 1) {
-        const uint32_t mid = lo + ((hi - lo) >> 1);
-        if (W.seg_start[mid] <= i) lo = mid;
-        else hi = mid;
-      }
-      atomicAdd(&hist[lo], 1u);
+      atomicAdd(&hist[extra + (uint32_t)(i >> W.win_shift)], 1u);
     }
   }
   __syncthreads();
@@ -336,13 +368,12 @@ __global__ __launch_bounds__(1024) void k_sps_win_count(SpsWinLaunch W) {
     if (hist[k]) atomicAdd(&W.count[k], hist[k]);
 }
 
-// One block of 1024 threads: seg_off = exclusive prefix of the counts, the
-// per-run item prefixes and zeroed item counters, then the histogram back to
-// zero.  Each thread owns a contiguous chunk; every stage is a chunk pass and
-// a block scan.
-// One block.  The histogram is read into LDS with coalesced loads (and
-// cleared for the next use), so the chunk passes below read LDS, not memory.
-__global__ __launch_bounds__(1024) void k_sps_win_scan(SpsWinLaunch W) {
+// One block of 1024 threads: seg_off = exclusive prefix of the counts and, with
+// `runs`, the per-run item prefixes and zeroed item counters (the passes by
+// tiles read seg_off alone).  Each thread owns a contiguous chunk; every stage
+// is a chunk pass and a block scan.  The histogram is read into LDS with
+// coalesced loads (and cleared for the next use), so the chunk passes read LDS.
+__global__ __launch_bounds__(1024) void k_sps_win_scan(SpsWinLaunch W, uint32_t runs) {
   extern __shared__ __align__(16) char lds[];
   __shared__ uint64_t lds16[16];
   uint32_t* cnt = reinterpret_cast<uint32_t*>(lds);
@@ -364,6 +395,7 @@ __global__ __launch_bounds__(1024) void k_sps_win_scan(SpsWinLaunch W) {
     acc += cnt[k];
   }
   if (threadIdx.x == 0) W.seg_off[n] = total;
+  if (!runs) return;
   for (uint32_t run = 0; run < kXcds; ++run) {  // run x: segments [sbeg[x], sbeg[x + 1])
     const uint32_t b = W.sbeg[run], e = W.sbeg[run + 1], nq = e - b;
     const uint32_t rper = (nq + blockDim.x - 1) / blockDim.x;
@@ -457,28 +489,6 @@ __global__ __launch_bounds__(kPair ? 1024 : 512) void k_sps_win(SpsWinLaunch W, 
 // part_f: per-block sum of the pair means; part_n: per-block pair count.
 // ---------------------------------------------------------------------------
 constexpr uint32_t kExactRows = 256, kExactCols = 512;
-
-// ((|v| - d) / d)^2 for v = (dx, dy), |dx|, |dy| 0 or in [2^-150, 2^130], 1 <= d < 2^63, each operation rounded
-// as by sqrt and /: Goldschmidt's iteration for the root and Newton's for the reciprocal, each with a last step on
-// the residual (Markstein, IBM J. Res. Dev. 34, 1990).  NaN where |v| is infinite.
-__device__ __forceinline__ double exact_stress(double dx, double dy, double d) {
-#pragma clang fp contract(off)
-  const double x = dx * dx + dy * dy;
-  const double y = __builtin_amdgcn_rsq(__builtin_fmax(x, 0x1p-1000));  // x = 0 gives 0 below
-  double g = x * y, h = 0.5 * y;
-  const double r = __builtin_fma(-h, g, 0.5);
-  g = __builtin_fma(g, r, g);
-  h = __builtin_fma(h, r, h);
-  g = __builtin_fma(__builtin_fma(-g, g, x), h, g);
-  g = __builtin_fma(__builtin_fma(-g, g, x), h, g);
-  double c = __builtin_amdgcn_rcp(d);
-  c = __builtin_fma(c, __builtin_fma(-d, c, 1.0), c);
-  c = __builtin_fma(c, __builtin_fma(-d, c, 1.0), c);
-  const double n = g - d;
-  const double q = n * c;
-  const double e = __builtin_fma(__builtin_fma(-d, q, n), c, q);
-  return e * e;
-}
 
 // Pos: double (differences of positions below 2^53 are exact: one instruction instead of six), or int64_t.
 template <typename Pos>
@@ -711,9 +721,9 @@ __global__ __launch_bounds__(256) void k_stress_bwd(StressLaunch P, const float*
     double d;
     if (!loss_pair(P, off, zipf, guide, q, a, b, d)) continue;
     double dx, dy;
-    const double mag = delta_work(P.work, a, b, dx, dy);
+    const double mag = delta_xy(P.work[a], P.work[b], dx, dy);
     if (mag == 0.0) continue;
-    const double c = scale * (mag - d) / (d * d) / mag;
+    const double c = gradient_factor(scale, mag, d);
     const float gx = (float)(c * dx), gy = (float)(c * dy);
     float* __restrict__ GX = grad;
     float* __restrict__ GY = grad + 2ull * P.n_nodes;
@@ -799,9 +809,9 @@ __global__ __launch_bounds__(256) void k_loss_win(SpsWinLaunch W, const float* _
       ++nv;
     } else {
       double dx, dy;
-      const double mag = delta_work(P.work, a, b, dx, dy);
+      const double mag = delta_xy(P.work[a], P.work[b], dx, dy);
       if (mag == 0.0) continue;
-      const double c = scale * (mag - d) / (d * d) / mag;
+      const double c = gradient_factor(scale, mag, d);
       const float gx = (float)(c * dx), gy = (float)(c * dy);
       if (P.inv) {  // the gradient is in the caller's node order
         a = 2ull * P.inv[a >> 1] + (a & 1);
@@ -830,15 +840,25 @@ __global__ __launch_bounds__(256) void k_loss_win(SpsWinLaunch W, const float* _
 // paths), so most of a tile's adjoint lands in an LDS image of that range and
 // reaches memory once per touched entry instead of once per pair.
 // ---------------------------------------------------------------------------
-size_t loss_tile_lds_bytes(uint32_t W, bool grad) {
+size_t loss_tile_lds_bytes(uint32_t W, bool grad, bool stage) {
   const size_t head = ((size_t)(W + 1) * 4 + (size_t)(kGuideSize + 1) * 2 + 15) & ~(size_t)15;
-  return head + (grad ? (size_t)4 * kTileNodes * sizeof(float2) : 0);
+  return head + (size_t)4 * kTileNodes * sizeof(float2) * ((grad ? 1 : 0) + (stage ? 1 : 0));
 }
 
 // kGrad = false: the forward pass over the same tiles (per-block sums of the
-// stress and the valid-pair count; the tile order keeps a block's coordinate
-// reads within one range of node ids).
-template <bool kGrad>
+// stress and the valid-pair count).
+//
+// kStage: the coordinates of the tile's ids are copied to LDS first, with
+// coalesced loads.  A pair's two records and two coordinates are scattered
+// 8 and 16-byte loads, 64 cache-line requests each for a wave, and those
+// requests bound the kernel, not latency (twice the waves: 231 -> 223 us; the
+// parts of the forward pass over 1e7 pairs: draws 80, records 74, coordinates
+// 78 us); a tile's 22K pairs share 4,096 nodes.  The gradient's image holds x
+// and y in planes of their own, so the adds of a wave use all LDS banks.
+//
+// A unit of work is one of T.split equal parts of a tile's pairs (see
+// loss_tile_split for where a tile is cut).
+template <bool kGrad, bool kStage>
 __global__ __launch_bounds__(kTileThreads) void k_loss_tile(SpsWinLaunch W, TileLaunch T,
                                                            const float* __restrict__ grad_out,
                                                            const uint64_t* __restrict__ n_valid,
@@ -850,15 +870,19 @@ __global__ __launch_bounds__(kTileThreads) void k_loss_tile(SpsWinLaunch W, Tile
   __shared__ uint64_t s_flat[kTileMaxSeg + 1];  // slot prefix over the tile's segments
   __shared__ uint64_t s_slot[kTileMaxSeg];      // first slot of each segment
   __shared__ uint64_t s_start[kTileMaxSeg];     // first step of each segment
+  __shared__ uint64_t s_pst[kTileMaxSeg];       // first step of its path
   __shared__ uint32_t s_len[kTileMaxSeg];       // steps of each segment
-  __shared__ uint32_t s_path[kTileMaxSeg];
-  __shared__ uint32_t s_tile;
+  __shared__ uint32_t s_plen[kTileMaxSeg];      // steps of its path
+  __shared__ uint8_t s_near[kTileGuide];        // the segment of slots 0, 1 << shift, 2 << shift, ...
+  __shared__ uint32_t s_unit;
   const StressLaunch& P = W.P;
   uint32_t* zipf = reinterpret_cast<uint32_t*>(lds);
   uint16_t* guide = reinterpret_cast<uint16_t*>(lds + (size_t)(P.W + 1) * 4);
-  float2* acc = reinterpret_cast<float2*>(
-      lds + (((size_t)(P.W + 1) * 4 + (size_t)(kGuideSize + 1) * 2 + 15) & ~(size_t)15));
   constexpr uint32_t kAcc = 4 * kTileNodes;  // entries: 2 * kTileNodes nodes x 2 endpoints
+  float* acc_x =
+      reinterpret_cast<float*>(lds + (((size_t)(P.W + 1) * 4 + (size_t)(kGuideSize + 1) * 2 + 15) & ~(size_t)15));
+  float* acc_y = acc_x + kAcc;
+  float2* xy = reinterpret_cast<float2*>(acc_x + (kGrad ? 2 * kAcc : 0));
   for (uint32_t k = threadIdx.x; k <= P.W; k += blockDim.x) zipf[k] = P.zipf[k];
   for (uint32_t k = threadIdx.x; k <= kGuideSize; k += blockDim.x) guide[k] = P.guide[k];
   double scale = 0.0;
@@ -877,68 +901,97 @@ __global__ __launch_bounds__(kTileThreads) void k_loss_tile(SpsWinLaunch W, Tile
     unsafeAtomicAdd(&GY[a], gy);
   };
   for (;;) {
-    __syncthreads();  // the previous tile's flush (and the tables above) are done
-    if (threadIdx.x == 0) s_tile = atomicAdd(T.queue, 1u);
+    __syncthreads();  // the previous unit's flush (and the tables above) are done
+    if (threadIdx.x == 0) s_unit = atomicAdd(T.queue, 1u);
     __syncthreads();
-    const uint32_t t = s_tile;
+    const uint32_t t = s_unit / T.split, part = s_unit % T.split;
     if (t >= T.n_tiles) break;
     const uint64_t base = T.base[t];
     const uint32_t k0 = T.off[t];
     const uint32_t nk = T.off[t + 1] - k0;
     if (kGrad)
-      for (uint32_t e = threadIdx.x; e < kAcc; e += blockDim.x) acc[e] = make_float2(0.0f, 0.0f);
+      for (uint32_t e = threadIdx.x; e < 2 * kAcc; e += blockDim.x) acc_x[e] = 0.0f;
+    if (kStage) {
+      const uint32_t ends = (uint32_t)min((uint64_t)kAcc, 2 * (P.n_nodes - base));
+      for (uint32_t e = threadIdx.x; e < ends; e += blockDim.x) xy[e] = P.work[2 * base + e];
+    }
+    auto coords = [&](uint64_t a) -> float2 {
+      const uint64_t e = a - 2 * base;  // wraps to huge below the base
+      return kStage && e < kAcc ? xy[e] : P.work[a];
+    };
     for (uint32_t k = threadIdx.x; k < nk; k += blockDim.x) {
       const uint32_t g = T.seg[k0 + k];
       s_slot[k] = W.seg_off[g];
       s_flat[k + 1] = W.seg_off[g + 1] - W.seg_off[g];
       s_start[k] = W.seg_start[g];
       s_len[k] = (uint32_t)(W.seg_start[g + 1] - W.seg_start[g]);
-      s_path[k] = W.seg_path[g];
+      const uint32_t p = W.seg_path[g];
+      s_pst[k] = P.path_off[p];
+      s_plen[k] = (uint32_t)(P.path_off[p + 1] - P.path_off[p]);
     }
     __syncthreads();
-    if (threadIdx.x == 0) {
-      s_flat[0] = 0;
-      for (uint32_t k = 0; k < nk; ++k) s_flat[k + 1] += s_flat[k];
+    if (threadIdx.x < 64) {  // inclusive prefix by one wave, 64 segments at a time
+      uint64_t carry = 0;
+      if (threadIdx.x == 0) s_flat[0] = 0;
+      for (uint32_t k = 0; k < nk; k += 64) {
+        uint64_t x = k + threadIdx.x < nk ? s_flat[k + threadIdx.x + 1] : 0;
+#pragma unroll
+        for (uint32_t d = 1; d < 64; d <<= 1) {
+          const uint64_t y = __shfl_up(x, d, 64);
+          if (threadIdx.x >= d) x += y;
+        }
+        x += carry;
+        if (k + threadIdx.x < nk) s_flat[k + threadIdx.x + 1] = x;
+        carry = __shfl(x, 63, 64);
+      }
     }
     __syncthreads();
     const uint64_t total = s_flat[nk];
-    for (uint64_t f = threadIdx.x; f < total; f += blockDim.x) {
-      uint32_t lo = 0, hi = nk;  // the segment k with s_flat[k] <= f < s_flat[k + 1]
+    uint32_t shift = 6;  // the guide's step: it spans the tile's slots
+    while ((total >> shift) >= kTileGuide) ++shift;
+    for (uint32_t e = threadIdx.x; ((uint64_t)e << shift) < total; e += blockDim.x) {
+      uint32_t lo = 0, hi = nk;  // the segment k with s_flat[k] <= e << shift < s_flat[k + 1]
       while (hi - lo > 1) {
         const uint32_t mid = (lo + hi) >> 1;
-        if (s_flat[mid] <= f) lo = mid;
+        if (s_flat[mid] <= (uint64_t)e << shift) lo = mid;
         else hi = mid;
       }
+      s_near[e] = (uint8_t)lo;
+    }
+    __syncthreads();
+    const uint64_t f_end = total * (part + 1) / T.split;
+    for (uint64_t f = total * part / T.split + threadIdx.x; f < f_end; f += blockDim.x) {
+      uint32_t lo = s_near[f >> shift];  // the segment k with s_flat[k] <= f < s_flat[k + 1]
+      while (s_flat[lo + 1] <= f) ++lo;
       const uint64_t u = s_slot[lo] + (f - s_flat[lo]);
-      const uint32_t p = s_path[lo];
-      const uint64_t pst = P.path_off[p];
-      const uint64_t plen = P.path_off[p + 1] - pst;
+      const uint64_t pst = s_pst[lo], plen = s_plen[lo];
       const Rand4 r = philox10((uint32_t)u, (uint32_t)(u >> 32), P.word2, W.slot_c3, P.k0, P.k1);
-      const uint64_t i = s_start[lo] + mulhi64((uint64_t)r.r0 | ((uint64_t)r.r1 << 32), s_len[lo]);
+      const uint64_t i = s_start[lo] + mulhi64(r.r0, r.r1, s_len[lo]);
       uint64_t j, a, b;
       double d;
       if (!partner_power_law(i, pst, plen, r.r2, r.r3, zipf, guide, P.W, j)) continue;
       if (!pair_terms(P.rec, i, j, r.r3 & 1u, (r.r3 >> 1) & 1u, a, b, d) || a == b) continue;
+      const float2 va = coords(a), vb = coords(b);
       if (!kGrad) {
-        sum += stress_work(P.work, a, b, d);
+        sum += pair_stress(va, vb, d);
         ++nv;
         continue;
       }
       double dx, dy;
-      const double mag = delta_work(P.work, a, b, dx, dy);
+      const double mag = delta_xy(va, vb, dx, dy);
       if (mag == 0.0) continue;
-      const double c = scale * (mag - d) / (d * d) / mag;
+      const double c = gradient_factor(scale, mag, d);
       const float gx = (float)(c * dx), gy = (float)(c * dy);
-      const uint64_t oa = (a >> 1) - base, ob = (b >> 1) - base;  // wraps to huge below the base
-      if (oa < 2ull * kTileNodes) {
-        atomicAdd(&acc[(oa << 1) | (a & 1)].x, gx);
-        atomicAdd(&acc[(oa << 1) | (a & 1)].y, gy);
+      const uint64_t ea = a - 2 * base, eb = b - 2 * base;  // wrap to huge below the base
+      if (ea < kAcc) {
+        atomicAdd(&acc_x[ea], gx);
+        atomicAdd(&acc_y[ea], gy);
       } else {
         global_add(a, gx, gy);
       }
-      if (ob < 2ull * kTileNodes) {
-        atomicAdd(&acc[(ob << 1) | (b & 1)].x, -gx);
-        atomicAdd(&acc[(ob << 1) | (b & 1)].y, -gy);
+      if (eb < kAcc) {
+        atomicAdd(&acc_x[eb], -gx);
+        atomicAdd(&acc_y[eb], -gy);
       } else {
         global_add(b, -gx, -gy);
       }
@@ -946,9 +999,8 @@ __global__ __launch_bounds__(kTileThreads) void k_loss_tile(SpsWinLaunch W, Tile
     if (kGrad) {
       __syncthreads();
       for (uint32_t e = threadIdx.x; e < kAcc; e += blockDim.x) {
-        const float2 v = acc[e];
-        const uint64_t node = base + (e >> 1);
-        if ((v.x != 0.0f || v.y != 0.0f) && node < P.n_nodes) global_add(2ull * node + (e & 1), v.x, v.y);
+        const float vx = acc_x[e], vy = acc_y[e];
+        if ((vx != 0.0f || vy != 0.0f) && 2 * base + e < 2 * P.n_nodes) global_add(2 * base + e, vx, vy);
       }
     }
   }
@@ -1081,12 +1133,12 @@ hipError_t launch_reduce_sps(const StressLaunch& P, const double* part_f, const 
   return hipGetLastError();
 }
 
-hipError_t launch_sps_win_count_scan(const SpsWinLaunch& W, hipStream_t s) {
+hipError_t launch_sps_win_count_scan(const SpsWinLaunch& W, bool runs, hipStream_t s) {
   const size_t lds = (size_t)W.P.path_slots * 8 + (size_t)W.n_seg * 4;
   hipLaunchKernelGGL(k_sps_win_count, dim3(W.count_blocks), dim3(1024), lds, s, W);
   hipError_t e = hipGetLastError();
   if (e) return e;
-  hipLaunchKernelGGL(k_sps_win_scan, dim3(1), dim3(1024), (size_t)W.n_seg * 4, s, W);
+  hipLaunchKernelGGL(k_sps_win_scan, dim3(1), dim3(1024), (size_t)W.n_seg * 4, s, W, runs ? 1u : 0u);
   return hipGetLastError();
 }
 
@@ -1150,18 +1202,28 @@ hipError_t launch_loss_win_bwd(const SpsWinLaunch& W, const float* grad_out, con
   return hipGetLastError();
 }
 
+template <bool kGrad>
+static hipError_t launch_loss_tile(const SpsWinLaunch& W, const TileLaunch& T, const float* grad_out,
+                                   const uint64_t* n_valid, float* grad, double* part_f, uint64_t* part_n,
+                                   uint32_t blocks, hipStream_t s) {
+  const size_t lds = loss_tile_lds_bytes(W.P.W, kGrad, T.stage);
+  if (T.stage)
+    hipLaunchKernelGGL((k_loss_tile<kGrad, true>), dim3(blocks), dim3(kTileThreads), lds, s, W, T, grad_out, n_valid,
+                       grad, part_f, part_n);
+  else
+    hipLaunchKernelGGL((k_loss_tile<kGrad, false>), dim3(blocks), dim3(kTileThreads), lds, s, W, T, grad_out, n_valid,
+                       grad, part_f, part_n);
+  return hipGetLastError();
+}
+
 hipError_t launch_loss_tile_bwd(const SpsWinLaunch& W, const TileLaunch& T, const float* grad_out,
                                 const uint64_t* n_valid, float* grad, uint32_t blocks, hipStream_t s) {
-  hipLaunchKernelGGL(k_loss_tile<true>, dim3(blocks), dim3(kTileThreads), loss_tile_lds_bytes(W.P.W, true), s, W,
-                     T, grad_out, n_valid, grad, nullptr, nullptr);
-  return hipGetLastError();
+  return launch_loss_tile<true>(W, T, grad_out, n_valid, grad, nullptr, nullptr, blocks, s);
 }
 
 hipError_t launch_loss_tile_fwd(const SpsWinLaunch& W, const TileLaunch& T, double* part_f, uint64_t* part_n,
                                 uint32_t blocks, hipStream_t s) {
-  hipLaunchKernelGGL(k_loss_tile<false>, dim3(blocks), dim3(kTileThreads), loss_tile_lds_bytes(W.P.W, false), s,
-                     W, T, nullptr, nullptr, nullptr, part_f, part_n);
-  return hipGetLastError();
+  return launch_loss_tile<false>(W, T, nullptr, nullptr, nullptr, part_f, part_n, blocks, s);
 }
 
 hipError_t launch_segment_min_node(const StepRec* rec, const uint64_t* start, uint32_t nseg, uint32_t* out,

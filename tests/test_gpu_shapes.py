@@ -121,3 +121,32 @@ def test_ordered_layout_with_coincident_and_distant_points(P, span):  # noqa: F8
     torch.cuda.synchronize()
     assert bool(((a == b) | (a.isnan() & b.isnan())).all())
     assert span > 60 or bool(torch.isfinite(a).all())
+
+
+# few pairs (tiles not staged, one unit each), a tile cut into many units, every tile staged, a zipf window whose
+# tables leave no room for the staged coordinates (3,500 and more) and one without room for tiles, renumbered ids
+@pytest.mark.parametrize("backbone,paths,pairs,window,renumber", [
+    (300, 3, 40, 1000, "auto"), (900, 4, 60000, 1000, "auto"), (9000, 5, 200, 1000, "auto"),
+    (9000, 5, 300000, 1000, "always"), (5000, 6, 100001, 4000, "auto"), (5000, 6, 30011, 20000, "auto")])
+def test_loss_tiles_at_their_split_sizes(P, backbone, paths, pairs, window, renumber):  # noqa: F811
+    import torch
+    sg = synth.generate(backbone, 0.2, paths, 31)
+    og, g = O.Graph.from_synth(sg), P.Graph.from_synth(sg, renumber=renumber)
+    rng = np.random.default_rng(pairs)
+    c = (O.init_coords(og) + rng.normal(scale=5.0, size=4 * sg.n_nodes)).astype(np.float32)
+    t = torch.from_numpy(c).cuda()
+    kw = dict(seed=11, zipf_window=window)
+    for step in (0, 3):
+        ol, ov, ograd = O.stress_loss_grad_windowed(og, c, pairs, seed=11, step=step, window=window)
+        loss, nv = P.stress_forward(g, t, pairs, step, **kw)
+        grad = torch.zeros_like(t)
+        P.stress_backward(g, t, pairs, step, torch.ones(1, device="cuda"), nv, grad, **kw)
+        assert int(nv.item()) == ov
+        assert abs(loss.item() - ol) <= 1e-5 * abs(ol)
+        err = np.abs(grad.cpu().numpy().astype(np.float64) - ograd)
+        assert np.all(err <= 1e-4 * np.abs(ograd) + 1e-6 * np.abs(ograd).max())
+    t[: 2 * sg.n_nodes] = float("inf")  # as the plain FP64 sum
+    assert np.isnan(P.stress_forward(g, t, pairs, 0, **kw)[0].item())
+    t[: 2 * sg.n_nodes] = 0.0
+    t[0] = float("inf")
+    assert P.stress_forward(g, t, pairs, 0, **kw)[0].item() in (float("inf"), 0.0) or pairs < 1000
