@@ -750,12 +750,13 @@ namespace {
 // nodes the cap is n_nodes / 2048 waves, one or two per XCD, whose runs repeat
 // to about 3e-4 of the coordinates (one wave: exactly) where more waves would
 // move the layout by 1e-3; from there on n_nodes / 64 waves up to 1,024, and
-// n_nodes / per_wave where that is more.
+// where that is more n_nodes / 512 up to `most`, and n_nodes / 2048.
 constexpr uint32_t kManyWaveNodes = 32768;
 constexpr uint32_t kManyWaveNodesPlain = 16384;  // plain order: runs of 8 waves already differ by 6e-4 to 9e-4
-uint64_t auto_inflight_waves(const pgsgd_graph* g, uint32_t many, uint32_t per_wave) {
-  if (g->n_nodes < many) return std::max<uint64_t>(1, g->n_nodes / 2048);
-  return std::max<uint64_t>(g->n_nodes / per_wave, std::min<uint64_t>(g->n_nodes / 64, 1024));
+uint64_t auto_inflight_waves(const pgsgd_graph* g, uint32_t many, uint64_t most) {
+  const uint64_t n = g->n_nodes;
+  if (n < many) return std::max<uint64_t>(1, n / 2048);
+  return std::max({n / 2048, std::min<uint64_t>(n / 512, most), std::min<uint64_t>(n / 64, 1024)});
 }
 
 pgsgd_status layout_grid(pgsgd_graph* g, const pgsgd_params* p, size_t lds, uint64_t n_groups, uint32_t* blocks,
@@ -765,7 +766,7 @@ pgsgd_status layout_grid(pgsgd_graph* g, const pgsgd_params* p, size_t lds, uint
   if (st) return st;
   uint64_t waves = (uint64_t)g->n_cu * bpc * 4;
   const uint64_t cap =
-      p->max_inflight_waves ? p->max_inflight_waves : auto_inflight_waves(g, kManyWaveNodesPlain, 2048);
+      p->max_inflight_waves ? p->max_inflight_waves : auto_inflight_waves(g, kManyWaveNodesPlain, 0);
   waves = std::min(waves, cap);
   waves = std::min(waves, std::max<uint64_t>(1, n_groups));
   if (waves >= 4ull * g->n_cu) {
@@ -1041,7 +1042,7 @@ uint64_t auto_local_waves(const pgsgd_graph* g, LocalPhase phase, bool batched) 
   const uint64_t per = phase == kPhaseCooling ? kLocalNodesPerWaveCooling : kLocalNodesPerWave;
   uint64_t w = (uint64_t)(nodes_w / (double)per);
   w = std::min<uint64_t>(w, batched ? g->n_nodes / 2048
-                                    : auto_inflight_waves(g, kManyWaveNodes, kLocalNodesPerWavePlain));
+                                    : auto_inflight_waves(g, kManyWaveNodes, kLocalMostWaves));
   if (phase == kPhaseEarly) w = std::min(w, std::max<uint64_t>(g->n_nodes / 2048, kLocalEarlyWaves));
   return std::max<uint64_t>(1, w);
 }
@@ -1058,6 +1059,7 @@ uint64_t auto_local_waves(const pgsgd_graph* g, LocalPhase phase, bool batched) 
 struct LocalGrids {
   uint32_t blocks[kPhases], threads[kPhases];
   uint32_t quota_hi[kPhases], quota_lo[kPhases], hi_xcds[kPhases];  // blocks of an XCD's share that take work
+  bool ahead[kPhases];  // draw the next item ahead also beside uniform partners (see kLocalAheadWaves)
 };
 
 pgsgd_status local_grids(pgsgd_graph* g, const pgsgd_params* p, size_t lds, LocalGrids* out, bool batched = false) {
@@ -1068,6 +1070,7 @@ pgsgd_status local_grids(pgsgd_graph* g, const pgsgd_params* p, size_t lds, Loca
     uint64_t waves = (uint64_t)g->n_cu * (uint64_t)std::max(nb, 1) * 4;
     const uint64_t cap = p->max_inflight_waves ? p->max_inflight_waves : auto_local_waves(g, (LocalPhase)ph, batched);
     waves = std::max<uint64_t>(1, std::min(waves, cap));
+    out->ahead[ph] = !p->max_inflight_waves && !batched && g->n_nodes >= kManyWaveNodes && waves <= kLocalAheadWaves;
     out->quota_hi[ph] = out->quota_lo[ph] = 0xFFFFFFFFu;
     out->hi_xcds[ph] = kXcds;
     const bool wide = waves >= 4ull * kXcds;
@@ -1210,23 +1213,19 @@ pgsgd_status local_plan_scratch(pgsgd_graph* g, const pgsgd_params* p, size_t ld
   return PGSGD_OK;
 }
 
-// The layout part of a windowed iteration whose counts and offsets are in W:
-// run counters cleared, layout kernel.  With e_mid set, an event is recorded
-// right before the layout kernel.
+// The layout part of a windowed iteration whose counts, offsets and cleared
+// item counters are in W.  With e_mid set, an event is recorded right before it.
 hipError_t local_layout(const LocalLaunch& W, const LocalGrids& grids, LocalPhase phase, hipStream_t s,
                         hipEvent_t e_mid = nullptr) {
-  if (W.list && ordered_phase(grids, phase) && !W.L.trace_f && !W.L.apply_mask) {
-    const hipError_t e = e_mid ? hipEventRecord(e_mid, s) : hipSuccess;
-    return e ? e : launch_layout_ordered(W, s);
-  }
-  hipError_t e = launch_fill_u32(reinterpret_cast<uint32_t*>(W.queue), 2ull * kXcds * W.streams * 16, 0u, s);
-  if (!e && e_mid) e = hipEventRecord(e_mid, s);
+  const hipError_t e = e_mid ? hipEventRecord(e_mid, s) : hipSuccess;
+  if (e) return e;
+  if (W.list && ordered_phase(grids, phase) && !W.L.trace_f && !W.L.apply_mask) return launch_layout_ordered(W, s);
   LocalLaunch Wp = W;
   Wp.quota_hi = grids.quota_hi[phase];
   Wp.quota_lo = grids.quota_lo[phase];
   Wp.hi_xcds = grids.hi_xcds[phase];
-  if (!e) e = launch_layout_local(Wp, grids.blocks[phase], grids.threads[phase], s);
-  return e;
+  Wp.ahead = grids.ahead[phase] ? 1u : 0u;
+  return launch_layout_local(Wp, grids.blocks[phase], grids.threads[phase], s);
 }
 
 // One windowed iteration (W.L.iter, cool_all and eta set) on one stream:

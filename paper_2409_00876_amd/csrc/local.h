@@ -29,10 +29,18 @@ constexpr uint64_t kLocalNodesPerWave = 8;
 // same pairs of Eq. 2 at m = 3000: nodes_w / 8 left 5.3% more stress, nodes_w /
 // 32 2.6%, for 0.6 s more per layout of 3.5 s).
 constexpr uint64_t kLocalNodesPerWaveCooling = 32;
-// Both caps stay below n_nodes / 512 waves on graphs of more than 524K nodes
-// (1.8M nodes, 32 paths, 15 mixed iterations: 183 ms at 862 waves, 150 at
-// 2,048, 139 at 3,000, 142 at 4,096, the paired stress flat within 1%).
-constexpr uint32_t kLocalNodesPerWavePlain = 512;
+// Both caps stay below n_nodes / 512 waves up to this many (1.8M nodes, 32
+// paths, 15 mixed iterations: 183 ms at 862 waves, 150 at 2,048, 139 at 3,000,
+// 142 at 4,096; 7.2M nodes: 538 at 3,466, 544 at 4,096; the paired stress flat
+// within 1%), and below n_nodes / 2048 beyond.
+constexpr uint64_t kLocalMostWaves = 3584;
+// Up to this many waves the iterations with uniform partners draw the next item
+// while the current one's records load, as the all-cooling ones do: 15 such
+// iterations on 51K / 342K / 985K nodes took 5.9 / 42.8 / 70.8 ms without and
+// 4.8 / 35.0 / 60.7 with (500 to 1,900 waves); from about 3,500 waves on their
+// far lines fill the fabric and it is slower (2.7M nodes: 167.9 and 173.0 ms,
+// 7.2M: 437 and 448).  Graphs below 32,768 nodes keep their pace.
+constexpr uint64_t kLocalAheadWaves = 3072;
 constexpr uint64_t kLocalEarlyWaves = 512;    // cap of the first eighth of the iterations below 1M nodes
 
 // log2 of the window length for S steps: 2^14, halved while there would be
@@ -84,6 +92,7 @@ struct LocalLaunch {
   uint32_t count_blocks;   // grid of the count kernel
   uint32_t streams;        // concurrent window streams per XCD
   uint32_t xstride;        // row length of xitem
+  uint32_t ahead;          // iterations with uniform partners draw the next item ahead too
   uint32_t grab;           // items a wave takes from its stream's counter at once
   uint32_t quota_hi, quota_lo, hi_xcds;  // blocks of XCDs [0, hi_xcds) and of the others (see LocalGrids)
   uint32_t* wcount;        // [n_win] histogram (zeroed by the scan for the next iteration)
@@ -93,7 +102,7 @@ struct LocalLaunch {
   const uint32_t* wpath;   // [n_win] path holding the whole window, or bit 31 set if it spans paths
   uint64_t* xitem;         // [kXcds * streams][xstride] prefix of 64-slot groups over the windows of each run
   OrderedTerm* list;       // the ordered form's terms (see launch_layout_ordered), or NULL
-  uint64_t* queue;         // [kXcds * streams * 16] item counters, one per run on its own 128-byte line
+  uint64_t* queue;         // [kXcds * streams * 16] item counters (zeroed by the scan), one per run on its own 128-byte line
 };
 
 hipError_t launch_local_count_scan(const LocalLaunch& P, hipStream_t s);

@@ -63,10 +63,11 @@ __global__ __launch_bounds__(1024) void k_local_count(LocalLaunch P) {
 }
 
 // One block of 1024 threads.  woff = exclusive prefix of wcount (window-id
-// order); per run the prefix of ceil(n_w / 64) over its windows (run order);
-// then wcount = 0.  Each thread owns a contiguous chunk of windows; every
-// stage is a chunk pass plus a block scan, so no thread walks a long chain of
-// dependent loads.
+// order): each thread owns a contiguous chunk of windows, a chunk pass and a
+// block scan.  Per run the prefix of ceil(n_w / 64) over its windows (run
+// order): one wave per run, 64 windows at a time, so the runs advance together
+// (a block scan per run, one after another, took 11.6 us for 40 windows, now
+// 4.4).  Then the item counters and wcount = 0.
 __global__ __launch_bounds__(1024) void k_local_scan(LocalLaunch P) {
   __shared__ uint64_t lds16[16];
   const uint32_t n = P.n_win;
@@ -82,22 +83,28 @@ __global__ __launch_bounds__(1024) void k_local_scan(LocalLaunch P) {
     acc += P.wcount[k];
   }
   if (threadIdx.x == 0) P.woff[n] = total;
-  // per run: the threads split the run's windows (in run order) into chunks
   const uint32_t runs = kXcds * P.streams;
-  for (uint32_t run = 0; run < runs; ++run) {
-    const uint32_t b = P.sbeg[run], e = P.sbeg[run + 1], nq = e - b;
-    const uint32_t rper = (nq + blockDim.x - 1) / blockDim.x;
-    const uint32_t q0 = min(nq, threadIdx.x * rper), q1 = min(nq, q0 + rper);
-    uint64_t items = 0;
-    for (uint32_t q = q0; q < q1; ++q) items += (P.wcount[P.worder[b + q]] + 63) >> 6;
-    uint64_t run_total;
-    uint64_t pre = block_exclusive_scan(items, lds16, &run_total);
+  const uint32_t lane = threadIdx.x & 63u;
+  for (uint32_t run = uniform_u32(threadIdx.x >> 6); run < runs; run += blockDim.x >> 6) {
+    const uint32_t b = P.sbeg[run], nq = P.sbeg[run + 1] - b;
     uint64_t* xi = P.xitem + (size_t)run * P.xstride;
-    for (uint32_t q = q0; q < q1; ++q) {
-      xi[q] = pre;
-      pre += (P.wcount[P.worder[b + q]] + 63) >> 6;
+    uint64_t before = 0;
+    for (uint32_t q0 = 0; q0 < nq; q0 += 64) {
+      const uint32_t q = q0 + lane;
+      const uint64_t items = q < nq ? ((uint64_t)P.wcount[P.worder[b + q]] + 63) >> 6 : 0;
+      uint64_t x = items;
+#pragma unroll
+      for (uint32_t d = 1; d < 64; d <<= 1) {
+        const uint64_t y = __shfl_up(x, d, 64);
+        if (lane >= d) x += y;
+      }
+      if (q < nq) xi[q] = before + x - items;
+      before += __shfl(x, 63, 64);
     }
-    if (threadIdx.x == 0) xi[nq] = run_total;
+    if (lane == 0) {
+      xi[nq] = before;
+      P.queue[(size_t)run * 16] = 0;
+    }
   }
   __syncthreads();
   for (uint32_t k = k0; k < k1; ++k) P.wcount[k] = 0;
@@ -219,7 +226,7 @@ __device__ __forceinline__ Term item_draw(const LocalLaunch& P, const LdsView& V
   return T;
 }
 
-// A run of an all-cooling iteration, two items deep: the step records of
+// A run, two items deep (kCooling: of an all-cooling iteration): the step records of
 // item m are requested, then item m + 1 is drawn (Philox, path, power-law
 // partner: arithmetic and LDS only) while they arrive, then item m is updated.
 // Only the draw runs ahead; the coordinates of item m are read and written as
@@ -227,7 +234,8 @@ __device__ __forceinline__ Term item_draw(const LocalLaunch& P, const LdsView& V
 // are those of local_item; with the recording hook set (trace_f) the terms of
 // the slots [t_begin, t_end) are recorded instead of applied, as local_item
 // records them.
-__device__ __forceinline__ void local_run_cooling(const LocalLaunch& P, const LdsView& V, uint32_t wb, uint32_t nq,
+template <bool kCooling>
+__device__ __forceinline__ void local_run_ahead(const LocalLaunch& P, const LdsView& V, uint32_t wb, uint32_t nq,
                                                   const uint64_t* __restrict__ xi_in, uint64_t n_items,
                                                   unsigned long long* ctr) {
   const LayoutLaunch& L = P.L;
@@ -249,7 +257,7 @@ __device__ __forceinline__ void local_run_cooling(const LocalLaunch& P, const Ld
   uint64_t slot;
   if (L.trace_f) {  // parity hook: the drawn terms of the slots [t_begin, t_end), nothing applied
     for (;;) {
-      Term T = item_draw<true>(P, V, wb, nq, xi, m, q, slot);
+      Term T = item_draw<kCooling>(P, V, wb, nq, xi, m, q, slot);
       if (slot >= L.t_begin && slot < L.t_end) {
         if (!(T.flags & 8u)) {
           uint64_t a, b;
@@ -264,7 +272,7 @@ __device__ __forceinline__ void local_run_cooling(const LocalLaunch& P, const Ld
       if (++m >= m_end && !grab(m, m_end)) return;
     }
   }
-  Term cur = item_draw<true>(P, V, wb, nq, xi, m, q, slot);
+  Term cur = item_draw<kCooling>(P, V, wb, nq, xi, m, q, slot);
   for (;;) {
     // the next item's index first: a grab waits for its atomic before this item's loads are issued
     uint64_t mn = m + 1, mn_end = m_end;
@@ -277,13 +285,17 @@ __device__ __forceinline__ void local_run_cooling(const LocalLaunch& P, const Ld
     }
     Term nxt;
     nxt.flags = 8u;
-    if (more) nxt = item_draw<true>(P, V, wb, nq, xi, mn, q, slot);
+    if (more) nxt = item_draw<kCooling>(P, V, wb, nq, xi, mn, q, slot);
     if (live) {
       const uint32_t ei = cur.flags & 1u, ej = (cur.flags >> 1) & 1u;
       const uint64_t a = 2ull * (si.node_rev & kNodeMask) + ei;
       const uint64_t b = 2ull * (sj.node_rev & kNodeMask) + ej;
       const int64_t dd = endpoint_pos(si, ei) - endpoint_pos(sj, ej);
-      if (a != b && dd != 0) apply_update(L.work, a, b, (float)(dd < 0 ? -dd : dd), L.eta);
+      if (a != b && dd != 0) {
+        const float d = (float)(dd < 0 ? -dd : dd);
+        if (kCooling || (cur.flags & 4u)) apply_update(L.work, a, b, d, L.eta);
+        else apply_update_far_first(L.work, a, b, d, L.eta);
+      }
     }
     if (!more) break;
     cur = nxt;
@@ -559,6 +571,11 @@ __device__ __forceinline__ void local_item_reuse(const LocalLaunch& P, const Lds
   }
 }
 
+// The forms of k_layout_local, each a kernel of its own (together in one they
+// shared its registers and schedule: few-wave layouts ran 4% slower).
+enum LocalForm { kItems, kItemsReuse, kRunAhead, kRunCooling };
+
+template <LocalForm kForm>
 __global__ __launch_bounds__(256) void k_layout_local(LocalLaunch P) {
   extern __shared__ __align__(16) char lds[];
   if (blockIdx.x / kXcds >= (blockIdx.x % kXcds < P.hi_xcds ? P.quota_hi : P.quota_lo)) return;
@@ -583,8 +600,8 @@ __global__ __launch_bounds__(256) void k_layout_local(LocalLaunch P) {
     const uint64_t* __restrict__ xi = P.xitem + (size_t)run * P.xstride;
     const uint64_t n_items = uniform_u64(uload(xi + nq));
     unsigned long long* ctr = reinterpret_cast<unsigned long long*>(P.queue + (size_t)run * 16);
-    if (L.cool_all && L.drf <= 1 && !L.apply_mask) {
-      local_run_cooling(P, V, wb, nq, xi, n_items, ctr);
+    if (kForm == kRunAhead || kForm == kRunCooling) {
+      local_run_ahead<kForm == kRunCooling>(P, V, wb, nq, xi, n_items, ctr);
       continue;
     }
     uint32_t q = 0;
@@ -596,7 +613,7 @@ __global__ __launch_bounds__(256) void k_layout_local(LocalLaunch P) {
         if (m >= n_items) break;
         m_end = min(m + P.grab, n_items);
       }
-      if (L.drf > 1) local_item_reuse(P, V, wb, nq, xi, m, q);
+      if (kForm == kItemsReuse) local_item_reuse(P, V, wb, nq, xi, m, q);
       else local_item(P, V, wb, nq, xi, m, q);
     }
   }
@@ -628,10 +645,16 @@ hipError_t launch_layout_ordered(const LocalLaunch& P, hipStream_t s) {
 }
 
 hipError_t launch_layout_local(const LocalLaunch& P, uint32_t blocks, uint32_t threads, hipStream_t s) {
-  hipLaunchKernelGGL(k_layout_local, dim3(blocks), dim3(threads), layout_lds_bytes(P.L.path_slots, P.L.W), s, P);
-  return hipGetLastError();
+  auto go = [&](auto kernel) {
+    hipLaunchKernelGGL(kernel, dim3(blocks), dim3(threads), layout_lds_bytes(P.L.path_slots, P.L.W), s, P);
+    return hipGetLastError();
+  };
+  if (P.L.drf > 1) return go(k_layout_local<kItemsReuse>);
+  if (P.L.apply_mask) return go(k_layout_local<kItems>);
+  if (P.L.cool_all) return go(k_layout_local<kRunCooling>);
+  return P.ahead ? go(k_layout_local<kRunAhead>) : go(k_layout_local<kItems>);
 }
 
-const void* layout_local_kernel() { return reinterpret_cast<const void*>(&k_layout_local); }
+const void* layout_local_kernel() { return reinterpret_cast<const void*>(&k_layout_local<kItems>); }
 
 }  // namespace pgsgd
