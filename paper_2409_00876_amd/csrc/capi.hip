@@ -1030,20 +1030,34 @@ LocalPhase local_phase(uint32_t iter, uint32_t n_iters) {
 // not bring the layout's place on the axes back: with 1,024 waves in them a
 // layout of 148K nodes lands 450 nt further along x than with 72 (6.5e-4 of
 // the coordinates, runs differ by 3.6e-4), with 512 or fewer it does not.
-// Graphs of a batch keep n_nodes / 2048 throughout: several of them share each
-// L2 and what one evicts of another's coordinates other XCDs then see, so a
-// graph's place depends on the pace of its neighbours (with the caps of a
-// single layout a batch took 174 ms instead of 1,080, but its 60K-node graph
-// lay 5e-3 from where it was, runs differing by 1e-3).
-uint64_t auto_local_waves(const pgsgd_graph* g, LocalPhase phase, bool batched) {
+// Graphs of a batch run `scale` times n_nodes / 2048 waves in every iteration
+// (scale = 0: no batch).  Several of them share each L2, and what one evicts of
+// another's coordinates the other XCDs then see, so a graph's place depends on
+// the pace of its neighbours: all must gain alike, and not by much.  Six graphs
+// of 60K to 351K nodes took 1,080 ms at scale 1 and 475 / 270 / 195 at 2 / 4 /
+// 8; graph by graph, layouts of scale 1 / 2 / 4 / 8 lie 1.1 / 1.1 / 1.3 / 1.5
+// times as far from a set of scale 1 as its own lie from each other (means over
+// 24).  With the caps of single layouts (174 ms) the smallest graph lay five
+// times as far.
+constexpr uint32_t kBatchScale = 2;
+uint32_t batch_scale(pgsgd_graph* const* graphs, uint32_t n) {
+  for (uint32_t k = 0; k < n; ++k)
+    if (graphs[k]->n_nodes < kManyWaveNodes) return 1;  // such a graph keeps its waves, so all do
+  return kBatchScale;
+}
+
+uint64_t auto_local_waves(const pgsgd_graph* g, LocalPhase phase, uint32_t scale) {
   const uint32_t sh = window_shift(g->S);
   const double nodes_w = std::min<double>((double)g->n_nodes,
                                           std::ldexp(1.0, (int)sh) * (double)g->n_nodes * g->n_paths / (double)g->S);
   const uint64_t per = phase == kPhaseCooling ? kLocalNodesPerWaveCooling : kLocalNodesPerWave;
   uint64_t w = (uint64_t)(nodes_w / (double)per);
-  w = std::min<uint64_t>(w, batched ? g->n_nodes / 2048
-                                    : auto_inflight_waves(g, kManyWaveNodes, kLocalMostWaves));
-  if (phase == kPhaseEarly) w = std::min(w, std::max<uint64_t>(g->n_nodes / 2048, kLocalEarlyWaves));
+  if (scale) {
+    w = std::min<uint64_t>(w, (uint64_t)scale * std::max(1u, g->n_nodes / 2048));
+  } else {
+    w = std::min<uint64_t>(w, auto_inflight_waves(g, kManyWaveNodes, kLocalMostWaves));
+    if (phase == kPhaseEarly) w = std::min(w, std::max<uint64_t>(g->n_nodes / 2048, kLocalEarlyWaves));
+  }
   return std::max<uint64_t>(1, w);
 }
 
@@ -1062,15 +1076,16 @@ struct LocalGrids {
   bool ahead[kPhases];  // draw the next item ahead also beside uniform partners (see kLocalAheadWaves)
 };
 
-pgsgd_status local_grids(pgsgd_graph* g, const pgsgd_params* p, size_t lds, LocalGrids* out, bool batched = false) {
+pgsgd_status local_grids(pgsgd_graph* g, const pgsgd_params* p, size_t lds, LocalGrids* out, uint32_t scale = 0) {
   int nb = 0;
   HIP_TRY(hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, layout_local_kernel(), 256, lds));
   const uint32_t base = g->n_nodes / 2048;
   for (uint32_t ph = 0; ph < kPhases; ++ph) {
     uint64_t waves = (uint64_t)g->n_cu * (uint64_t)std::max(nb, 1) * 4;
-    const uint64_t cap = p->max_inflight_waves ? p->max_inflight_waves : auto_local_waves(g, (LocalPhase)ph, batched);
+    const uint64_t cap = p->max_inflight_waves ? p->max_inflight_waves : auto_local_waves(g, (LocalPhase)ph, scale);
     waves = std::max<uint64_t>(1, std::min(waves, cap));
-    out->ahead[ph] = !p->max_inflight_waves && !batched && g->n_nodes >= kManyWaveNodes && waves <= kLocalAheadWaves;
+    out->ahead[ph] =
+        !p->max_inflight_waves && scale != 1 && g->n_nodes >= kManyWaveNodes && waves <= kLocalAheadWaves;
     out->quota_hi[ph] = out->quota_lo[ph] = 0xFFFFFFFFu;
     out->hi_xcds[ph] = kXcds;
     const bool wide = waves >= 4ull * kXcds;
@@ -1129,10 +1144,10 @@ OrderedTerm* ordered_list(pgsgd_graph* g, const LocalLaunch& W, const LocalGrids
 // Scratch, grid and launch arguments of the windowed schedule for graph g
 // (L: the sampling arguments of make_layout_launch).
 pgsgd_status local_plan(pgsgd_graph* g, const pgsgd_params* p, size_t lds, const LayoutLaunch& L, hipStream_t s,
-                        LocalLaunch* W, LocalGrids* grids, bool batched = false) {
+                        LocalLaunch* W, LocalGrids* grids, uint32_t scale = 0) {
   pgsgd_status st;
   if ((st = ensure_local(g, kLocalStreams, s))) return st;
-  if ((st = local_grids(g, p, lds, grids, batched))) return st;
+  if ((st = local_grids(g, p, lds, grids, scale))) return st;
   *W = LocalLaunch{};
   W->L = L;
   W->n_win = g->loc_nwin;
@@ -1148,7 +1163,7 @@ pgsgd_status local_plan(pgsgd_graph* g, const pgsgd_params* p, size_t lds, const
   W->wpath = g->d_lwpath;
   W->streams = kLocalStreams;
   W->grab = kLocalGrab;
-  W->list = batched ? nullptr : ordered_list(g, *W, *grids);
+  W->list = scale ? nullptr : ordered_list(g, *W, *grids);
   return PGSGD_OK;
 }
 
@@ -2127,7 +2142,7 @@ pgsgd_status batch_build_windowed(pgsgd_graph* const* graphs, uint32_t n, const 
     L.g_end = L.n_groups;
     LocalLaunch W;
     LocalGrids grids;
-    if ((st = local_plan(g, &q, lds, L, cs, &W, &grids, true))) break;
+    if ((st = local_plan(g, &q, lds, L, cs, &W, &grids, batch_scale(graphs, n)))) break;
     // a list per graph: graphs of different branches apply theirs at the same time
     if (const uint64_t terms = ordered_terms(W, grids)) {
       if (hipMalloc((void**)&W.list, terms * sizeof(OrderedTerm)) == hipSuccess) {
