@@ -1680,24 +1680,30 @@ pgsgd_status loss_win_prepare(pgsgd_graph* g, const pgsgd_params* p, const Stres
   return PGSGD_OK;
 }
 
-// The tiles of one pass and its grid.  The tile's coordinates are staged where
-// their LDS fits and there are enough pairs to use them: staging reads the
-// 512 lines of 4,096 nodes once, not staging two scattered lines a pair.
+// Whether the power-law tables of window W leave a block room for `form`.
+bool tile_fits(const pgsgd_graph* g, uint32_t W, TileForm form) {
+  return loss_tile_lds_bytes(W, form) + kTileStaticLds <= g->lds_limit;
+}
+
+// The tiles of one pass and its grid.  The forward pass stages a tile's
+// coordinates where two blocks of a CU have room and there are enough pairs to
+// use them: staging reads the 512 lines of 4,096 nodes once, not staging two
+// scattered lines a pair.
 TileLaunch loss_tile_launch(const pgsgd_graph* g, const pgsgd_params* p, uint64_t n_pairs, bool grad,
                             uint32_t* blocks) {
-  TileLaunch T{g->d_tile_seg, g->d_tile_off, g->d_tile_base, g->n_tiles, 1, false, g->d_tile_queue};
-  T.stage = loss_tile_lds_bytes(p->zipf_window, grad, true) + kTileStaticLds <= g->lds_limit &&
-            n_pairs >= 512ull * std::max(1u, g->n_tiles);
-  const uint32_t per_cu = grad && T.stage ? 1 : 2;  // blocks that a CU's LDS and waves hold
+  const uint32_t W = p->zipf_window;
+  TileLaunch T{g->d_tile_seg, g->d_tile_off, g->d_tile_base, g->n_tiles, 1, kTileFwd, g->d_tile_queue};
+  if (grad)
+    T.form = tile_fits(g, W, kTileBwd64) ? kTileBwd64 : kTileBwd32;
+  else if (2 * (loss_tile_lds_bytes(W, kTileFwdStaged) + kTileStaticLds) <= g->lds_limit &&
+           n_pairs >= 512ull * std::max(1u, g->n_tiles))
+    T.form = kTileFwdStaged;
+  const uint32_t per_cu = T.form == kTileBwd64 ? 1 : 2;  // blocks that a CU's LDS and waves hold
   const uint32_t cap = per_cu * (uint32_t)g->n_cu;
   T.split = loss_tile_split(g->n_tiles, cap, n_pairs, grad);
   *blocks = (uint32_t)std::max<uint64_t>(1, std::min<uint64_t>((uint64_t)g->n_tiles * T.split, cap));
   return T;
 }
-
-}  // namespace
-
-namespace {
 
 struct OutlierSink {
   double threshold = 0.0;
@@ -1953,13 +1959,13 @@ pgsgd_status pgsgd_stress_forward(pgsgd_graph* g, const pgsgd_params* p, const f
   uint32_t parts = kStressBlocks;
   if (P.count && resolve_schedule(p) == PGSGD_SCHEDULE_WINDOWED) {
     SpsWinLaunch W;
-    const bool tiles = loss_tile_lds_bytes(p->zipf_window, true, false) + kTileStaticLds <= g->lds_limit;
+    const bool tiles = tile_fits(g, p->zipf_window, kTileBwd32);
     if ((st = loss_win_prepare(g, p, P, n_pairs, s, &W, tiles))) return st;
     if (tiles) {
       if ((st = ensure_loss_tiles(g, s))) return st;
       HIP_TRY(copy_in(g->d_tile_queue));
       const TileLaunch T = loss_tile_launch(g, p, n_pairs, false, &parts);
-      HIP_TRY(launch_loss_tile_fwd(W, T, g->d_part_f, g->d_part_n, parts, s));
+      HIP_TRY(launch_loss_tile(W, T, nullptr, nullptr, nullptr, g->d_part_f, g->d_part_n, parts, s));
     } else {
       HIP_TRY(copy_in(nullptr));
       HIP_TRY(launch_loss_win_fwd(W, g->d_part_f, g->d_part_n, kStressBlocks, s));
@@ -1995,7 +2001,7 @@ pgsgd_status pgsgd_stress_backward(pgsgd_graph* g, const pgsgd_params* p, const 
   if (resolve_schedule(p) == PGSGD_SCHEDULE_WINDOWED) {
     SpsWinLaunch W;
     // by tiles when their LDS image fits a block (it does for every window W up to ~10^4)
-    const bool tiles = loss_tile_lds_bytes(p->zipf_window, true, false) + kTileStaticLds <= g->lds_limit;
+    const bool tiles = tile_fits(g, p->zipf_window, kTileBwd32);
     if ((st = loss_win_prepare(g, p, P, n_pairs, s, &W, tiles))) return st;
     if (tiles) {
       if ((st = ensure_loss_tiles(g, s))) return st;
@@ -2003,7 +2009,7 @@ pgsgd_status pgsgd_stress_backward(pgsgd_graph* g, const pgsgd_params* p, const 
       if (g->n_tiles) {
         uint32_t blocks = 0;
         const TileLaunch T = loss_tile_launch(g, p, n_pairs, true, &blocks);
-        HIP_TRY(launch_loss_tile_bwd(W, T, grad_out_dev, n_valid_dev, grad_coords, blocks, s));
+        HIP_TRY(launch_loss_tile(W, T, grad_out_dev, n_valid_dev, grad_coords, nullptr, nullptr, blocks, s));
       }
     } else {
       HIP_TRY(copy_in(nullptr));

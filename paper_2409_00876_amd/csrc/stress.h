@@ -110,13 +110,15 @@ constexpr uint32_t kTileNodes = 2048;
 constexpr uint32_t kTileMaxSeg = 256;    // a segment's number in its tile is a byte of k_loss_tile's guide
 constexpr uint32_t kTileGuide = 1024;
 constexpr uint32_t kTileThreads = 1024;
+// The forms of k_loss_tile (see there).
+enum TileForm { kTileFwd, kTileFwdStaged, kTileBwd32, kTileBwd64 };
 struct TileLaunch {
   const uint32_t* seg;
   const uint32_t* off;
   const uint32_t* base;
   uint32_t n_tiles;
   uint32_t split;  // parts of a tile's pairs, a unit of work each
-  bool stage;      // the tile's coordinates in LDS
+  TileForm form;
   uint32_t* queue;
 };
 // Parts of a tile.  A gradient unit zeroes and flushes the tile's whole image,
@@ -130,13 +132,13 @@ inline uint32_t loss_tile_split(uint32_t n_tiles, uint32_t blocks, uint64_t n_pa
   if (grad && n_tiles >= blocks) return 1;
   return (uint32_t)std::max<uint64_t>(1, std::min(want, room));
 }
-hipError_t launch_loss_tile_bwd(const SpsWinLaunch& W, const TileLaunch& T, const float* grad_out,
-                                const uint64_t* n_valid, float* grad, uint32_t blocks, hipStream_t s);
-// The forward pass over the same tiles: per-block sums into part_f / part_n[0 .. blocks).
-hipError_t launch_loss_tile_fwd(const SpsWinLaunch& W, const TileLaunch& T, double* part_f, uint64_t* part_n,
-                                uint32_t blocks, hipStream_t s);
-size_t loss_tile_lds_bytes(uint32_t W, bool grad, bool stage);  // dynamic LDS of k_loss_tile
-constexpr size_t kTileStaticLds = 12 * 1024;  // static LDS of k_loss_tile (a tile's segment table), rounded up
+// kTileFwd*: per-block sums into part_f / part_n[0 .. blocks); kTileBwd*: the
+// adjoint of grad_out added to grad.
+hipError_t launch_loss_tile(const SpsWinLaunch& W, const TileLaunch& T, const float* grad_out,
+                            const uint64_t* n_valid, float* grad, double* part_f, uint64_t* part_n, uint32_t blocks,
+                            hipStream_t s);
+size_t loss_tile_lds_bytes(uint32_t W, TileForm form);  // dynamic LDS of k_loss_tile
+constexpr size_t kTileStaticLds = 10 * 1024;  // static LDS of k_loss_tile (a tile's segment table), rounded up
 // out[g] = the lowest device node id over the steps [start[g], start[g + 1])
 hipError_t launch_segment_min_node(const StepRec* rec, const uint64_t* start, uint32_t nseg, uint32_t* out,
                                    hipStream_t s);

@@ -7,6 +7,7 @@
 // ((|v_i - v_j| - d)/d)^2; block partials are FP64 and reduced in a fixed
 // order, so results are deterministic for a given launch shape.
 #include <algorithm>
+#include <type_traits>
 
 #include "device.h"
 #include "internal.h"
@@ -334,7 +335,7 @@ __device__ __forceinline__ uint64_t uniform_u64(uint64_t v) {
 // instead.  The segments start at the window starts and the path starts, so
 // step i of path p lies in segment (i >> win_shift) + path_extra[p], the path
 // starts inside windows up to that of p (a search of the window's segments,
-// with three random loads, bound the count of 1e7 loss pairs: 70 us, now 41).
+// with three random loads, bound the count of 1e7 loss pairs: 70 us, now 59).
 __global__ __launch_bounds__(1024) void k_sps_win_count(SpsWinLaunch W) {
   extern __shared__ __align__(16) char lds[];
   const StressLaunch& P = W.P;
@@ -840,35 +841,42 @@ __global__ __launch_bounds__(256) void k_loss_win(SpsWinLaunch W, const float* _
 // paths), so most of a tile's adjoint lands in an LDS image of that range and
 // reaches memory once per touched entry instead of once per pair.
 // ---------------------------------------------------------------------------
-size_t loss_tile_lds_bytes(uint32_t W, bool grad, bool stage) {
+size_t loss_tile_lds_bytes(uint32_t W, TileForm form) {
   const size_t head = ((size_t)(W + 1) * 4 + (size_t)(kGuideSize + 1) * 2 + 15) & ~(size_t)15;
-  return head + (size_t)4 * kTileNodes * sizeof(float2) * ((grad ? 1 : 0) + (stage ? 1 : 0));
+  const size_t entry = form == kTileFwd ? 0 : form == kTileBwd64 ? sizeof(double2) : sizeof(float2);
+  return head + (size_t)4 * kTileNodes * entry;
 }
 
-// kGrad = false: the forward pass over the same tiles (per-block sums of the
-// stress and the valid-pair count).
+// kTileFwd, kTileFwdStaged: the forward pass over the same tiles (per-block
+// sums of the stress and the valid-pair count), with the coordinates of the
+// tile's ids copied to LDS first by coalesced loads; a pair's two records and
+// two coordinates are scattered 8 and 16-byte loads, 64 cache-line requests
+// each for a wave (the parts of the forward pass over 1e7 pairs: draws 80,
+// records 74, coordinates 78 us), and a tile's 22K pairs share 4,096 nodes.
 //
-// kStage: the coordinates of the tile's ids are copied to LDS first, with
-// coalesced loads.  A pair's two records and two coordinates are scattered
-// 8 and 16-byte loads, 64 cache-line requests each for a wave, and those
-// requests bound the kernel, not latency (twice the waves: 231 -> 223 us; the
-// parts of the forward pass over 1e7 pairs: draws 80, records 74, coordinates
-// 78 us); a tile's 22K pairs share 4,096 nodes.  The gradient's image holds x
-// and y in planes of their own, so the adds of a wave use all LDS banks.
+// kTileBwd32, kTileBwd64: the gradient, its image in float or in double.  A
+// wave's ds_add_f32 at scattered addresses takes 185 cycles here, ds_add_f64
+// 21 (and ds_add_u32 7), so the double image is the faster one and rounds once,
+// at the flush: 360 -> 282 us over 1e7 pairs.  It fills the LDS (128 KB), so
+// power-law tables of more than ~4,500 hops take the float image.  x and y have
+// planes of their own, so the adds of a wave use all banks.
 //
 // A unit of work is one of T.split equal parts of a tile's pairs (see
 // loss_tile_split for where a tile is cut).
-template <bool kGrad, bool kStage>
+template <TileForm kForm>
 __global__ __launch_bounds__(kTileThreads) void k_loss_tile(SpsWinLaunch W, TileLaunch T,
                                                            const float* __restrict__ grad_out,
                                                            const uint64_t* __restrict__ n_valid,
                                                            float* __restrict__ grad, double* __restrict__ part_f,
                                                            uint64_t* __restrict__ part_n) {
+  constexpr bool kGrad = kForm == kTileBwd32 || kForm == kTileBwd64;
+  constexpr bool kStage = kForm == kTileFwdStaged;
+  using Acc = typename std::conditional<kForm == kTileBwd64, double, float>::type;
   __shared__ double red_f[16];
   __shared__ uint64_t red_n[16];
   extern __shared__ __align__(16) char lds[];
-  __shared__ uint64_t s_flat[kTileMaxSeg + 1];  // slot prefix over the tile's segments
-  __shared__ uint64_t s_slot[kTileMaxSeg];      // first slot of each segment
+  __shared__ uint32_t s_flat[kTileMaxSeg + 1];  // slot prefix over the tile's segments (fewer than 2^32 pairs)
+  __shared__ uint32_t s_slot[kTileMaxSeg];      // first slot of each segment
   __shared__ uint64_t s_start[kTileMaxSeg];     // first step of each segment
   __shared__ uint64_t s_pst[kTileMaxSeg];       // first step of its path
   __shared__ uint32_t s_len[kTileMaxSeg];       // steps of each segment
@@ -879,10 +887,10 @@ __global__ __launch_bounds__(kTileThreads) void k_loss_tile(SpsWinLaunch W, Tile
   uint32_t* zipf = reinterpret_cast<uint32_t*>(lds);
   uint16_t* guide = reinterpret_cast<uint16_t*>(lds + (size_t)(P.W + 1) * 4);
   constexpr uint32_t kAcc = 4 * kTileNodes;  // entries: 2 * kTileNodes nodes x 2 endpoints
-  float* acc_x =
-      reinterpret_cast<float*>(lds + (((size_t)(P.W + 1) * 4 + (size_t)(kGuideSize + 1) * 2 + 15) & ~(size_t)15));
-  float* acc_y = acc_x + kAcc;
-  float2* xy = reinterpret_cast<float2*>(acc_x + (kGrad ? 2 * kAcc : 0));
+  char* image = lds + (((size_t)(P.W + 1) * 4 + (size_t)(kGuideSize + 1) * 2 + 15) & ~(size_t)15);
+  Acc* acc_x = reinterpret_cast<Acc*>(image);
+  Acc* acc_y = acc_x + kAcc;
+  float2* xy = reinterpret_cast<float2*>(image);
   for (uint32_t k = threadIdx.x; k <= P.W; k += blockDim.x) zipf[k] = P.zipf[k];
   for (uint32_t k = threadIdx.x; k <= kGuideSize; k += blockDim.x) guide[k] = P.guide[k];
   double scale = 0.0;
@@ -910,7 +918,7 @@ __global__ __launch_bounds__(kTileThreads) void k_loss_tile(SpsWinLaunch W, Tile
     const uint32_t k0 = T.off[t];
     const uint32_t nk = T.off[t + 1] - k0;
     if (kGrad)
-      for (uint32_t e = threadIdx.x; e < 2 * kAcc; e += blockDim.x) acc_x[e] = 0.0f;
+      for (uint32_t e = threadIdx.x; e < 2 * kAcc; e += blockDim.x) acc_x[e] = 0;
     if (kStage) {
       const uint32_t ends = (uint32_t)min((uint64_t)kAcc, 2 * (P.n_nodes - base));
       for (uint32_t e = threadIdx.x; e < ends; e += blockDim.x) xy[e] = P.work[2 * base + e];
@@ -921,8 +929,8 @@ __global__ __launch_bounds__(kTileThreads) void k_loss_tile(SpsWinLaunch W, Tile
     };
     for (uint32_t k = threadIdx.x; k < nk; k += blockDim.x) {
       const uint32_t g = T.seg[k0 + k];
-      s_slot[k] = W.seg_off[g];
-      s_flat[k + 1] = W.seg_off[g + 1] - W.seg_off[g];
+      s_slot[k] = (uint32_t)W.seg_off[g];
+      s_flat[k + 1] = (uint32_t)(W.seg_off[g + 1] - W.seg_off[g]);
       s_start[k] = W.seg_start[g];
       s_len[k] = (uint32_t)(W.seg_start[g + 1] - W.seg_start[g]);
       const uint32_t p = W.seg_path[g];
@@ -931,13 +939,13 @@ __global__ __launch_bounds__(kTileThreads) void k_loss_tile(SpsWinLaunch W, Tile
     }
     __syncthreads();
     if (threadIdx.x < 64) {  // inclusive prefix by one wave, 64 segments at a time
-      uint64_t carry = 0;
+      uint32_t carry = 0;
       if (threadIdx.x == 0) s_flat[0] = 0;
       for (uint32_t k = 0; k < nk; k += 64) {
-        uint64_t x = k + threadIdx.x < nk ? s_flat[k + threadIdx.x + 1] : 0;
+        uint32_t x = k + threadIdx.x < nk ? s_flat[k + threadIdx.x + 1] : 0;
 #pragma unroll
         for (uint32_t d = 1; d < 64; d <<= 1) {
-          const uint64_t y = __shfl_up(x, d, 64);
+          const uint32_t y = __shfl_up(x, d, 64);
           if (threadIdx.x >= d) x += y;
         }
         x += carry;
@@ -946,7 +954,7 @@ __global__ __launch_bounds__(kTileThreads) void k_loss_tile(SpsWinLaunch W, Tile
       }
     }
     __syncthreads();
-    const uint64_t total = s_flat[nk];
+    const uint32_t total = s_flat[nk];
     uint32_t shift = 6;  // the guide's step: it spans the tile's slots
     while ((total >> shift) >= kTileGuide) ++shift;
     for (uint32_t e = threadIdx.x; ((uint64_t)e << shift) < total; e += blockDim.x) {
@@ -959,8 +967,8 @@ __global__ __launch_bounds__(kTileThreads) void k_loss_tile(SpsWinLaunch W, Tile
       s_near[e] = (uint8_t)lo;
     }
     __syncthreads();
-    const uint64_t f_end = total * (part + 1) / T.split;
-    for (uint64_t f = total * part / T.split + threadIdx.x; f < f_end; f += blockDim.x) {
+    const uint64_t f_end = (uint64_t)total * (part + 1) / T.split;
+    for (uint64_t f = (uint64_t)total * part / T.split + threadIdx.x; f < f_end; f += blockDim.x) {
       uint32_t lo = s_near[f >> shift];  // the segment k with s_flat[k] <= f < s_flat[k + 1]
       while (s_flat[lo + 1] <= f) ++lo;
       const uint64_t u = s_slot[lo] + (f - s_flat[lo]);
@@ -981,25 +989,25 @@ __global__ __launch_bounds__(kTileThreads) void k_loss_tile(SpsWinLaunch W, Tile
       const double mag = delta_xy(va, vb, dx, dy);
       if (mag == 0.0) continue;
       const double c = gradient_factor(scale, mag, d);
-      const float gx = (float)(c * dx), gy = (float)(c * dy);
+      const Acc gx = (Acc)(c * dx), gy = (Acc)(c * dy);
       const uint64_t ea = a - 2 * base, eb = b - 2 * base;  // wrap to huge below the base
       if (ea < kAcc) {
-        atomicAdd(&acc_x[ea], gx);
-        atomicAdd(&acc_y[ea], gy);
+        unsafeAtomicAdd(&acc_x[ea], gx);
+        unsafeAtomicAdd(&acc_y[ea], gy);
       } else {
-        global_add(a, gx, gy);
+        global_add(a, (float)gx, (float)gy);
       }
       if (eb < kAcc) {
-        atomicAdd(&acc_x[eb], -gx);
-        atomicAdd(&acc_y[eb], -gy);
+        unsafeAtomicAdd(&acc_x[eb], -gx);
+        unsafeAtomicAdd(&acc_y[eb], -gy);
       } else {
-        global_add(b, -gx, -gy);
+        global_add(b, (float)-gx, (float)-gy);
       }
     }
     if (kGrad) {
       __syncthreads();
       for (uint32_t e = threadIdx.x; e < kAcc; e += blockDim.x) {
-        const float vx = acc_x[e], vy = acc_y[e];
+        const float vx = (float)acc_x[e], vy = (float)acc_y[e];
         if ((vx != 0.0f || vy != 0.0f) && 2 * base + e < 2 * P.n_nodes) global_add(2 * base + e, vx, vy);
       }
     }
@@ -1202,28 +1210,20 @@ hipError_t launch_loss_win_bwd(const SpsWinLaunch& W, const float* grad_out, con
   return hipGetLastError();
 }
 
-template <bool kGrad>
-static hipError_t launch_loss_tile(const SpsWinLaunch& W, const TileLaunch& T, const float* grad_out,
-                                   const uint64_t* n_valid, float* grad, double* part_f, uint64_t* part_n,
-                                   uint32_t blocks, hipStream_t s) {
-  const size_t lds = loss_tile_lds_bytes(W.P.W, kGrad, T.stage);
-  if (T.stage)
-    hipLaunchKernelGGL((k_loss_tile<kGrad, true>), dim3(blocks), dim3(kTileThreads), lds, s, W, T, grad_out, n_valid,
-                       grad, part_f, part_n);
-  else
-    hipLaunchKernelGGL((k_loss_tile<kGrad, false>), dim3(blocks), dim3(kTileThreads), lds, s, W, T, grad_out, n_valid,
-                       grad, part_f, part_n);
-  return hipGetLastError();
-}
-
-hipError_t launch_loss_tile_bwd(const SpsWinLaunch& W, const TileLaunch& T, const float* grad_out,
-                                const uint64_t* n_valid, float* grad, uint32_t blocks, hipStream_t s) {
-  return launch_loss_tile<true>(W, T, grad_out, n_valid, grad, nullptr, nullptr, blocks, s);
-}
-
-hipError_t launch_loss_tile_fwd(const SpsWinLaunch& W, const TileLaunch& T, double* part_f, uint64_t* part_n,
-                                uint32_t blocks, hipStream_t s) {
-  return launch_loss_tile<false>(W, T, nullptr, nullptr, nullptr, part_f, part_n, blocks, s);
+hipError_t launch_loss_tile(const SpsWinLaunch& W, const TileLaunch& T, const float* grad_out,
+                            const uint64_t* n_valid, float* grad, double* part_f, uint64_t* part_n, uint32_t blocks,
+                            hipStream_t s) {
+  auto go = [&](auto kernel) {
+    hipLaunchKernelGGL(kernel, dim3(blocks), dim3(kTileThreads), loss_tile_lds_bytes(W.P.W, T.form), s, W, T, grad_out,
+                       n_valid, grad, part_f, part_n);
+    return hipGetLastError();
+  };
+  switch (T.form) {
+    case kTileFwd: return go(k_loss_tile<kTileFwd>);
+    case kTileFwdStaged: return go(k_loss_tile<kTileFwdStaged>);
+    case kTileBwd32: return go(k_loss_tile<kTileBwd32>);
+    default: return go(k_loss_tile<kTileBwd64>);
+  }
 }
 
 hipError_t launch_segment_min_node(const StepRec* rec, const uint64_t* start, uint32_t nseg, uint32_t* out,

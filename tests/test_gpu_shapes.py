@@ -124,7 +124,7 @@ def test_ordered_layout_with_coincident_and_distant_points(P, span):  # noqa: F8
 
 
 # few pairs (tiles not staged, one unit each), a tile cut into many units, every tile staged, a zipf window whose
-# tables leave no room for the staged coordinates (3,500 and more) and one without room for tiles, renumbered ids
+# tables just leave room for the image in double and one that takes the image in float, renumbered ids
 @pytest.mark.parametrize("backbone,paths,pairs,window,renumber", [
     (300, 3, 40, 1000, "auto"), (900, 4, 60000, 1000, "auto"), (9000, 5, 200, 1000, "auto"),
     (9000, 5, 300000, 1000, "always"), (5000, 6, 100001, 4000, "auto"), (5000, 6, 30011, 20000, "auto")])
