@@ -961,10 +961,9 @@ pgsgd_status ensure_sps_windowed(pgsgd_graph* g, hipStream_t s) {
   return ensure_seg_tables(g, g->sps, window_shift(g->S), s);
 }
 
-// Tiles of the loss adjoint: the loss's segments grouped by the lowest device
-// node id their steps visit, in units of kTileNodes ids; a tile (at most
-// kTileMaxSeg segments; a fuller group is split) accumulates the gradient of
-// the 2 * kTileNodes ids from its base in LDS.
+// Tiles of the loss: its segments grouped by the lowest device node id that
+// their steps visit, in units of kTileNodes ids, at most kTileMaxSeg a tile (a
+// fuller group is split); a tile's range begins at the lowest id of its own.
 pgsgd_status ensure_loss_tiles(pgsgd_graph* g, hipStream_t s) {
   const SegTables& T = g->loss;
   if (g->d_tile_seg && g->tile_shift == T.shift) return PGSGD_OK;
@@ -993,7 +992,9 @@ pgsgd_status ensure_loss_tiles(pgsgd_graph* g, hipStream_t s) {
   for (uint32_t key = 0; key < n_keys; ++key)
     for (uint32_t a = kb[key]; a < kb[key + 1]; a += kTileMaxSeg) {
       toff.push_back(std::min(kb[key + 1], a + kTileMaxSeg));
-      tbase.push_back(key * kTileNodes);
+      uint32_t low = UINT32_MAX;
+      for (uint32_t k = a; k < toff.back(); ++k) low = std::min(low, lo[order[k]]);
+      tbase.push_back(low);
     }
   const uint32_t nt = (uint32_t)tbase.size();
   st = [&]() -> pgsgd_status {
@@ -1680,27 +1681,31 @@ pgsgd_status loss_win_prepare(pgsgd_graph* g, const pgsgd_params* p, const Stres
   return PGSGD_OK;
 }
 
-// Whether the power-law tables of window W leave a block room for `form`.
-bool tile_fits(const pgsgd_graph* g, uint32_t W, TileForm form) {
-  return loss_tile_lds_bytes(W, form) + kTileStaticLds <= g->lds_limit;
-}
+// Whether the power-law tables of window W leave the tiles room (their smallest image, in float).
+bool tiles_fit(const pgsgd_graph* g, uint32_t W) { return loss_tile_entries(W, kTileBwd32, g->lds_limit) != 0; }
 
-// The tiles of one pass and its grid.  The forward pass stages a tile's
-// coordinates where two blocks of a CU have room and there are enough pairs to
-// use them: staging reads the 512 lines of 4,096 nodes once, not staging two
-// scattered lines a pair.
+// The tiles of one pass and its grid.  A unit's range is staged from 512 pairs
+// on: staging reads its lines once (three to four loads a thread), not staging
+// two scattered lines a pair.  The two are even at the 1,200 pairs a unit of a
+// small graph (12.7 and 12.9 us for 1e5 pairs over 20,000 backbone nodes).
 TileLaunch loss_tile_launch(const pgsgd_graph* g, const pgsgd_params* p, uint64_t n_pairs, bool grad,
                             uint32_t* blocks) {
-  const uint32_t W = p->zipf_window;
-  TileLaunch T{g->d_tile_seg, g->d_tile_off, g->d_tile_base, g->n_tiles, 1, kTileFwd, g->d_tile_queue};
-  if (grad)
-    T.form = tile_fits(g, W, kTileBwd64) ? kTileBwd64 : kTileBwd32;
-  else if (2 * (loss_tile_lds_bytes(W, kTileFwdStaged) + kTileStaticLds) <= g->lds_limit &&
-           n_pairs >= 512ull * std::max(1u, g->n_tiles))
-    T.form = kTileFwdStaged;
-  const uint32_t per_cu = T.form == kTileBwd64 ? 1 : 2;  // blocks that a CU's LDS and waves hold
-  const uint32_t cap = per_cu * (uint32_t)g->n_cu;
+  TileLaunch T{g->d_tile_seg, g->d_tile_off, g->d_tile_base, g->n_tiles, 1, kTileFwd, 0, g->d_tile_queue};
+  const uint32_t cap = tile_blocks(grad ? kTileBwd64 : kTileFwd) * (uint32_t)g->n_cu;
   T.split = loss_tile_split(g->n_tiles, cap, n_pairs, grad);
+  const bool stage = n_pairs >= 512ull * std::max(1u, g->n_tiles) * T.split;
+  auto take = [&](TileForm form) {
+    const uint32_t n = loss_tile_entries(p->zipf_window, form, g->lds_limit);
+    if (n) {
+      T.form = form;
+      T.entries = n;
+    }
+    return n != 0;
+  };
+  if (grad)
+    (void)((stage && take(kTileBwd64Staged)) || take(kTileBwd64) || take(kTileBwd32));
+  else if (stage)
+    (void)take(kTileFwdStaged);
   *blocks = (uint32_t)std::max<uint64_t>(1, std::min<uint64_t>((uint64_t)g->n_tiles * T.split, cap));
   return T;
 }
@@ -1959,7 +1964,7 @@ pgsgd_status pgsgd_stress_forward(pgsgd_graph* g, const pgsgd_params* p, const f
   uint32_t parts = kStressBlocks;
   if (P.count && resolve_schedule(p) == PGSGD_SCHEDULE_WINDOWED) {
     SpsWinLaunch W;
-    const bool tiles = tile_fits(g, p->zipf_window, kTileBwd32);
+    const bool tiles = tiles_fit(g, p->zipf_window);
     if ((st = loss_win_prepare(g, p, P, n_pairs, s, &W, tiles))) return st;
     if (tiles) {
       if ((st = ensure_loss_tiles(g, s))) return st;
@@ -2001,7 +2006,7 @@ pgsgd_status pgsgd_stress_backward(pgsgd_graph* g, const pgsgd_params* p, const 
   if (resolve_schedule(p) == PGSGD_SCHEDULE_WINDOWED) {
     SpsWinLaunch W;
     // by tiles when their LDS image fits a block (it does for every window W up to ~10^4)
-    const bool tiles = tile_fits(g, p->zipf_window, kTileBwd32);
+    const bool tiles = tiles_fit(g, p->zipf_window);
     if ((st = loss_win_prepare(g, p, P, n_pairs, s, &W, tiles))) return st;
     if (tiles) {
       if ((st = ensure_loss_tiles(g, s))) return st;

@@ -100,18 +100,32 @@ hipError_t launch_loss_win_fwd(const SpsWinLaunch& W, double* part_f, uint64_t* 
                                hipStream_t s);
 hipError_t launch_loss_win_bwd(const SpsWinLaunch& W, const float* grad_out, const uint64_t* n_valid, float* grad,
                                uint32_t blocks, hipStream_t s);
-// The loss adjoint by tiles: block b takes tiles from *queue (zero at
-// launch); tile t covers the segments seg[off[t] .. off[t + 1]) (at most
-// kTileMaxSeg) and accumulates the gradient of device node ids [base[t],
-// base[t] + 2 * kTileNodes) in LDS, flushed with one atomic add per touched
-// entry; other endpoints are added directly.  The pairs are the window-major
-// loss pairs of W, the same slots as launch_loss_win_bwd.
-constexpr uint32_t kTileNodes = 2048;
+// The loss by tiles: tile t covers the segments seg[off[t] .. off[t + 1]) (at
+// most kTileMaxSeg), whose lowest device node ids lie in kTileNodes ids from
+// base[t] on, and keeps the endpoints of up to kTileRange ids from base[t] on in
+// LDS: their coordinates, and in the adjoint an image of their gradient, flushed
+// with one atomic add per touched entry; other endpoints are read and added
+// directly.  Block b starts with unit b and takes the others from *queue (zero
+// at launch).  The pairs are the window-major loss pairs of W, the same slots as
+// launch_loss_win_bwd.
+//
+// A segment's steps climb through up to ~2,000 ids, so what lies above the range
+// grows fast once the range is less than that beyond a tile's last start: over
+// 1e7 pairs the adjoint with 3,072 ids in LDS takes 207 us with tiles of 1,024
+// ids, 227 with 1,536 and 321 with 2,048; tiles of 512 zero and flush twice as
+// many images (253).
+constexpr uint32_t kTileNodes = 1024;
+constexpr uint32_t kTileRange = 4096;
 constexpr uint32_t kTileMaxSeg = 256;    // a segment's number in its tile is a byte of k_loss_tile's guide
 constexpr uint32_t kTileGuide = 1024;
 constexpr uint32_t kTileThreads = 1024;
 // The forms of k_loss_tile (see there).
-enum TileForm { kTileFwd, kTileFwdStaged, kTileBwd32, kTileBwd64 };
+enum TileForm { kTileFwd, kTileFwdStaged, kTileBwd32, kTileBwd64, kTileBwd64Staged };
+constexpr bool tile_grad(TileForm f) { return f != kTileFwd && f != kTileFwdStaged; }
+constexpr bool tile_double(TileForm f) { return f == kTileBwd64 || f == kTileBwd64Staged; }
+constexpr bool tile_staged(TileForm f) { return f == kTileFwdStaged || f == kTileBwd64Staged; }
+// Blocks of 16 waves that a CU holds: the images of the gradient leave room for one.
+constexpr uint32_t tile_blocks(TileForm f) { return tile_grad(f) ? 1 : 2; }
 struct TileLaunch {
   const uint32_t* seg;
   const uint32_t* off;
@@ -119,14 +133,16 @@ struct TileLaunch {
   uint32_t n_tiles;
   uint32_t split;  // parts of a tile's pairs, a unit of work each
   TileForm form;
+  uint32_t entries;  // loss_tile_entries
   uint32_t* queue;
 };
 // Parts of a tile.  A gradient unit zeroes and flushes the tile's whole image,
-// so its tiles stay whole while they fill the blocks; below that (and always
-// in the forward pass, which has no image) a tile is cut until the blocks have
-// `rounds` units each, with at least one pair for every thread.
+// so its tiles stay whole while they fill the blocks; below that (and in the
+// forward pass, which has no image) a tile is cut until the blocks have `rounds`
+// units each, with at least one pair for every thread.  Forward over 1e7 pairs
+// with 1, 2 and 4 units a block: 172, 161 and 165 us.
 inline uint32_t loss_tile_split(uint32_t n_tiles, uint32_t blocks, uint64_t n_pairs, bool grad) {
-  const uint64_t rounds = grad ? 1 : 4;
+  const uint64_t rounds = grad ? 1 : 2;
   const uint64_t want = (rounds * blocks + n_tiles - 1) / std::max(1u, n_tiles);
   const uint64_t room = n_pairs / ((uint64_t)kTileThreads * std::max(1u, n_tiles));
   if (grad && n_tiles >= blocks) return 1;
@@ -137,7 +153,10 @@ inline uint32_t loss_tile_split(uint32_t n_tiles, uint32_t blocks, uint64_t n_pa
 hipError_t launch_loss_tile(const SpsWinLaunch& W, const TileLaunch& T, const float* grad_out,
                             const uint64_t* n_valid, float* grad, double* part_f, uint64_t* part_n, uint32_t blocks,
                             hipStream_t s);
-size_t loss_tile_lds_bytes(uint32_t W, TileForm form);  // dynamic LDS of k_loss_tile
+// Endpoints (two a node) of a tile's range that fit beside the power-law tables
+// of window W, at most 2 * kTileRange; 0 if they are too few for the form to be
+// the faster one.
+uint32_t loss_tile_entries(uint32_t W, TileForm form, size_t lds_limit);
 constexpr size_t kTileStaticLds = 10 * 1024;  // static LDS of k_loss_tile (a tile's segment table), rounded up
 // out[g] = the lowest device node id over the steps [start[g], start[g + 1])
 hipError_t launch_segment_min_node(const StepRec* rec, const uint64_t* start, uint32_t nseg, uint32_t* out,

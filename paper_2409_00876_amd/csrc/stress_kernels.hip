@@ -882,37 +882,58 @@ __global__ __launch_bounds__(256) void k_loss_win(SpsWinLaunch W, const float* _
 // paths), so most of a tile's adjoint lands in an LDS image of that range and
 // reaches memory once per touched entry instead of once per pair.
 // ---------------------------------------------------------------------------
-size_t loss_tile_lds_bytes(uint32_t W, TileForm form) {
-  const size_t head = ((size_t)(W + 1) * 4 + (size_t)(kGuideSize + 1) * 2 + 15) & ~(size_t)15;
-  const size_t entry = form == kTileFwd ? 0 : form == kTileBwd64 ? sizeof(double2) : sizeof(float2);
-  return head + (size_t)4 * kTileNodes * entry;
+static size_t tile_tables_bytes(uint32_t W) {
+  return ((size_t)(W + 1) * 4 + (size_t)(kGuideSize + 1) * 2 + 15) & ~(size_t)15;
+}
+static size_t tile_entry_bytes(TileForm f) {
+  return (tile_grad(f) ? 2 * (tile_double(f) ? sizeof(double) : sizeof(float)) : 0) +
+         (tile_staged(f) ? sizeof(float2) : 0);
 }
 
-// kTileFwd, kTileFwdStaged: the forward pass over the same tiles (per-block
-// sums of the stress and the valid-pair count), with the coordinates of the
-// tile's ids copied to LDS first by coalesced loads; a pair's two records and
-// two coordinates are scattered 8 and 16-byte loads, 64 cache-line requests
-// each for a wave (the parts of the forward pass over 1e7 pairs: draws 80,
-// records 74, coordinates 78 us), and a tile's 22K pairs share 4,096 nodes.
+// The least entries that a form is taken for.  4e6 pairs over 300,000 backbone
+// nodes, by window W: the adjoint staged 67 / 113 / 129 / 158 us for W = 1,000 /
+// 4,000 / 6,000 / 9,000 (6,144 / 5,632 / 5,312 / 4,800 entries), not staged 79 /
+// 116 / 130 / 144, with the image in float 148 / 150 / 156 / 166; not staged in
+// double 173 and 214 for W = 17,000 and 20,000 (5,184 and 4,416 entries), in
+// float 176 and 179.  Forward staged and not: 51 / 57 / 60 / 66 and 63 / 72 / 75 / 77.
+uint32_t loss_tile_entries(uint32_t W, TileForm form, size_t lds_limit) {
+  if (form == kTileFwd) return 0;
+  const uint32_t least = form == kTileFwdStaged ? kTileRange : tile_double(form) ? 5120 : 2 * kTileRange;
+  const size_t have = lds_limit / tile_blocks(form), head = tile_tables_bytes(W) + kTileStaticLds;
+  const size_t fit = have > head ? (have - head) / tile_entry_bytes(form) : 0;
+  const uint32_t n = (uint32_t)std::min<size_t>(2 * kTileRange, fit & ~(size_t)63);
+  return n >= least ? n : 0;
+}
+
+// kTileFwd, kTileFwdStaged: the forward pass (per-block sums of the stress and
+// the valid-pair count).  kTileBwd32, kTileBwd64, kTileBwd64Staged: the adjoint,
+// its image in float or in double.
 //
-// kTileBwd32, kTileBwd64: the gradient, its image in float or in double.  A
-// wave's ds_add_f32 at scattered addresses takes 185 cycles here, ds_add_f64
-// 21 (and ds_add_u32 7), so the double image is the faster one and rounds once,
-// at the flush: 360 -> 282 us over 1e7 pairs.  It fills the LDS (128 KB), so
-// power-law tables of more than ~4,500 hops take the float image.  x and y have
-// planes of their own, so the adds of a wave use all banks.
+// Staged: the coordinates of the tile's ids are copied to LDS first by coalesced
+// loads, all in flight at once.  A pair's two records and two coordinates are
+// scattered 8 and 16-byte loads, 64 cache-line requests each for a wave: of the
+// 161 us of the forward pass over 1e7 pairs, draws take 62, records 52, staged
+// coordinates 8 (96 us if they are not staged) and the units' tables and copies
+// 36.  More pairs of a thread in flight do not help (two: 170 us).
+//
+// The image: a wave's ds_add_f32 at scattered addresses takes 185 cycles here,
+// ds_add_f64 21 (and ds_add_u32 7), so the double image is the faster one and
+// rounds once, at the flush; the float image remains where the tables leave the
+// double one too little room.  x and y have planes of their own, so the adds of a
+// wave use all banks.  Adjoint over 1e7 pairs: 360 us with staging and the image
+// in float, 278 in double without staging, 206 with both.
 //
 // A unit of work is one of T.split equal parts of a tile's pairs (see
 // loss_tile_split for where a tile is cut).
 template <TileForm kForm>
-__global__ __launch_bounds__(kTileThreads) void k_loss_tile(SpsWinLaunch W, TileLaunch T,
+__global__ __launch_bounds__(kTileThreads, tile_blocks(kForm) * 4) void k_loss_tile(SpsWinLaunch W, TileLaunch T,
                                                            const float* __restrict__ grad_out,
                                                            const uint64_t* __restrict__ n_valid,
                                                            float* __restrict__ grad, double* __restrict__ part_f,
                                                            uint64_t* __restrict__ part_n) {
-  constexpr bool kGrad = kForm == kTileBwd32 || kForm == kTileBwd64;
-  constexpr bool kStage = kForm == kTileFwdStaged;
-  using Acc = typename std::conditional<kForm == kTileBwd64, double, float>::type;
+  constexpr bool kGrad = tile_grad(kForm);
+  constexpr bool kStage = tile_staged(kForm);
+  using Acc = typename std::conditional<tile_double(kForm), double, float>::type;
   __shared__ double red_f[16];
   __shared__ uint64_t red_n[16];
   extern __shared__ __align__(16) char lds[];
@@ -927,11 +948,11 @@ __global__ __launch_bounds__(kTileThreads) void k_loss_tile(SpsWinLaunch W, Tile
   const StressLaunch& P = W.P;
   uint32_t* zipf = reinterpret_cast<uint32_t*>(lds);
   uint16_t* guide = reinterpret_cast<uint16_t*>(lds + (size_t)(P.W + 1) * 4);
-  constexpr uint32_t kAcc = 4 * kTileNodes;  // entries: 2 * kTileNodes nodes x 2 endpoints
+  const uint32_t n_acc = T.entries;  // endpoints of the tile's range: n_acc / 2 nodes x 2
   char* image = lds + (((size_t)(P.W + 1) * 4 + (size_t)(kGuideSize + 1) * 2 + 15) & ~(size_t)15);
   Acc* acc_x = reinterpret_cast<Acc*>(image);
-  Acc* acc_y = acc_x + kAcc;
-  float2* xy = reinterpret_cast<float2*>(image);
+  Acc* acc_y = acc_x + n_acc;
+  float2* xy = reinterpret_cast<float2*>(image + (kGrad ? (size_t)n_acc * 2 * sizeof(Acc) : 0));
   for (uint32_t k = threadIdx.x; k <= P.W; k += blockDim.x) zipf[k] = P.zipf[k];
   for (uint32_t k = threadIdx.x; k <= kGuideSize; k += blockDim.x) guide[k] = P.guide[k];
   double scale = 0.0;
@@ -949,24 +970,34 @@ __global__ __launch_bounds__(kTileThreads) void k_loss_tile(SpsWinLaunch W, Tile
     unsafeAtomicAdd(&GX[a], gx);
     unsafeAtomicAdd(&GY[a], gy);
   };
-  for (;;) {
-    __syncthreads();  // the previous unit's flush (and the tables above) are done
-    if (threadIdx.x == 0) s_unit = atomicAdd(T.queue, 1u);
-    __syncthreads();
-    const uint32_t t = s_unit / T.split, part = s_unit % T.split;
-    if (t >= T.n_tiles) break;
+  const uint32_t n_units = T.n_tiles * T.split;
+  uint32_t unit = blockIdx.x;  // the first one; the others from the queue
+  while (unit < n_units) {
+    const uint32_t t = unit / T.split, part = unit % T.split;
     const uint64_t base = T.base[t];
     const uint32_t k0 = T.off[t];
     const uint32_t nk = T.off[t + 1] - k0;
     if (kGrad)
-      for (uint32_t e = threadIdx.x; e < 2 * kAcc; e += blockDim.x) acc_x[e] = 0;
+      for (uint32_t e = threadIdx.x; e < 2 * n_acc; e += blockDim.x) acc_x[e] = 0;
+    // the coordinates of the range, a node (two endpoints) a load, all in flight at once
+    constexpr uint32_t kLoads = kTileRange / kTileThreads;
+    using Pair2 = float __attribute__((ext_vector_type(2)));
+    using Node = float __attribute__((ext_vector_type(4)));  // float4 arrays go to scratch
+    Node node[kLoads];
+    const uint32_t nodes = (uint32_t)min((uint64_t)(n_acc / 2), P.n_nodes - base);
     if (kStage) {
-      const uint32_t ends = (uint32_t)min((uint64_t)kAcc, 2 * (P.n_nodes - base));
-      for (uint32_t e = threadIdx.x; e < ends; e += blockDim.x) xy[e] = P.work[2 * base + e];
+      const Node* __restrict__ work = reinterpret_cast<const Node*>(P.work) + base;
+#pragma unroll
+      for (uint32_t q = 0; q < kLoads; ++q) {
+        const uint32_t e = threadIdx.x + q * kTileThreads;
+        if (e < nodes) node[q] = work[e];
+      }
     }
     auto coords = [&](uint64_t a) -> float2 {
       const uint64_t e = a - 2 * base;  // wraps to huge below the base
-      return kStage && e < kAcc ? xy[e] : P.work[a];
+      if (!kStage || e >= n_acc) return P.work[a];
+      const Pair2 v = ((const __attribute__((address_space(3))) Pair2*)xy)[e];  // or both became flat loads
+      return make_float2(v.x, v.y);
     };
     for (uint32_t k = threadIdx.x; k < nk; k += blockDim.x) {
       const uint32_t g = T.seg[k0 + k];
@@ -977,6 +1008,13 @@ __global__ __launch_bounds__(kTileThreads) void k_loss_tile(SpsWinLaunch W, Tile
       const uint32_t p = W.seg_path[g];
       s_pst[k] = P.path_off[p];
       s_plen[k] = (uint32_t)(P.path_off[p + 1] - P.path_off[p]);
+    }
+    if (kStage) {
+#pragma unroll
+      for (uint32_t q = 0; q < kLoads; ++q) {
+        const uint32_t e = threadIdx.x + q * kTileThreads;
+        if (e < nodes) reinterpret_cast<Node*>(xy)[e] = node[q];
+      }
     }
     __syncthreads();
     if (threadIdx.x < 64) {  // inclusive prefix by one wave, 64 segments at a time
@@ -1032,26 +1070,30 @@ __global__ __launch_bounds__(kTileThreads) void k_loss_tile(SpsWinLaunch W, Tile
       const double c = gradient_factor(scale, mag, d);
       const Acc gx = (Acc)(c * dx), gy = (Acc)(c * dy);
       const uint64_t ea = a - 2 * base, eb = b - 2 * base;  // wrap to huge below the base
-      if (ea < kAcc) {
+      if (ea < n_acc) {
         unsafeAtomicAdd(&acc_x[ea], gx);
         unsafeAtomicAdd(&acc_y[ea], gy);
       } else {
         global_add(a, (float)gx, (float)gy);
       }
-      if (eb < kAcc) {
+      if (eb < n_acc) {
         unsafeAtomicAdd(&acc_x[eb], -gx);
         unsafeAtomicAdd(&acc_y[eb], -gy);
       } else {
         global_add(b, (float)-gx, (float)-gy);
       }
     }
-    if (kGrad) {
-      __syncthreads();
-      for (uint32_t e = threadIdx.x; e < kAcc; e += blockDim.x) {
+    if (kGrad) __syncthreads();  // the image is complete
+    const bool more = n_units > gridDim.x;
+    if (more && threadIdx.x == 0) s_unit = gridDim.x + atomicAdd(T.queue, 1u);
+    if (kGrad)
+      for (uint32_t e = threadIdx.x; e < n_acc; e += blockDim.x) {
         const float vx = (float)acc_x[e], vy = (float)acc_y[e];
         if ((vx != 0.0f || vy != 0.0f) && 2 * base + e < 2 * P.n_nodes) global_add(2 * base + e, vx, vy);
       }
-    }
+    if (!more) break;
+    __syncthreads();  // the tile's tables and image are free again
+    unit = uniform_u32(s_unit);
   }
   if (!kGrad) {
     sum = block_sum(sum, red_f);
@@ -1255,7 +1297,8 @@ hipError_t launch_loss_tile(const SpsWinLaunch& W, const TileLaunch& T, const fl
                             const uint64_t* n_valid, float* grad, double* part_f, uint64_t* part_n, uint32_t blocks,
                             hipStream_t s) {
   auto go = [&](auto kernel) {
-    hipLaunchKernelGGL(kernel, dim3(blocks), dim3(kTileThreads), loss_tile_lds_bytes(W.P.W, T.form), s, W, T, grad_out,
+    hipLaunchKernelGGL(kernel, dim3(blocks), dim3(kTileThreads),
+                       tile_tables_bytes(W.P.W) + T.entries * tile_entry_bytes(T.form), s, W, T, grad_out,
                        n_valid, grad, part_f, part_n);
     return hipGetLastError();
   };
@@ -1263,7 +1306,8 @@ hipError_t launch_loss_tile(const SpsWinLaunch& W, const TileLaunch& T, const fl
     case kTileFwd: return go(k_loss_tile<kTileFwd>);
     case kTileFwdStaged: return go(k_loss_tile<kTileFwdStaged>);
     case kTileBwd32: return go(k_loss_tile<kTileBwd32>);
-    default: return go(k_loss_tile<kTileBwd64>);
+    case kTileBwd64: return go(k_loss_tile<kTileBwd64>);
+    default: return go(k_loss_tile<kTileBwd64Staged>);
   }
 }
 

@@ -123,11 +123,12 @@ def test_ordered_layout_with_coincident_and_distant_points(P, span):  # noqa: F8
     assert span > 60 or bool(torch.isfinite(a).all())
 
 
-# few pairs (tiles not staged, one unit each), a tile cut into many units, every tile staged, a zipf window whose
-# tables just leave room for the image in double and one that takes the image in float, renumbered ids
+# few pairs (tiles not staged, one unit each), a tile cut into many units, every tile staged, zipf windows whose tables
+# leave room for a shorter range, for none staged and for the image in float alone, renumbered ids
 @pytest.mark.parametrize("backbone,paths,pairs,window,renumber", [
     (300, 3, 40, 1000, "auto"), (900, 4, 60000, 1000, "auto"), (9000, 5, 200, 1000, "auto"),
-    (9000, 5, 300000, 1000, "always"), (5000, 6, 100001, 4000, "auto"), (5000, 6, 30011, 20000, "auto")])
+    (9000, 5, 300000, 1000, "always"), (5000, 6, 100001, 4000, "auto"), (9000, 5, 100003, 9000, "auto"),
+    (5000, 6, 30011, 20000, "auto")])
 def test_loss_tiles_at_their_split_sizes(P, backbone, paths, pairs, window, renumber):  # noqa: F811
     import torch
     sg = synth.generate(backbone, 0.2, paths, 31)
