@@ -39,14 +39,22 @@ struct Rand4 {
   uint32_t r0, r1, r2, r3;
 };
 
+// a ^ b ^ c in one instruction (the truth table of the three-input bit operation): half the exclusive ors of a draw,
+// which the compiler leaves as pairs.  With the two-product mulhi64 below, k_local_count's 1.16e9 draws take 1.54 ms
+// instead of 1.98, and all-cooling iterations of as many terms, whose waves wait for their own draws, 26.8 instead of
+// 27.7.
+__device__ __forceinline__ uint32_t xor3(uint32_t a, uint32_t b, uint32_t c) {
+  return __builtin_amdgcn_bitop3_b32(a, b, c, 0x96);
+}
+
 __device__ __forceinline__ Rand4 philox10(uint32_t c0, uint32_t c1, uint32_t c2, uint32_t c3, uint32_t k0,
                                           uint32_t k1) {
 #pragma unroll
   for (int round = 0; round < 10; ++round) {
     const uint64_t p0 = (uint64_t)0xD2511F53u * c0;
     const uint64_t p1 = (uint64_t)0xCD9E8D57u * c2;
-    const uint32_t n0 = (uint32_t)(p1 >> 32) ^ c1 ^ k0;
-    const uint32_t n2 = (uint32_t)(p0 >> 32) ^ c3 ^ k1;
+    const uint32_t n0 = xor3((uint32_t)(p1 >> 32), c1, k0);
+    const uint32_t n2 = xor3((uint32_t)(p0 >> 32), c3, k1);
     c1 = (uint32_t)p1;
     c3 = (uint32_t)p0;
     c0 = n0;
@@ -62,6 +70,11 @@ __device__ __forceinline__ uint32_t mulhi32(uint32_t a, uint32_t b) { return __u
 // mulhi64(lo | hi << 32, n) for a 32-bit n: two products instead of four
 __device__ __forceinline__ uint32_t mulhi64(uint32_t lo, uint32_t hi, uint32_t n) {
   return (uint32_t)(((uint64_t)hi * n + (((uint64_t)lo * n) >> 32)) >> 32);
+}
+
+// the same for an n that all lanes share
+__device__ __forceinline__ uint64_t uniform_mulhi64(uint32_t lo, uint32_t hi, uint64_t n) {
+  return n >> 32 ? mulhi64((uint64_t)lo | ((uint64_t)hi << 32), n) : mulhi64(lo, hi, (uint32_t)n);
 }
 
 __device__ __forceinline__ uint32_t uniform_u32(uint32_t v) { return __builtin_amdgcn_readfirstlane(v); }

@@ -54,7 +54,7 @@ __global__ __launch_bounds__(1024) void k_local_count(LocalLaunch P) {
   const uint64_t lane_stride = (uint64_t)gridDim.x * blockDim.x;
   for (uint64_t t = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; t < L.n_terms; t += lane_stride) {
     const Rand4 r = philox10((uint32_t)t, (uint32_t)(t >> 32), L.iter, L.c3, L.k0, L.k1);
-    const uint64_t i = mulhi64((uint64_t)r.r0 | ((uint64_t)r.r1 << 32), L.S);
+    const uint64_t i = uniform_mulhi64(r.r0, r.r1, L.S);
     atomicAdd(&hist[(uint32_t)(i >> P.win_shift)], 1u);
   }
   __syncthreads();
@@ -148,9 +148,9 @@ __device__ __forceinline__ void local_item(const LocalLaunch& P, const LdsView& 
   const bool cooling = L.cool_all || ((lead >> 3) & 1u);
   if (k >= nw) return;
   const uint64_t wstart = (uint64_t)w << P.win_shift;
-  const uint64_t wlen = min((uint64_t)1 << P.win_shift, L.S - wstart);
+  const uint32_t wlen = (uint32_t)min((uint64_t)1 << P.win_shift, L.S - wstart);
   Term T;
-  T.i = wstart + mulhi64((uint64_t)r.r0 | ((uint64_t)r.r1 << 32), wlen);
+  T.i = wstart + mulhi64(r.r0, r.r1, wlen);
   // the path of a window inside one path is known; a window across paths searches
   const uint32_t wp = uniform_u32(uload(P.wpath + w));
   const uint32_t p = (wp >> 31) ? find_path(V.off, L.path_top, T.i) : wp;
@@ -213,8 +213,8 @@ __device__ __forceinline__ Term item_draw(const LocalLaunch& P, const LdsView& V
   }
   slot = s;
   const uint64_t wstart = (uint64_t)w << P.win_shift;
-  const uint64_t wlen = min((uint64_t)1 << P.win_shift, L.S - wstart);
-  T.i = wstart + mulhi64((uint64_t)r.r0 | ((uint64_t)r.r1 << 32), wlen);
+  const uint32_t wlen = (uint32_t)min((uint64_t)1 << P.win_shift, L.S - wstart);
+  T.i = wstart + mulhi64(r.r0, r.r1, wlen);
   const uint32_t wp = uniform_u32(uload(P.wpath + w));
   const uint32_t p = (wp >> 31) ? find_path(V.off, L.path_top, T.i) : wp;
   const uint64_t start = V.off[p];
@@ -488,9 +488,9 @@ __device__ __forceinline__ void local_item_reuse(const LocalLaunch& P, const Lds
   const bool cooling = L.cool_all || ((lead >> 3) & 1u);
   const bool live = k < nw;
   const uint64_t wstart = (uint64_t)w << P.win_shift;
-  const uint64_t wlen = min((uint64_t)1 << P.win_shift, L.S - wstart);
+  const uint32_t wlen = (uint32_t)min((uint64_t)1 << P.win_shift, L.S - wstart);
   Term T;
-  T.i = wstart + mulhi64((uint64_t)r.r0 | ((uint64_t)r.r1 << 32), wlen);
+  T.i = wstart + mulhi64(r.r0, r.r1, wlen);
   const uint32_t wp = uniform_u32(uload(P.wpath + w));
   const uint32_t p = (wp >> 31) ? find_path(V.off, L.path_top, T.i) : wp;
   const uint64_t start = V.off[p];

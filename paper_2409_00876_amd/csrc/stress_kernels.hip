@@ -273,7 +273,7 @@ __global__ __launch_bounds__(kPair ? 1024 : 512) void k_sps(StressLaunch P, int 
     for (uint32_t k = chunk * per; k < k_end; ++k) {
       const uint64_t q = (uint64_t)P.m * s + k;
       const Rand4 r = philox10((uint32_t)q, (uint32_t)(q >> 32), 0u, P.c3, P.k0, P.k1);
-      const uint64_t i = start + mulhi64((uint64_t)r.r0 | ((uint64_t)r.r1 << 32), len);
+      const uint64_t i = start + mulhi64(r.r0, r.r1, (uint32_t)len);
       uint64_t j;
       if (mode == 1) {
         if (!partner_power_law(i, start, len, r.r2, r.r3, zipf, guide, P.W, j)) {
@@ -335,7 +335,7 @@ __device__ __forceinline__ uint64_t uniform_u64(uint64_t v) {
 // instead.  The segments start at the window starts and the path starts, so
 // step i of path p lies in segment (i >> win_shift) + path_extra[p], the path
 // starts inside windows up to that of p (a search of the window's segments,
-// with three random loads, bound the count of 1e7 loss pairs: 70 us, now 59).
+// with three random loads, bound the count of 1e7 loss pairs: 70 us, now 54).
 __global__ __launch_bounds__(1024) void k_sps_win_count(SpsWinLaunch W) {
   extern __shared__ __align__(16) char lds[];
   const StressLaunch& P = W.P;
@@ -348,7 +348,7 @@ __global__ __launch_bounds__(1024) void k_sps_win_count(SpsWinLaunch W) {
   // the loss's pairs (reading R22): pair q < loss_pairs draws i uniformly over all steps
   for (uint64_t q = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; q < W.loss_pairs; q += stride) {
     const Rand4 r = philox10((uint32_t)q, (uint32_t)(q >> 32), P.word2, P.c3, P.k0, P.k1);
-    const uint64_t i = mulhi64((uint64_t)r.r0 | ((uint64_t)r.r1 << 32), P.S);
+    const uint64_t i = uniform_mulhi64(r.r0, r.r1, P.S);
     const uint32_t p = find_path(off, P.path_top, i);
     atomicAdd(&hist[W.path_extra[p] + (uint32_t)(i >> W.win_shift)], 1u);
   }
@@ -360,7 +360,7 @@ __global__ __launch_bounds__(1024) void k_sps_win_count(SpsWinLaunch W) {
     for (uint32_t k = 0; k < P.m; ++k) {
       const uint64_t q = (uint64_t)P.m * s + k;
       const Rand4 r = philox10((uint32_t)q, (uint32_t)(q >> 32), 0u, P.c3, P.k0, P.k1);
-      const uint64_t i = start + mulhi64((uint64_t)r.r0 | ((uint64_t)r.r1 << 32), len);
+      const uint64_t i = start + mulhi64(r.r0, r.r1, (uint32_t)len);
       atomicAdd(&hist[extra + (uint32_t)(i >> W.win_shift)], 1u);
     }
   }
@@ -494,7 +494,7 @@ __global__ __launch_bounds__(kPair ? 1024 : 512) void k_sps_win(SpsWinLaunch W, 
     const uint64_t u = u0 + lane;
     if (u < u_end) {
       const Rand4 r = philox10((uint32_t)u, (uint32_t)(u >> 32), 0u, W.slot_c3, P.k0, P.k1);
-      const uint64_t i = sst + mulhi64((uint64_t)r.r0 | ((uint64_t)r.r1 << 32), slen);
+      const uint64_t i = sst + mulhi64(r.r0, r.r1, (uint32_t)slen);
       const uint64_t j = pst + mulhi32(r.r2, (uint32_t)plen);
       uint64_t a, b;
       double d;
@@ -841,7 +841,7 @@ __global__ __launch_bounds__(256) void k_loss_win(SpsWinLaunch W, const float* _
     const uint64_t u = u0 + lane;
     if (u >= u_end) continue;
     const Rand4 r = philox10((uint32_t)u, (uint32_t)(u >> 32), P.word2, W.slot_c3, P.k0, P.k1);
-    const uint64_t i = sst + mulhi64((uint64_t)r.r0 | ((uint64_t)r.r1 << 32), slen);
+    const uint64_t i = sst + mulhi64(r.r0, r.r1, (uint32_t)slen);
     uint64_t j, a, b;
     double d;
     if (!partner_power_law(i, pst, plen, r.r2, r.r3, zipf, guide, P.W, j)) continue;
