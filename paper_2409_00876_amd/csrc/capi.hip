@@ -179,7 +179,7 @@ struct pgsgd_graph {
   double* d_out_f = nullptr;    // [8]
   uint64_t* d_out_n = nullptr;  // [4]
   SpsHostSums* h_sums = nullptr;  // pinned, on first use
-  float2* d_work2 = nullptr;    // a second layout's working copy (pgsgd_path_stress_compare, on first use)
+  float2* d_work2 = nullptr;    // the second half of two layouts' copy (pgsgd_path_stress_compare, on first use)
   size_t device_bytes = 0;
   std::unordered_map<void*, size_t> alloc_bytes;  // size of every lazily allocated buffer
   int layout_blocks_per_cu = 0;  // occupancy of k_layout_iter, filled on first use
@@ -1864,8 +1864,8 @@ pgsgd_status path_stress_impl(pgsgd_graph* g, const float* coords, uint32_t m, u
     W = sps_win_launch(g, g->sps, P, kStreamSpsSlot, graph_id, 0);
   }
   if (!g->h_sums) HIP_TRY(hipHostMalloc((void**)&g->h_sums, sizeof(SpsHostSums), hipHostMallocDefault));
-  HIP_TRY(launch_to_work(coords, g->d_work, g->n_nodes, g->d_inv, s));
-  if (coords_b) HIP_TRY(launch_to_work(coords_b, g->d_work2, g->n_nodes, g->d_inv, s));
+  if (coords_b) HIP_TRY(launch_to_work_pair(coords, coords_b, g->d_work, g->d_work2, g->n_nodes, g->d_inv, s));
+  else HIP_TRY(launch_to_work(coords, g->d_work, g->n_nodes, g->d_inv, s));
   uint32_t parts = 0;
   if (windowed) {
     HIP_TRY(launch_sps_win_count_scan(W, true, s));

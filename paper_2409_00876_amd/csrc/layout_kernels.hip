@@ -190,6 +190,21 @@ __global__ __launch_bounds__(256) void k_to_work(const float* __restrict__ coord
   }
 }
 
+// Two layouts side by side, for the metric of both on the same pairs: endpoint k
+// is (x, y) of the first and (x, y) of the second, in `lo` for the first half of
+// the endpoints and in `hi` for the others (the working copies' own memory).
+__global__ __launch_bounds__(256) void k_to_work_pair(const float* __restrict__ a, const float* __restrict__ b,
+                                                      float4* __restrict__ lo, float4* __restrict__ hi, uint64_t n2,
+                                                      const uint32_t* __restrict__ inv) {
+  const uint64_t stride = (uint64_t)gridDim.x * blockDim.x;
+  for (uint64_t k = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; k < n2; k += stride) {
+    const uint64_t c = inv ? 2ull * inv[k >> 1] + (k & 1) : k;
+    const float4 v = make_float4(a[c], a[n2 + c], b[c], b[n2 + c]);
+    if (k < n2 / 2) lo[k] = v;
+    else hi[k - n2 / 2] = v;
+  }
+}
+
 __global__ __launch_bounds__(256) void k_from_work(const float2* __restrict__ work, float* __restrict__ coords,
                                                    uint64_t n2, const uint32_t* __restrict__ inv) {
   const uint64_t stride = (uint64_t)gridDim.x * blockDim.x;
@@ -233,6 +248,13 @@ hipError_t launch_to_work(const float* coords, float2* work, uint64_t n_nodes, c
                           uint32_t* zero) {
   hipLaunchKernelGGL(k_to_work, dim3(elementwise_grid(2 * n_nodes)), dim3(256), 0, s, coords, work, 2 * n_nodes,
                      inv, zero);
+  return hipGetLastError();
+}
+
+hipError_t launch_to_work_pair(const float* a, const float* b, float2* work, float2* work2, uint64_t n_nodes,
+                               const uint32_t* inv, hipStream_t s) {
+  hipLaunchKernelGGL(k_to_work_pair, dim3(elementwise_grid(2 * n_nodes)), dim3(256), 0, s, a, b,
+                     reinterpret_cast<float4*>(work), reinterpret_cast<float4*>(work2), 2 * n_nodes, inv);
   return hipGetLastError();
 }
 

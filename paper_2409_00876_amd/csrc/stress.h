@@ -19,7 +19,8 @@ struct StressLaunch {
   const float* coords;
   const float2* work;      // interleaved copy of coords (sampled path stress only)
   const uint32_t* inv;     // renumbered graph: caller id of every device node id (else NULL)
-  const float2* work2;     // a second layout's interleaved copy: the SPS evaluates it on the same pairs
+  const float2* work2;     // not NULL: the SPS of two layouts on the same pairs, whose copy work and work2 hold
+                           // (k_to_work_pair)
   const uint64_t* path_off;
   const uint32_t* zipf;
   const uint16_t* guide;

@@ -170,12 +170,25 @@ struct SpsAcc {
   Sum2 v[kSums];
   uint64_t nv = 0, ns = 0;
 
-  __device__ __forceinline__ void take(const StressLaunch& P, uint64_t a, uint64_t b, double d, double st) {
+  // The stress of endpoints a and b, and with two layouts the second one's (sb).
+  // The two layouts' coordinates lie side by side, one line an endpoint: a pair's
+  // lines, not its arithmetic, bound the kernel (2.9e7 power-law pairs, 303K nodes: 1.91 ms apart, 1.32 so).
+  static __device__ __forceinline__ double stress(const StressLaunch& P, uint64_t a, uint64_t b, double d, double& sb) {
+    if constexpr (kPair) {
+      const float4* lo = reinterpret_cast<const float4*>(P.work);
+      const float4* hi = reinterpret_cast<const float4*>(P.work2) - P.n_nodes;
+      const float4 va = (a < P.n_nodes ? lo : hi)[a], vb = (b < P.n_nodes ? lo : hi)[b];
+      sb = pair_stress(make_float2(va.z, va.w), make_float2(vb.z, vb.w), d);
+      return pair_stress(make_float2(va.x, va.y), make_float2(vb.x, vb.y), d);
+    }
+    return stress_work(P.work, a, b, d);
+  }
+
+  __device__ __forceinline__ void take(double st, double sb) {
     ++nv;
     v[0].add(st);
     v[1].add_product(st, st);
     if constexpr (kPair) {
-      const double sb = stress_work(P.work2, a, b, d);
       v[2].add(sb);
       v[3].add_product(sb, sb);
       v[4].add_product(st, sb);
@@ -289,9 +302,10 @@ __global__ __launch_bounds__(kPair ? 1024 : 512) void k_sps(StressLaunch P, int 
         ++acc.ns;
         continue;
       }
-      const double st = stress_work(P.work, a, b, d);
+      double sb = 0.0;
+      const double st = acc.stress(P, a, b, d, sb);
       keep_outlier(P, i, j, r.r3 & 3u, st);
-      acc.take(P, a, b, d, st);
+      acc.take(st, sb);
     }
   }
   acc.write(lds, blockIdx.x, gridDim.x, part_f, part_n, part_skip);
@@ -501,9 +515,10 @@ __global__ __launch_bounds__(kPair ? 1024 : 512) void k_sps_win(SpsWinLaunch W, 
       if (!pair_terms(P.rec, i, j, r.r3 & 1u, (r.r3 >> 1) & 1u, a, b, d)) {
         ++acc.ns;
       } else {
-        const double st = stress_work(P.work, a, b, d);
+        double sb = 0.0;
+        const double st = acc.stress(P, a, b, d, sb);
         keep_outlier(P, i, j, r.r3 & 3u, st);
-        acc.take(P, a, b, d, st);
+        acc.take(st, sb);
       }
     }
   }

@@ -151,3 +151,24 @@ def test_loss_tiles_at_their_split_sizes(P, backbone, paths, pairs, window, renu
     t[: 2 * sg.n_nodes] = 0.0
     t[0] = float("inf")
     assert P.stress_forward(g, t, pairs, 0, **kw)[0].item() in (float("inf"), 0.0) or pairs < 1000
+
+
+# an odd number of nodes (the copy's halves meet inside a node) and renumbered ids; FP64 terms summed in
+# another order: 1e-9
+@pytest.mark.parametrize("pairs", ["uniform", "power_law", "uniform_windowed"])
+@pytest.mark.parametrize("backbone,renumber", [(301, "auto"), (1203, "always")])
+def test_two_layouts_side_by_side(P, backbone, renumber, pairs):  # noqa: F811
+    import torch
+    sg = synth.generate(backbone, 0.2, 5, 23)
+    og, g = O.Graph.from_synth(sg), P.Graph.from_synth(sg, renumber=renumber)
+    rng = np.random.default_rng(backbone)
+    ca = (O.init_coords(og) + rng.normal(scale=3.0, size=4 * sg.n_nodes)).astype(np.float32)
+    cb = (O.init_coords(og) + rng.normal(scale=9.0, size=4 * sg.n_nodes)).astype(np.float32)
+    ref = O.sps_compare(og, ca, cb, m=7, seed=5, pairs=pairs)
+    ta, tb = torch.from_numpy(ca).cuda(), torch.from_numpy(cb).cuda()
+    r = P.path_stress_compare(g, ta, tb, 7, 5, pairs=pairs)
+    assert r["n_valid"] == ref["n_valid"] and r["n_skipped"] == ref["n_skipped"]
+    for k in ("sum_a", "sum_b", "ratio", "sd_a", "sd_b", "sd_diff"):
+        assert abs(r[k] - ref[k]) <= 1e-9 * abs(ref[k]), k
+    one = P.path_stress(g, ta, 7, seed=5, pairs=pairs)  # the copy of one layout afterwards
+    assert one["n_valid"] == r["n_valid"] and abs(one["mean"] - ref["mean_a"]) <= 1e-9 * abs(ref["mean_a"])
