@@ -266,7 +266,8 @@ enum { PGSGD_FLAG_COUNT_AHEAD = 1, PGSGD_FLAG_COUNT_IN_ORDER = 2 };
 
 /* Processing order of the terms of an iteration.
  *   PLAIN    term groups in index order over a grid capped by
- *            max_inflight_waves
+ *            max_inflight_waves (automatic: n_nodes / 2048 below 16,384 nodes,
+ *            the larger of that and min(n_nodes / 64, 1024) from there on)
  *   WINDOWED window-major enumeration: the steps are cut into windows of
  *            2^h consecutive global steps (h = 14, decreased while there
  *            would be fewer than 16 windows but not below 6, increased while
@@ -288,7 +289,15 @@ enum { PGSGD_FLAG_COUNT_AHEAD = 1, PGSGD_FLAG_COUNT_IN_ORDER = 2 };
  *            waves in every iteration (automatic: about nodes_w / 8, nodes_w =
  *            2^h * n_nodes * n_paths / S the nodes a window visits, and
  *            nodes_w / 32 in the iterations t >= n_iters / 2, whose partners
- *            all lie in the active window; both at most the PLAIN cap).
+ *            all lie in the active window; both at most n_nodes / 2048 below
+ *            32,768 nodes and the largest of n_nodes / 2048,
+ *            min(n_nodes / 512, 3584) and min(n_nodes / 64, 1024) from there
+ *            on, and the first eighth of the iterations at most
+ *            max(n_nodes / 2048, 512); in a batch n_nodes / 2048, or twice
+ *            that if every graph has 32,768 nodes or more).  A layout of one
+ *            wave takes its terms from a list of one iteration's, at most
+ *            64 MB, that the graph (or the batch) keeps; it is the same
+ *            layout bit for bit without it.
  *            Uniform-partner updates read the partner first and the window-
  *            local endpoint after it arrived, which keeps the window in which
  *            a concurrent update of a local node can be lost short.  Scratch: a few

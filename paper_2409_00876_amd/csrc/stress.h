@@ -87,7 +87,7 @@ struct SpsWinLaunch {
   uint64_t* seg_off;          // [n_seg + 1] first slot of every segment
   const uint32_t* sbeg;       // [kXcds + 1] first segment of every run
   uint64_t* xitem;            // [kXcds][xstride] prefix of 64-slot items over the segments of each run
-  uint64_t* queue;            // [2][kXcds][16] item counters of the two passes (zeroed by the scan)
+  uint64_t* queue;            // [2][kXcds][16] item counters of the loss's passes or the SPS (zeroed by the scan)
   uint64_t loss_pairs;        // the loss's window-major pairs (reading R22): the number of plain pairs; 0 = SPS
 };
 // runs: also the runs' item prefixes and counters, which the passes by tiles do not read
