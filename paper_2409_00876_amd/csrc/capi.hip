@@ -8,6 +8,7 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
+#include <functional>
 #include <atomic>
 #include <chrono>
 #include <cmath>
@@ -1002,6 +1003,8 @@ pgsgd_status ensure_loss_tiles(pgsgd_graph* g, hipStream_t s) {
     if ((e = dev_alloc(g, &g->d_tile_off, nt + 1))) return e;
     if ((e = dev_alloc(g, &g->d_tile_base, std::max<uint32_t>(nt, 1)))) return e;
     if ((e = dev_alloc(g, &g->d_tile_queue, 64))) return e;
+    const uint32_t none[64] = {};
+    HIP_TRY(hipMemcpy(g->d_tile_queue, none, sizeof(none), hipMemcpyHostToDevice));
     if (nseg) HIP_TRY(hipMemcpy(g->d_tile_seg, order.data(), sizeof(uint32_t) * nseg, hipMemcpyHostToDevice));
     HIP_TRY(hipMemcpy(g->d_tile_off, toff.data(), sizeof(uint32_t) * (nt + 1), hipMemcpyHostToDevice));
     if (nt) HIP_TRY(hipMemcpy(g->d_tile_base, tbase.data(), sizeof(uint32_t) * nt, hipMemcpyHostToDevice));
@@ -1688,11 +1691,16 @@ bool tiles_fit(const pgsgd_graph* g, uint32_t W) { return loss_tile_entries(W, k
 // on: staging reads its lines once (three to four loads a thread), not staging
 // two scattered lines a pair.  The two are even at the 1,200 pairs a unit of a
 // small graph (12.7 and 12.9 us for 1e5 pairs over 20,000 backbone nodes).
-TileLaunch loss_tile_launch(const pgsgd_graph* g, const pgsgd_params* p, uint64_t n_pairs, bool grad,
-                            uint32_t* blocks) {
-  TileLaunch T{g->d_tile_seg, g->d_tile_off, g->d_tile_base, g->n_tiles, 1, kTileFwd, 0, g->d_tile_queue};
+//
+// The caller's coordinates are read in place where the ids are the caller's and
+// the range is staged (or the pairs are too few for that): a copy of them all
+// costs a launch and 12 us for 1.8M nodes (a step of 1e7 pairs: 509 -> 488 us).  Elsewhere (pairs that read scattered
+// endpoints, renumbered ids, a gradient that overlaps them) the working copy.
+TileLaunch loss_tile_launch(const pgsgd_graph* g, const pgsgd_params* p, uint64_t n_pairs, const float* coords,
+                            const float* grad, uint32_t* blocks) {
+  TileLaunch T{g->d_tile_seg, g->d_tile_off, g->d_tile_base, g->n_tiles, 1, kTileFwd, 0, g->d_tile_queue, nullptr};
   const uint32_t cap = tile_blocks(grad ? kTileBwd64 : kTileFwd) * (uint32_t)g->n_cu;
-  T.split = loss_tile_split(g->n_tiles, cap, n_pairs, grad);
+  T.split = loss_tile_split(g->n_tiles, cap, n_pairs, grad != nullptr);
   const bool stage = n_pairs >= 512ull * std::max(1u, g->n_tiles) * T.split;
   auto take = [&](TileForm form) {
     const uint32_t n = loss_tile_entries(p->zipf_window, form, g->lds_limit);
@@ -1706,6 +1714,10 @@ TileLaunch loss_tile_launch(const pgsgd_graph* g, const pgsgd_params* p, uint64_
     (void)((stage && take(kTileBwd64Staged)) || take(kTileBwd64) || take(kTileBwd32));
   else if (stage)
     (void)take(kTileFwdStaged);
+  const uint64_t n = 4ull * g->n_nodes;
+  const bool apart = !grad || std::less_equal<const float*>()(coords + n, grad) ||
+                     std::less_equal<const float*>()(grad + n, coords);
+  if (!g->d_inv && apart && tile_staged(T.form) == stage) T.planes = coords;
   *blocks = (uint32_t)std::max<uint64_t>(1, std::min<uint64_t>((uint64_t)g->n_tiles * T.split, cap));
   return T;
 }
@@ -1960,7 +1972,7 @@ pgsgd_status pgsgd_stress_forward(pgsgd_graph* g, const pgsgd_params* p, const f
   P.word2 = step;
   P.count = g->S ? n_pairs : 0;
   P.work = g->d_work;
-  auto copy_in = [&](uint32_t* zero) { return launch_to_work(coords, g->d_work, g->n_nodes, g->d_inv, s, zero); };
+  auto copy_in = [&] { return launch_to_work(coords, g->d_work, g->n_nodes, g->d_inv, s); };
   uint32_t parts = kStressBlocks;
   if (P.count && resolve_schedule(p) == PGSGD_SCHEDULE_WINDOWED) {
     SpsWinLaunch W;
@@ -1968,15 +1980,15 @@ pgsgd_status pgsgd_stress_forward(pgsgd_graph* g, const pgsgd_params* p, const f
     if ((st = loss_win_prepare(g, p, P, n_pairs, s, &W, tiles))) return st;
     if (tiles) {
       if ((st = ensure_loss_tiles(g, s))) return st;
-      HIP_TRY(copy_in(g->d_tile_queue));
-      const TileLaunch T = loss_tile_launch(g, p, n_pairs, false, &parts);
+      const TileLaunch T = loss_tile_launch(g, p, n_pairs, coords, nullptr, &parts);
+      if (!T.planes) HIP_TRY(copy_in());
       HIP_TRY(launch_loss_tile(W, T, nullptr, nullptr, nullptr, g->d_part_f, g->d_part_n, parts, s));
     } else {
-      HIP_TRY(copy_in(nullptr));
+      HIP_TRY(copy_in());
       HIP_TRY(launch_loss_win_fwd(W, g->d_part_f, g->d_part_n, kStressBlocks, s));
     }
   } else {
-    if (P.count) HIP_TRY(copy_in(nullptr));
+    if (P.count) HIP_TRY(copy_in());
     HIP_TRY(launch_stress_fwd(P, g->d_part_f, g->d_part_n, s));
   }
   HIP_TRY(launch_reduce_parts(g->d_part_f, g->d_part_n, parts, nullptr, nullptr, loss_dev, n_valid_dev, s));
@@ -2002,7 +2014,7 @@ pgsgd_status pgsgd_stress_backward(pgsgd_graph* g, const pgsgd_params* p, const 
   P.word2 = step;
   P.count = n_pairs;
   P.work = g->d_work;
-  auto copy_in = [&](uint32_t* zero) { return launch_to_work(coords, g->d_work, g->n_nodes, g->d_inv, s, zero); };
+  auto copy_in = [&] { return launch_to_work(coords, g->d_work, g->n_nodes, g->d_inv, s); };
   if (resolve_schedule(p) == PGSGD_SCHEDULE_WINDOWED) {
     SpsWinLaunch W;
     // by tiles when their LDS image fits a block (it does for every window W up to ~10^4)
@@ -2010,18 +2022,18 @@ pgsgd_status pgsgd_stress_backward(pgsgd_graph* g, const pgsgd_params* p, const 
     if ((st = loss_win_prepare(g, p, P, n_pairs, s, &W, tiles))) return st;
     if (tiles) {
       if ((st = ensure_loss_tiles(g, s))) return st;
-      HIP_TRY(copy_in(g->d_tile_queue));
       if (g->n_tiles) {
         uint32_t blocks = 0;
-        const TileLaunch T = loss_tile_launch(g, p, n_pairs, true, &blocks);
+        const TileLaunch T = loss_tile_launch(g, p, n_pairs, coords, grad_coords, &blocks);
+        if (!T.planes) HIP_TRY(copy_in());
         HIP_TRY(launch_loss_tile(W, T, grad_out_dev, n_valid_dev, grad_coords, nullptr, nullptr, blocks, s));
       }
     } else {
-      HIP_TRY(copy_in(nullptr));
+      HIP_TRY(copy_in());
       HIP_TRY(launch_loss_win_bwd(W, grad_out_dev, n_valid_dev, grad_coords, kStressBlocks, s));
     }
   } else {
-    HIP_TRY(copy_in(nullptr));
+    HIP_TRY(copy_in());
     HIP_TRY(launch_stress_bwd(P, grad_out_dev, n_valid_dev, grad_coords, s));
   }
   return ok();

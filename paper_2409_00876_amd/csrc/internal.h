@@ -55,9 +55,7 @@ hipError_t launch_apply_terms(const StepRec* rec, float2* work, float eta, const
 // boundary layout [2][n][2] (caller's node ids) <-> interleaved working copy
 // [n][2](x, y) (device node ids); inv[m] = caller id of device node m, or
 // NULL when the two orders are the same
-// (zero, when given, is set to 0: the work counter of the kernel that follows)
-hipError_t launch_to_work(const float* coords, float2* work, uint64_t n_nodes, const uint32_t* inv, hipStream_t s,
-                          uint32_t* zero = nullptr);
+hipError_t launch_to_work(const float* coords, float2* work, uint64_t n_nodes, const uint32_t* inv, hipStream_t s);
 hipError_t launch_to_work_pair(const float* a, const float* b, float2* work, float2* work2, uint64_t n_nodes,
                                const uint32_t* inv, hipStream_t s);
 hipError_t launch_from_work(const float2* work, float* coords, uint64_t n_nodes, const uint32_t* inv, hipStream_t s);

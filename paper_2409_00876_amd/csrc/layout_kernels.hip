@@ -180,9 +180,7 @@ __global__ __launch_bounds__(256) void k_apply_terms(const StepRec* __restrict__
 // Working copy <-> boundary layout.  Thread k handles endpoint k = 2m + e of
 // device node m; with a renumbered graph its caller id is inv[m].
 __global__ __launch_bounds__(256) void k_to_work(const float* __restrict__ coords, float2* __restrict__ work,
-                                                 uint64_t n2, const uint32_t* __restrict__ inv,
-                                                 uint32_t* __restrict__ zero) {
-  if (zero && blockIdx.x == 0 && threadIdx.x == 0) *zero = 0;
+                                                 uint64_t n2, const uint32_t* __restrict__ inv) {
   const uint64_t stride = (uint64_t)gridDim.x * blockDim.x;
   for (uint64_t k = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; k < n2; k += stride) {
     const uint64_t c = inv ? 2ull * inv[k >> 1] + (k & 1) : k;
@@ -244,10 +242,9 @@ hipError_t launch_apply_terms(const StepRec* rec, float2* work, float eta, const
   return hipGetLastError();
 }
 
-hipError_t launch_to_work(const float* coords, float2* work, uint64_t n_nodes, const uint32_t* inv, hipStream_t s,
-                          uint32_t* zero) {
+hipError_t launch_to_work(const float* coords, float2* work, uint64_t n_nodes, const uint32_t* inv, hipStream_t s) {
   hipLaunchKernelGGL(k_to_work, dim3(elementwise_grid(2 * n_nodes)), dim3(256), 0, s, coords, work, 2 * n_nodes,
-                     inv, zero);
+                     inv);
   return hipGetLastError();
 }
 

@@ -106,8 +106,7 @@ hipError_t launch_loss_win_bwd(const SpsWinLaunch& W, const float* grad_out, con
 // base[t] on, and keeps the endpoints of up to kTileRange ids from base[t] on in
 // LDS: their coordinates, and in the adjoint an image of their gradient, flushed
 // with one atomic add per touched entry; other endpoints are read and added
-// directly.  Block b starts with unit b and takes the others from *queue (zero
-// at launch).  The pairs are the window-major loss pairs of W, the same slots as
+// directly.  Block b starts with unit b and takes the others from *queue.  The pairs are the window-major loss pairs of W, the same slots as
 // launch_loss_win_bwd.
 //
 // A segment's steps climb through up to ~2,000 ids, so what lies above the range
@@ -120,6 +119,7 @@ constexpr uint32_t kTileRange = 4096;
 constexpr uint32_t kTileMaxSeg = 256;    // a segment's number in its tile is a byte of k_loss_tile's guide
 constexpr uint32_t kTileGuide = 1024;
 constexpr uint32_t kTileThreads = 1024;
+constexpr uint32_t kTileDone = 32;
 // The forms of k_loss_tile (see there).
 enum TileForm { kTileFwd, kTileFwdStaged, kTileBwd32, kTileBwd64, kTileBwd64Staged };
 constexpr bool tile_grad(TileForm f) { return f != kTileFwd && f != kTileFwdStaged; }
@@ -135,7 +135,8 @@ struct TileLaunch {
   uint32_t split;  // parts of a tile's pairs, a unit of work each
   TileForm form;
   uint32_t entries;  // loss_tile_entries
-  uint32_t* queue;
+  uint32_t* queue;   // [0] the next unit, [kTileDone] the blocks that have taken their last; both 0 between launches
+  const float* planes;  // the caller's coordinates, read in place; NULL: the working copy
 };
 // Parts of a tile.  A gradient unit zeroes and flushes the tile's whole image,
 // so its tiles stay whole while they fill the blocks; below that (and in the

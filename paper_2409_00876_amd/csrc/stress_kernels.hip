@@ -985,6 +985,8 @@ __global__ __launch_bounds__(kTileThreads, tile_blocks(kForm) * 4) void k_loss_t
     unsafeAtomicAdd(&GX[a], gx);
     unsafeAtomicAdd(&GY[a], gy);
   };
+  const float* __restrict__ px = T.planes;
+  const float* __restrict__ py = T.planes + 2ull * P.n_nodes;
   const uint32_t n_units = T.n_tiles * T.split;
   uint32_t unit = blockIdx.x;  // the first one; the others from the queue
   while (unit < n_units) {
@@ -1000,7 +1002,14 @@ __global__ __launch_bounds__(kTileThreads, tile_blocks(kForm) * 4) void k_loss_t
     using Node = float __attribute__((ext_vector_type(4)));  // float4 arrays go to scratch
     Node node[kLoads];
     const uint32_t nodes = (uint32_t)min((uint64_t)(n_acc / 2), P.n_nodes - base);
-    if (kStage) {
+    if (kStage && px) {
+#pragma unroll
+      for (uint32_t q = 0; q < kLoads; ++q) {
+        const uint32_t e = threadIdx.x + q * kTileThreads;
+        const uint64_t k = 2 * (base + e);
+        if (e < nodes) node[q] = Node{px[k], py[k], px[k + 1], py[k + 1]};
+      }
+    } else if (kStage) {
       const Node* __restrict__ work = reinterpret_cast<const Node*>(P.work) + base;
 #pragma unroll
       for (uint32_t q = 0; q < kLoads; ++q) {
@@ -1010,7 +1019,7 @@ __global__ __launch_bounds__(kTileThreads, tile_blocks(kForm) * 4) void k_loss_t
     }
     auto coords = [&](uint64_t a) -> float2 {
       const uint64_t e = a - 2 * base;  // wraps to huge below the base
-      if (!kStage || e >= n_acc) return P.work[a];
+      if (!kStage || e >= n_acc) return px ? make_float2(px[a], py[a]) : P.work[a];
       const Pair2 v = ((const __attribute__((address_space(3))) Pair2*)xy)[e];  // or both became flat loads
       return make_float2(v.x, v.y);
     };
@@ -1109,6 +1118,11 @@ __global__ __launch_bounds__(kTileThreads, tile_blocks(kForm) * 4) void k_loss_t
     if (!more) break;
     __syncthreads();  // the tile's tables and image are free again
     unit = uniform_u32(s_unit);
+  }
+  // the block that is the last to leave the queue leaves it as it found it
+  if (n_units > gridDim.x && threadIdx.x == 0 && atomicAdd(T.queue + kTileDone, 1u) == gridDim.x - 1) {
+    T.queue[0] = 0;
+    T.queue[kTileDone] = 0;
   }
   if (!kGrad) {
     sum = block_sum(sum, red_f);

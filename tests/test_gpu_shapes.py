@@ -172,3 +172,26 @@ def test_two_layouts_side_by_side(P, backbone, renumber, pairs):  # noqa: F811
         assert abs(r[k] - ref[k]) <= 1e-9 * abs(ref[k]), k
     one = P.path_stress(g, ta, 7, seed=5, pairs=pairs)  # the copy of one layout afterwards
     assert one["n_valid"] == r["n_valid"] and abs(one["mean"] - ref["mean_a"]) <= 1e-9 * abs(ref["mean_a"])
+
+
+# coordinates read in place at an odd float offset, and calls one after another that share the work queue (several
+# tiles a block, then few); the same pairs of the same floats: equal up to the order of the sums
+@pytest.mark.parametrize("backbone,pairs", [(300011, 300000), (9000, 200)])
+def test_loss_reads_coordinates_in_place(P, backbone, pairs):  # noqa: F811
+    import torch
+    sg = synth.generate(backbone, 0.2, 4, 29)
+    og, g = O.Graph.from_synth(sg), P.Graph.from_synth(sg)
+    rng = np.random.default_rng(pairs)
+    c = (O.init_coords(og) + rng.normal(scale=5.0, size=4 * sg.n_nodes)).astype(np.float32)
+    t = torch.empty(c.size + 1, device="cuda")[1:]
+    t.copy_(torch.from_numpy(c))
+    one = torch.ones(1, device="cuda")
+    for step in (0, 0, 1):
+        ol, ov, ograd = O.stress_loss_grad_windowed(og, c, pairs, seed=11, step=step, window=1000)
+        loss, nv = P.stress_forward(g, t, pairs, step, seed=11)
+        assert int(nv.item()) == ov and abs(loss.item() - ol) <= 1e-5 * abs(ol)
+        for _ in range(2):
+            grad = torch.zeros_like(t)
+            P.stress_backward(g, t, pairs, step, one, nv, grad, seed=11)
+            err = np.abs(grad.cpu().numpy().astype(np.float64) - ograd)
+            assert np.all(err <= 1e-4 * np.abs(ograd) + 1e-6 * np.abs(ograd).max())
