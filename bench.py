@@ -87,7 +87,8 @@ def _read_counters(path):
     rows = []
     with open(path) as f:
         for r in csv.DictReader(f):
-            rows.append((r["Kernel_Name"], r["Counter_Name"], float(r["Counter_Value"])))
+            # a template's name begins with its return type
+            rows.append((r["Kernel_Name"].removeprefix("void "), r["Counter_Name"], float(r["Counter_Value"])))
     return rows
 
 
@@ -123,23 +124,24 @@ def summarize_counters(trace_dir: str, fetch_csv: str, write_csv: str, tcc_csv: 
     write_b = [v * 1024 * w_factor for v in w_lay]
     n_iter_profiled = 2  # --profile runs iterations 0 and 15
     launches = len(fetch_b) // n_iter_profiled
-    stats = None
+    calls, total_ns = 0, 0.0  # over the kernel's forms
     for name in os.listdir(trace_dir):
         if name.endswith("kernel_stats.csv"):
             with open(os.path.join(trace_dir, name)) as f:
                 for r in csv.DictReader(f):
-                    if r["Name"].startswith(dom):
-                        stats = r
+                    if r["Name"].removeprefix("void ").startswith(dom):
+                        calls += int(r["Calls"])
+                        total_ns += float(r["TotalDurationNs"])
     import synth
     sg = synth.config_graph("chromosome")
     T = 10 * sg.n_steps
-    avg_ns = float(stats["AverageNs"])
+    avg_ns = total_ns / calls
     traffic = (sum(fetch_b) + sum(write_b)) / len(fetch_b)
     it_traffic = (f_it * 1024 * f_factor + w_it * 1024 * w_factor) / n_iter_profiled
     rec = {"kernel": dom.split("::")[1], "workload": "chromosome", "terms_per_launch": T / launches,
            "launches_per_iteration": launches, "terms_per_iteration": T,
            "kernel_source_sha": kernel_source_hash(kernel), "command": command,
-           "trace_avg_launch_ms": avg_ns / 1e6, "trace_calls": int(stats["Calls"]),
+           "trace_avg_launch_ms": avg_ns / 1e6, "trace_calls": calls,
            "fetch_calibration_factor": f_factor, "write_calibration_factor": w_factor,
            "fetch_bytes_per_launch": sum(fetch_b) / len(fetch_b), "write_bytes_per_launch": sum(write_b) / len(write_b),
            "traffic_bytes_per_launch": traffic, "traffic_bytes_per_term": traffic / (T / launches),
