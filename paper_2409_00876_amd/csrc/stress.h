@@ -54,6 +54,18 @@ constexpr uint32_t kStressThreads = 256;
 // doubles of partials that a graph holds.
 constexpr uint32_t kSpsBlocks = 1024, kSpsThreads = 512;
 constexpr uint32_t kSpsPairBlocks = 512, kSpsPairThreads = 1024;
+// Chunks of a step's m pairs so that a small graph still has a pair for every
+// thread of the grid: as many as it takes (S >= 1, m >= 1), no more threads
+// than the grid has; chunk c holds the pairs [c * per, min(m, (c + 1) * per)).
+// In 64 bits: m may be any 32-bit number.
+struct SpsSplit {
+  uint32_t per, chunks;
+};
+inline SpsSplit sps_split(uint64_t S, uint32_t m, uint64_t threads) {
+  const uint64_t want = S >= threads ? 1 : std::max<uint64_t>(1, std::min<uint64_t>(m, threads / S));
+  const uint64_t per = (m + want - 1) / want;
+  return {(uint32_t)per, (uint32_t)((m + per - 1) / per)};
+}
 static_assert(4 * kSpsBlocks <= 3 * kStressBlocks && 10 * kSpsPairBlocks <= 3 * kStressBlocks, "partials");
 // The sums of one evaluation on the host: hi + lo of the sums of a, a^2 and, for
 // two layouts, b, b^2, a b; the valid and skipped pairs; the outliers found.

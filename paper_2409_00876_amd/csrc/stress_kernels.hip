@@ -282,7 +282,7 @@ __global__ __launch_bounds__(kPair ? 1024 : 512) void k_sps(StressLaunch P, int 
     const uint64_t s = u - (uint64_t)chunk * P.S;
     const uint32_t p = find_path(off, P.path_top, s);
     const uint64_t start = off[p], len = off[p + 1] - start;
-    const uint32_t k_end = min(P.m, (chunk + 1) * per);
+    const uint32_t k_end = (uint32_t)min((uint64_t)P.m, ((uint64_t)chunk + 1) * per);
     for (uint32_t k = chunk * per; k < k_end; ++k) {
       const uint64_t q = (uint64_t)P.m * s + k;
       const Rand4 r = philox10((uint32_t)q, (uint32_t)(q >> 32), 0u, P.c3, P.k0, P.k1);
@@ -1222,20 +1222,13 @@ static uint32_t grid_for(uint64_t n, uint32_t cap) {
   return (uint32_t)(b < 1 ? 1 : (b > cap ? cap : b));
 }
 
-// Chunks of a step's m pairs so that a small graph still has a pair for every
-// thread of the grid: as many as it takes, no more threads than the grid has.
-static uint32_t sps_chunks(uint64_t S, uint32_t m, uint64_t threads) {
-  if (S >= threads) return 1;
-  return (uint32_t)std::max<uint64_t>(1, std::min<uint64_t>(m, threads / S));
-}
-
 hipError_t launch_sps(const StressLaunch& P, int mode, double* part_f, uint64_t* part_n, uint64_t* part_skip,
                       uint32_t* n_parts, hipStream_t s) {
   const size_t lds = std::max(kSpsLds, mode == 1 ? loss_lds_bytes(P) : (size_t)P.path_slots * 8);
   const uint32_t threads = P.work2 ? kSpsPairThreads : kSpsThreads;
   const uint32_t cap = P.work2 ? kSpsPairBlocks : kSpsBlocks;
-  const uint32_t want = sps_chunks(P.S, P.m, (uint64_t)cap * threads);
-  const uint32_t per = (P.m + want - 1) / want, chunks = (P.m + per - 1) / per;
+  const SpsSplit split = sps_split(P.S, P.m, (uint64_t)cap * threads);
+  const uint32_t per = split.per, chunks = split.chunks;
   const uint64_t blocks = (P.S * chunks + threads - 1) / threads;
   *n_parts = (uint32_t)std::min<uint64_t>(cap, std::max<uint64_t>(1, blocks));
   if (P.work2)
