@@ -742,24 +742,6 @@ namespace {
 // params.max_inflight_waves (automatic: see auto_inflight_waves) and by the
 // number of 64-term groups.  Large grids use 4-wave blocks; small caps use
 // one-wave blocks so the number of concurrent waves is exactly the cap.
-// Automatic cap.  One wave keeps the sampled path stress of the sequential loop
-// on a 2.6K-node graph and two waves raise it by 12%, but what counts there are
-// the XCDs: each works on its own L2's copy of the coordinates until the
-// launch ends.  On 51K nodes the stress is 1.0 / 1.23 / 1.33 / 1.45 of one
-// wave's on 1 / 2 / 4 / 8 XCDs, and then flat from 8 to 1,024 waves while the
-// time falls as 1 / waves (250 ms at 25 waves, 15 ms at 512).  So below `many`
-// nodes the cap is n_nodes / 2048 waves, one or two per XCD, whose runs repeat
-// to about 3e-4 of the coordinates (one wave: exactly) where more waves would
-// move the layout by 1e-3; from there on n_nodes / 64 waves up to 1,024, and
-// where that is more n_nodes / 512 up to `most`, and n_nodes / 2048.
-constexpr uint32_t kManyWaveNodes = 32768;
-constexpr uint32_t kManyWaveNodesPlain = 16384;  // plain order: runs of 8 waves already differ by 6e-4 to 9e-4
-uint64_t auto_inflight_waves(const pgsgd_graph* g, uint32_t many, uint64_t most) {
-  const uint64_t n = g->n_nodes;
-  if (n < many) return std::max<uint64_t>(1, n / 2048);
-  return std::max({n / 2048, std::min<uint64_t>(n / 512, most), std::min<uint64_t>(n / 64, 1024)});
-}
-
 pgsgd_status layout_grid(pgsgd_graph* g, const pgsgd_params* p, size_t lds, uint64_t n_groups, uint32_t* blocks,
                          uint32_t* threads) {
   int bpc = 1;
@@ -767,7 +749,7 @@ pgsgd_status layout_grid(pgsgd_graph* g, const pgsgd_params* p, size_t lds, uint
   if (st) return st;
   uint64_t waves = (uint64_t)g->n_cu * bpc * 4;
   const uint64_t cap =
-      p->max_inflight_waves ? p->max_inflight_waves : auto_inflight_waves(g, kManyWaveNodesPlain, 0);
+      p->max_inflight_waves ? p->max_inflight_waves : auto_inflight_waves(g->n_nodes, kManyWaveNodesPlain, 0);
   waves = std::min(waves, cap);
   waves = std::min(waves, std::max<uint64_t>(1, n_groups));
   if (waves >= 4ull * g->n_cu) {
@@ -1019,92 +1001,17 @@ pgsgd_status ensure_loss_tiles(pgsgd_graph* g, hipStream_t s) {
   return PGSGD_OK;
 }
 
-// Iterations of a layout by their launch shape: the first eighth, whose steps
-// are full corrections (mu = 1 for every pair), the rest of the iterations
-// with uniform partners, and the all-cooling ones (t >= n_iters / 2).
-enum LocalPhase : uint32_t { kPhaseEarly = 0, kPhaseMixed, kPhaseCooling, kPhases };
-
-LocalPhase local_phase(uint32_t iter, uint32_t n_iters) {
-  return iter >= n_iters / 2 ? kPhaseCooling : iter < n_iters / 8 ? kPhaseEarly : kPhaseMixed;
-}
-
-// Automatic wave cap of the windowed schedule (see kLocalNodesPerWave; the
-// all-cooling iterations use kLocalNodesPerWaveCooling).  A lost update of the
-// first iterations moves a node by a whole correction, and the next ones do
-// not bring the layout's place on the axes back: with 1,024 waves in them a
-// layout of 148K nodes lands 450 nt further along x than with 72 (6.5e-4 of
-// the coordinates, runs differ by 3.6e-4), with 512 or fewer it does not.
-// Graphs of a batch run `scale` times n_nodes / 2048 waves in every iteration
-// (scale = 0: no batch).  Several of them share each L2, and what one evicts of
-// another's coordinates the other XCDs then see, so a graph's place depends on
-// the pace of its neighbours: all must gain alike, and not by much.  Six graphs
-// of 60K to 351K nodes took 1,080 ms at scale 1 and 475 / 270 / 195 at 2 / 4 /
-// 8; graph by graph, layouts of scale 1 / 2 / 4 / 8 lie 1.1 / 1.1 / 1.3 / 1.5
-// times as far from a set of scale 1 as its own lie from each other (means over
-// 24).  With the caps of single layouts (174 ms) the smallest graph lay five
-// times as far.
-constexpr uint32_t kBatchScale = 2;
 uint32_t batch_scale(pgsgd_graph* const* graphs, uint32_t n) {
   for (uint32_t k = 0; k < n; ++k)
     if (graphs[k]->n_nodes < kManyWaveNodes) return 1;  // such a graph keeps its waves, so all do
   return kBatchScale;
 }
 
-uint64_t auto_local_waves(const pgsgd_graph* g, LocalPhase phase, uint32_t scale) {
-  const uint32_t sh = window_shift(g->S);
-  const double nodes_w = std::min<double>((double)g->n_nodes,
-                                          std::ldexp(1.0, (int)sh) * (double)g->n_nodes * g->n_paths / (double)g->S);
-  const uint64_t per = phase == kPhaseCooling ? kLocalNodesPerWaveCooling : kLocalNodesPerWave;
-  uint64_t w = (uint64_t)(nodes_w / (double)per);
-  if (scale) {
-    w = std::min<uint64_t>(w, (uint64_t)scale * std::max(1u, g->n_nodes / 2048));
-  } else {
-    w = std::min<uint64_t>(w, auto_inflight_waves(g, kManyWaveNodes, kLocalMostWaves));
-    if (phase == kPhaseEarly) w = std::min(w, std::max<uint64_t>(g->n_nodes / 2048, kLocalEarlyWaves));
-  }
-  return std::max<uint64_t>(1, w);
-}
-
-// Grids of k_layout_local: the in-flight wave cap (params.max_inflight_waves,
-// automatic: auto_local_waves) and occupancy give the waves; 256-thread
-// blocks in a multiple of 8 (one share per XCD), or 64-thread blocks below 32
-// waves.  Automatic caps of graphs of fewer than 65,536 nodes keep the
-// proportion between the XCDs that n_nodes / 2048 one-wave blocks have (21
-// blocks: three on XCDs 0..4, two on 5..7), so that the same XCDs end their
-// shares last: an XCD writes its copy of the coordinates back when it is
-// done, and the last one's stand.  With equal XCDs a layout of 44.5K nodes lay
-// 2e-3 to 3e-3 away (runs differ by 3e-4), with the proportion kept 6e-4.
-struct LocalGrids {
-  uint32_t blocks[kPhases], threads[kPhases];
-  uint32_t quota_hi[kPhases], quota_lo[kPhases], hi_xcds[kPhases];  // blocks of an XCD's share that take work
-  bool ahead[kPhases];  // draw the next item ahead also beside uniform partners (see kLocalAheadWaves)
-};
-
-pgsgd_status local_grids(pgsgd_graph* g, const pgsgd_params* p, size_t lds, LocalGrids* out, uint32_t scale = 0) {
+pgsgd_status plan_grids(pgsgd_graph* g, const pgsgd_params* p, size_t lds, LocalGrids* out, uint32_t scale = 0) {
   int nb = 0;
   HIP_TRY(hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, layout_local_kernel(), 256, lds));
-  const uint32_t base = g->n_nodes / 2048;
-  for (uint32_t ph = 0; ph < kPhases; ++ph) {
-    uint64_t waves = (uint64_t)g->n_cu * (uint64_t)std::max(nb, 1) * 4;
-    const uint64_t cap = p->max_inflight_waves ? p->max_inflight_waves : auto_local_waves(g, (LocalPhase)ph, scale);
-    waves = std::max<uint64_t>(1, std::min(waves, cap));
-    out->ahead[ph] =
-        !p->max_inflight_waves && scale != 1 && g->n_nodes >= kManyWaveNodes && waves <= kLocalAheadWaves;
-    out->quota_hi[ph] = out->quota_lo[ph] = 0xFFFFFFFFu;
-    out->hi_xcds[ph] = kXcds;
-    const bool wide = waves >= 4ull * kXcds;
-    if (!p->max_inflight_waves && wide && base < 4 * kXcds) {
-      const uint32_t k = std::max<uint32_t>(1, (uint32_t)waves / (4 * base));  // 4-wave blocks for one of base
-      out->hi_xcds[ph] = base % kXcds;
-      out->quota_lo[ph] = base / kXcds * k;
-      out->quota_hi[ph] = out->quota_lo[ph] + k;
-      out->threads[ph] = 256;
-      out->blocks[ph] = kXcds * (base % kXcds ? out->quota_hi[ph] : out->quota_lo[ph]);
-      continue;
-    }
-    out->threads[ph] = wide ? 256 : 64;
-    out->blocks[ph] = (uint32_t)(wide ? (waves / 4) / kXcds * kXcds : waves);
-  }
+  *out = local_grids(g->n_nodes, g->n_paths, g->S, p->max_inflight_waves,
+                     (uint64_t)g->n_cu * (uint64_t)std::max(nb, 1) * 4, scale);
   return PGSGD_OK;
 }
 
@@ -1151,7 +1058,7 @@ pgsgd_status local_plan(pgsgd_graph* g, const pgsgd_params* p, size_t lds, const
                         LocalLaunch* W, LocalGrids* grids, uint32_t scale = 0) {
   pgsgd_status st;
   if ((st = ensure_local(g, kLocalStreams, s))) return st;
-  if ((st = local_grids(g, p, lds, grids, scale))) return st;
+  if ((st = plan_grids(g, p, lds, grids, scale))) return st;
   *W = LocalLaunch{};
   W->L = L;
   W->n_win = g->loc_nwin;
@@ -1201,7 +1108,7 @@ pgsgd_status local_plan_scratch(pgsgd_graph* g, const pgsgd_params* p, size_t ld
                                 LocalGrids* grids) {
   pgsgd_status st;
   if ((st = local_host_tables(g, kLocalStreams))) return st;
-  if ((st = local_grids(g, p, lds, grids))) return st;
+  if ((st = plan_grids(g, p, lds, grids))) return st;
   const uint32_t nwin = (uint32_t)g->h_lwpath.size();
   const uint32_t runs = kXcds * kLocalStreams;
   const ScratchCarve c = carve_scratch(nwin, runs, g->h_loc_xstride);

@@ -5,6 +5,9 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <algorithm>
+#include <cmath>
+
 #include "internal.h"
 
 namespace pgsgd {
@@ -52,6 +55,109 @@ inline uint32_t window_shift(uint64_t S) {
   while (sh > 6 && n(sh) < kLocalMinWindows) --sh;
   while (n(sh) > kLocalMaxWindows) ++sh;
   return sh;
+}
+
+// Automatic cap.  One wave keeps the sampled path stress of the sequential loop
+// on a 2.6K-node graph and two waves raise it by 12%, but what counts there are
+// the XCDs: each works on its own L2's copy of the coordinates until the
+// launch ends.  On 51K nodes the stress is 1.0 / 1.23 / 1.33 / 1.45 of one
+// wave's on 1 / 2 / 4 / 8 XCDs, and then flat from 8 to 1,024 waves while the
+// time falls as 1 / waves (250 ms at 25 waves, 15 ms at 512).  So below `many`
+// nodes the cap is n_nodes / 2048 waves, one or two per XCD, whose runs repeat
+// to about 3e-4 of the coordinates (one wave: exactly) where more waves would
+// move the layout by 1e-3; from there on n_nodes / 64 waves up to 1,024, and
+// where that is more n_nodes / 512 up to `most`, and n_nodes / 2048.
+constexpr uint32_t kManyWaveNodes = 32768;
+constexpr uint32_t kManyWaveNodesPlain = 16384;  // plain order: runs of 8 waves already differ by 6e-4 to 9e-4
+inline uint64_t auto_inflight_waves(uint64_t n, uint32_t many, uint64_t most) {
+  if (n < many) return std::max<uint64_t>(1, n / 2048);
+  return std::max({n / 2048, std::min<uint64_t>(n / 512, most), std::min<uint64_t>(n / 64, 1024)});
+}
+
+// Iterations of a layout by their launch shape: the first eighth, whose steps
+// are full corrections (mu = 1 for every pair), the rest of the iterations
+// with uniform partners, and the all-cooling ones (t >= n_iters / 2).
+enum LocalPhase : uint32_t { kPhaseEarly = 0, kPhaseMixed, kPhaseCooling, kPhases };
+
+inline LocalPhase local_phase(uint32_t iter, uint32_t n_iters) {
+  return iter >= n_iters / 2 ? kPhaseCooling : iter < n_iters / 8 ? kPhaseEarly : kPhaseMixed;
+}
+
+// Automatic wave cap of the windowed schedule (see kLocalNodesPerWave; the
+// all-cooling iterations use kLocalNodesPerWaveCooling).  A lost update of the
+// first iterations moves a node by a whole correction, and the next ones do
+// not bring the layout's place on the axes back: with 1,024 waves in them a
+// layout of 148K nodes lands 450 nt further along x than with 72 (6.5e-4 of
+// the coordinates, runs differ by 3.6e-4), with 512 or fewer it does not.
+// Graphs of a batch run `scale` times n_nodes / 2048 waves in every iteration
+// (scale = 0: no batch).  Several of them share each L2, and what one evicts of
+// another's coordinates the other XCDs then see, so a graph's place depends on
+// the pace of its neighbours: all must gain alike, and not by much.  Six graphs
+// of 60K to 351K nodes took 1,080 ms at scale 1 and 475 / 270 / 195 at 2 / 4 /
+// 8; graph by graph, layouts of scale 1 / 2 / 4 / 8 lie 1.1 / 1.1 / 1.3 / 1.5
+// times as far from a set of scale 1 as its own lie from each other (means over
+// 24).  With the caps of single layouts (174 ms) the smallest graph lay five
+// times as far.
+constexpr uint32_t kBatchScale = 2;
+
+inline uint64_t auto_local_waves(uint32_t n_nodes, uint32_t n_paths, uint64_t S, LocalPhase phase, uint32_t scale) {
+  const uint32_t sh = window_shift(S);
+  const double nodes_w =
+      std::min<double>((double)n_nodes, std::ldexp(1.0, (int)sh) * (double)n_nodes * n_paths / (double)S);
+  const uint64_t per = phase == kPhaseCooling ? kLocalNodesPerWaveCooling : kLocalNodesPerWave;
+  uint64_t w = (uint64_t)(nodes_w / (double)per);
+  if (scale) {
+    w = std::min<uint64_t>(w, (uint64_t)scale * std::max(1u, n_nodes / 2048));
+  } else {
+    w = std::min<uint64_t>(w, auto_inflight_waves(n_nodes, kManyWaveNodes, kLocalMostWaves));
+    if (phase == kPhaseEarly) w = std::min(w, std::max<uint64_t>(n_nodes / 2048, kLocalEarlyWaves));
+  }
+  return std::max<uint64_t>(1, w);
+}
+
+// Grids of k_layout_local: the in-flight wave cap (params.max_inflight_waves,
+// automatic: auto_local_waves) and the waves that the device holds give the
+// waves, which no phase exceeds; 256-thread blocks in a multiple of 8 (one
+// share per XCD), or 64-thread blocks below 32 waves.  Automatic caps of graphs of fewer than 65,536 nodes keep the
+// proportion between the XCDs that n_nodes / 2048 one-wave blocks have (21
+// blocks: three on XCDs 0..4, two on 5..7), so that the same XCDs end their
+// shares last: an XCD writes its copy of the coordinates back when it is
+// done, and the last one's stand.  With equal XCDs a layout of 44.5K nodes lay
+// 2e-3 to 3e-3 away (runs differ by 3e-4), with the proportion kept 6e-4.  Caps
+// below four waves for each of those blocks (few paths, or paths that revisit
+// nodes; batches) keep it with 64-thread blocks.
+struct LocalGrids {
+  uint32_t blocks[kPhases], threads[kPhases];
+  uint32_t quota_hi[kPhases], quota_lo[kPhases], hi_xcds[kPhases];  // blocks of an XCD's share that take work
+  bool ahead[kPhases];  // draw the next item ahead also beside uniform partners (see kLocalAheadWaves)
+};
+
+inline LocalGrids local_grids(uint32_t n_nodes, uint32_t n_paths, uint64_t S, uint64_t max_inflight_waves,
+                              uint64_t resident_waves, uint32_t scale) {
+  LocalGrids out{};
+  const uint32_t base = n_nodes / 2048;
+  for (uint32_t ph = 0; ph < kPhases; ++ph) {
+    const uint64_t cap =
+        max_inflight_waves ? max_inflight_waves : auto_local_waves(n_nodes, n_paths, S, (LocalPhase)ph, scale);
+    const uint64_t waves = std::max<uint64_t>(1, std::min(resident_waves, cap));
+    out.ahead[ph] = !max_inflight_waves && scale != 1 && n_nodes >= kManyWaveNodes && waves <= kLocalAheadWaves;
+    out.quota_hi[ph] = out.quota_lo[ph] = 0xFFFFFFFFu;
+    out.hi_xcds[ph] = kXcds;
+    const bool wide = waves >= 4ull * kXcds;
+    if (!max_inflight_waves && wide && base < 4 * kXcds) {
+      const uint32_t block = waves >= 4ull * base ? 4 : 1;  // waves
+      const uint32_t k = (uint32_t)waves / (block * base);  // blocks for one of base
+      out.hi_xcds[ph] = base % kXcds;
+      out.quota_lo[ph] = base / kXcds * k;
+      out.quota_hi[ph] = out.quota_lo[ph] + k;
+      out.threads[ph] = 64 * block;
+      out.blocks[ph] = kXcds * (base % kXcds ? out.quota_hi[ph] : out.quota_lo[ph]);
+      continue;
+    }
+    out.threads[ph] = wide ? 256 : 64;
+    out.blocks[ph] = (uint32_t)(wide ? (waves / 4) / kXcds * kXcds : waves);
+  }
+  return out;
 }
 
 // log2 of the segment length of the loss's window-major pairs (reading R22):

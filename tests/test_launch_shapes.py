@@ -54,3 +54,50 @@ def test_sps_split_covers_every_pair_of_a_step(sps_split):
         # chunks * per reaches m, the last chunk is not empty, and chunks of a small graph fit the grid
         assert (chunks - 1) * per < m <= chunks * per, (S, m)
         assert chunks == 1 or S * chunks <= threads, (S, m)
+
+
+@pytest.fixture(scope="module")
+def local_grids(tmp_path_factory):
+    exe = _compile(tmp_path_factory, "local_grids", r"""
+#include <cstdio>
+#include "local.h"
+using namespace pgsgd;
+int main() {  // per phase: the cap and the waves that take work on each XCD
+  unsigned long long n, paths, S, inflight, resident, scale;
+  while (scanf("%llu %llu %llu %llu %llu %llu", &n, &paths, &S, &inflight, &resident, &scale) == 6) {
+    const LocalGrids G = local_grids((uint32_t)n, (uint32_t)paths, S, inflight, resident, (uint32_t)scale);
+    for (uint32_t ph = 0; ph < kPhases; ++ph) {
+      unsigned long long cap = inflight ? inflight : auto_local_waves((uint32_t)n, (uint32_t)paths, S, (LocalPhase)ph,
+                                                                     (uint32_t)scale);
+      printf("%llu", cap < resident ? cap : resident);
+      for (uint32_t x = 0; x < kXcds; ++x) {
+        uint32_t blocks = 0;
+        for (uint32_t b = x; b < G.blocks[ph]; b += kXcds)
+          blocks += b / kXcds < (x < G.hi_xcds[ph] ? G.quota_hi[ph] : G.quota_lo[ph]);
+        printf(" %u", blocks * G.threads[ph] / 64);
+      }
+      printf("\n");
+    }
+  }
+}
+""")
+    return lambda lines: _rows(exe, lines)
+
+
+def test_window_grids_stay_within_their_wave_caps(local_grids):
+    # few and many paths over the range where the XCDs share unequally and beyond; single layouts, batches, a caller's cap
+    cases = []
+    for n in (1, 2047, 4096, 20000, 32767, 32768, 33000, 40961, 49000, 50000, 60000, 65000, 65535, 65536, 300000, 10 ** 7):
+        for paths, steps in ((1, n), (1, 3 * n), (4, n), (4, 60 * n), (24, 20 * n), (90, 80 * n)):
+            for scale in (0, 1, 2):
+                cases.append((n, paths, steps, 0, 6144, scale))
+            cases.append((n, paths, steps, 37, 6144, 0))
+        cases.append((n, 24, 20 * n, 0, 100, 0))
+    got = local_grids([" ".join(map(str, c)) for c in cases])
+    assert len(got) == 3 * len(cases)
+    for k, row in enumerate(got):
+        case, cap, xcds = cases[k // 3], row[0], row[1:]
+        assert 1 <= sum(xcds) <= max(1, cap), (case, row)
+        if cap >= 32:
+            assert min(xcds) >= 1, (case, row)  # every XCD works on its own run
+            assert 2 * sum(xcds) > cap, (case, row)  # and the cap is used
