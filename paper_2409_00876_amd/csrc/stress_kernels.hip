@@ -108,10 +108,12 @@ __device__ __forceinline__ double delta_xy(float2 va, float2 vb, double& dx, dou
   return root64(dx * dx + dy * dy);
 }
 
-// scale (mag - d) / d^2 / mag, the factor of (dx, dy) in a pair's gradient.
+// scale (mag - d) / d^2 / mag, the factor of (dx, dy) in a pair's gradient;
+// taken again the general way where it is not finite (an infinite grad_out).
 __device__ __forceinline__ double gradient_factor(double scale, double mag, double d) {
 #pragma clang fp contract(off)
-  return quotient64(quotient64(scale * (mag - d), d * d), mag);
+  const double c = quotient64(quotient64(scale * (mag - d), d * d), mag);
+  return c - c == 0.0 ? c : scale * (mag - d) / (d * d) / mag;
 }
 
 // The stress of endpoints a and b of the interleaved copy (W[e] = (x, y) of endpoint e).
