@@ -101,7 +101,9 @@ typedef struct {
  * per window on first use.  If the environment variable
  * PGSGD_MAX_DEVICE_BYTES holds a positive decimal number, no graph handle may
  * hold more device memory than that: a creation that would need more fails
- * with OOM before any device work, as does any later allocation of the handle.
+ * with OOM before any device work, as does any later allocation of the handle
+ * (after the term list of one-wave layouts, see PGSGD_SCHEDULE_WINDOWED, which
+ * the handle can do without, has been given up for it).
  * Errors: INVALID_ARG (null pointer, node id >= n_nodes, length 0, offsets not
  * monotone, step_pos mismatch, n_paths = 0), RANGE (sizes above the limits,
  * a path longer than 2^62 nt), OOM, DEVICE.  Synchronous.
@@ -296,8 +298,10 @@ enum { PGSGD_FLAG_COUNT_AHEAD = 1, PGSGD_FLAG_COUNT_IN_ORDER = 2 };
  *            max(n_nodes / 2048, 512); in a batch n_nodes / 2048, or twice
  *            that if every graph has 32,768 nodes or more).  A layout of one
  *            wave takes its terms from a list of one iteration's, at most
- *            64 MB, that the graph (or the batch) keeps; it is the same
- *            layout bit for bit without it.
+ *            64 MB, that the graph (or the batch) keeps; a graph gives its
+ *            list up when another buffer of it needs the memory, and a call
+ *            under stream capture takes none.  It is the same layout bit for
+ *            bit without the list, only slower.
  *            Uniform-partner updates read the partner first and the window-
  *            local endpoint after it arrived, which keeps the window in which
  *            a concurrent update of a local node can be lost short.  Scratch: a few

@@ -255,10 +255,14 @@ uint64_t device_byte_cap() {
   return (end && *end == '\0') ? (uint64_t)x : 0;
 }
 
+// The ordered form's list is the one buffer that a graph can do without.
+void release_ordered_list(pgsgd_graph* g);
+
 template <typename T>
 pgsgd_status dev_alloc(pgsgd_graph* g, T** p, size_t count) {
   size_t bytes = sizeof(T) * (count ? count : 1);
   const uint64_t cap = device_byte_cap();
+  if (cap && g->device_bytes + bytes > cap) release_ordered_list(g);
   if (cap && g->device_bytes + bytes > cap) {
     *p = nullptr;
     return fail(PGSGD_ERR_OOM, "allocating %zu bytes would take the graph to %llu bytes, above "
@@ -266,6 +270,11 @@ pgsgd_status dev_alloc(pgsgd_graph* g, T** p, size_t count) {
                 (unsigned long long)cap);
   }
   hipError_t e = hipMalloc((void**)p, bytes);
+  if (e == hipErrorOutOfMemory && g->d_ordered) {
+    (void)hipGetLastError();
+    release_ordered_list(g);
+    e = hipMalloc((void**)p, bytes);
+  }
   if (e != hipSuccess) {
     (void)hipGetLastError();
     *p = nullptr;
@@ -292,6 +301,13 @@ void free_set(pgsgd_graph* g, std::initializer_list<void**> set) {
       (void)hipFree(*q);
       *q = nullptr;
     }
+}
+
+void release_ordered_list(pgsgd_graph* g) {
+  if (!g->d_ordered) return;
+  (void)hipDeviceSynchronize();  // layouts that read it
+  free_set(g, {(void**)&g->d_ordered});
+  g->ordered_cap = 0;
 }
 
 // Ensures the graph holds the power-law table for (theta, W) on the device
@@ -1035,14 +1051,21 @@ uint64_t ordered_terms(const LocalLaunch& W, const LocalGrids& grids) {
 }
 
 // The graph's list for the plan W, grown when needed.  Without the memory for
-// it the layout runs k_layout_local, which gives the same coordinates.  Only
-// the calls that run at once use it: a batch holds lists of its own.
-OrderedTerm* ordered_list(pgsgd_graph* g, const LocalLaunch& W, const LocalGrids& grids) {
+// it the layout runs k_layout_local, which gives the same coordinates; so does a
+// layout that is captured, since the list may be freed (to grow, or for another
+// buffer) before the capture's graph is launched.  Only the calls that run at
+// once use it: a batch holds lists of its own.
+OrderedTerm* ordered_list(pgsgd_graph* g, const LocalLaunch& W, const LocalGrids& grids, hipStream_t s) {
   const uint64_t terms = ordered_terms(W, grids);
   if (!terms) return nullptr;
+  hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
+  if (hipStreamIsCapturing(s, &capture) != hipSuccess) {  // the null stream beside a capture
+    (void)hipGetLastError();
+    return nullptr;
+  }
+  if (capture != hipStreamCaptureStatusNone) return nullptr;
   if (g->ordered_cap < terms) {
-    free_set(g, {(void**)&g->d_ordered});
-    g->ordered_cap = 0;
+    release_ordered_list(g);
     if (dev_alloc(g, &g->d_ordered, terms) != PGSGD_OK) {
       clear_error();
       return nullptr;
@@ -1074,7 +1097,6 @@ pgsgd_status local_plan(pgsgd_graph* g, const pgsgd_params* p, size_t lds, const
   W->wpath = g->d_lwpath;
   W->streams = kLocalStreams;
   W->grab = kLocalGrab;
-  W->list = scale ? nullptr : ordered_list(g, *W, *grids);
   return PGSGD_OK;
 }
 
@@ -1217,6 +1239,7 @@ pgsgd_status layout_impl(pgsgd_graph* g, const pgsgd_params* p, float* coords, f
     if ((st = local_plan_scratch(g, p, lds, L, s, scratch, scratch_bytes, &W, &grids))) return st;
   } else if (windowed) {
     if ((st = local_plan(g, p, lds, L, s, &W, &grids))) return st;
+    if (!subset) W.list = ordered_list(g, W, grids, s);  // the hooks run k_layout_local
   } else {
     if ((st = layout_grid(g, p, lds, L.n_groups, &blocks, &threads))) return st;
     L.wave_stride = (uint64_t)blocks * (threads / 64);

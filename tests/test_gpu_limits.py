@@ -41,3 +41,70 @@ def test_loss_gradient_of_an_infinite_upstream(P, pairs, window, schedule):  # n
         grad = torch.zeros_like(c)
         P.stress_backward(g, c, pairs, 0, torch.tensor([up], device="cuda"), nv, grad, **kw)
         assert grad.tolist() == [-up, -up, up, up] * 2
+
+
+def _device_bytes(P, g):  # noqa: F811
+    import ctypes
+    from paper_2409_00876_amd import _lib
+    info = _lib.GraphInfo()
+    _lib.check(P.lib().pgsgd_graph_get_info(g.handle, ctypes.byref(info)))
+    return int(info.device_bytes)
+
+
+def test_term_list_gives_way_to_other_buffers(P, monkeypatch):  # noqa: F811
+    # a budget that the one-wave layout's list fills: the metric of two layouts, the window-major metric and the loss
+    # still find room for their buffers, and the layout is the same bit for bit with the list and without
+    import torch
+    sg = synth.generate(1500, 0.2, 8, 23)
+    g = P.Graph.from_synth(sg)
+    first = P.init_coords(g, g.new_coords())
+    P.sample_terms(g, 0, 0, 64)  # the window tables; the recording hook takes no list
+    tables = _device_bytes(P, g)
+    P.layout(g, first, n_iters=4)
+    cap = _device_bytes(P, g)
+    assert cap > tables
+    monkeypatch.setenv("PGSGD_MAX_DEVICE_BYTES", str(cap))
+    again = P.init_coords(g, g.new_coords())
+    P.layout(g, again, n_iters=4)
+    assert torch.equal(first, again) and _device_bytes(P, g) == cap
+    r = P.path_stress_compare(g, first, again, 5)
+    assert r["ratio"] == 1.0 and _device_bytes(P, g) <= cap
+    P.path_stress(g, first, 5, pairs="uniform_windowed")
+    loss, nv = P.stress_forward(g, first, 5000, 0)
+    P.stress_backward(g, first, 5000, 0, torch.ones(1, device="cuda"), nv, torch.zeros_like(first))
+    assert _device_bytes(P, g) <= cap
+    P.init_coords(g, again)
+    P.layout(g, again, n_iters=4)
+    torch.cuda.synchronize()
+    assert torch.equal(first, again) and _device_bytes(P, g) <= cap
+
+
+def test_captured_layout_outlives_the_term_list(P):  # noqa: F811
+    # a captured one-wave layout, larger than any before it, replayed around eager layouts that grow the list
+    import torch
+    sg = synth.generate(700, 0.2, 4, 29)
+    g = P.Graph.from_synth(sg)
+    c, ref = g.new_coords(), g.new_coords()
+    kw = dict(n_iters=4, terms_per_step=20)
+    P.init_coords(g, ref)
+    P.layout_noalloc(g, ref, **kw)
+    P.init_coords(g, c)
+    P.layout(g, c, n_iters=4, terms_per_step=2)
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        P.init_coords(g, c)
+        P.layout(g, c, **kw)
+    other = g.new_coords()
+    for terms in (0, 30, 60):
+        if terms:
+            P.init_coords(g, other)
+            P.layout(g, other, n_iters=4, terms_per_step=terms)
+        c.zero_()
+        graph.replay()
+        torch.cuda.synchronize()
+        assert torch.equal(c, ref)
+    P.init_coords(g, c)
+    P.layout(g, c, **kw)
+    torch.cuda.synchronize()
+    assert torch.equal(c, ref)
