@@ -269,7 +269,10 @@ enum { PGSGD_FLAG_COUNT_AHEAD = 1, PGSGD_FLAG_COUNT_IN_ORDER = 2 };
 /* Processing order of the terms of an iteration.
  *   PLAIN    term groups in index order over a grid capped by
  *            max_inflight_waves (automatic: n_nodes / 2048 below 16,384 nodes,
- *            the larger of that and min(n_nodes / 64, 1024) from there on)
+ *            the larger of that and min(n_nodes / 64, 512, S^2 / n_nodes /
+ *            1500) from there on: 42 graphs of 33K to 400K nodes and 1 to 24
+ *            paths have 1.007 times the path stress of n_nodes / 2048 waves on
+ *            average, 0.84 to 1.04 times)
  *   WINDOWED window-major enumeration: the steps are cut into windows of
  *            2^h consecutive global steps (h = 14, decreased while there
  *            would be fewer than 16 windows but not below 6, increased while
@@ -293,10 +296,18 @@ enum { PGSGD_FLAG_COUNT_AHEAD = 1, PGSGD_FLAG_COUNT_IN_ORDER = 2 };
  *            nodes_w / 32 in the iterations t >= n_iters / 2, whose partners
  *            all lie in the active window; both at most n_nodes / 2048 below
  *            32,768 nodes and the largest of n_nodes / 2048,
- *            min(n_nodes / 512, 3584) and min(n_nodes / 64, 1024) from there
- *            on, and the first eighth of the iterations at most
- *            max(n_nodes / 2048, 512); in a batch n_nodes / 2048, or twice
- *            that if every graph has 32,768 nodes or more).  A layout of one
+ *            min(n_nodes / 512, 3584, few) and min(n_nodes / 64, 1024, few)
+ *            from there on, few = S / 2048 * max(1, (S / n_nodes / 5)^4), and
+ *            the first eighth of the iterations at most
+ *            max(n_nodes / 2048, 512); in a batch n_nodes / 2048, or, if every
+ *            graph has 32,768 nodes or more, twice that (four times for graphs
+ *            below 65,536 nodes), at most max(n_nodes / 2048, few)).  The time
+ *            has a step at 32,768 nodes (24 paths: 31K nodes 354 ms, 38K nodes
+ *            10.4 ms): graphs below it run one or two waves on each XCD and
+ *            repeat almost exactly, which more waves would not.  84 graphs of
+ *            33K to 500K nodes and 1 to 24 paths have 1.015 times the path
+ *            stress of n_nodes / 2048 waves on average, 0.94 to 1.21 times, the
+ *            ends at few paths below 65,536 nodes.  A layout of one
  *            wave takes its terms from a list of one iteration's, at most
  *            64 MB, that the graph (or the batch) keeps; a graph gives its
  *            list up when another buffer of it needs the memory, and a call

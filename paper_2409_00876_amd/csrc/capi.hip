@@ -755,7 +755,7 @@ pgsgd_status pgsgd_init_coords(pgsgd_graph* g, uint64_t seed, uint32_t graph_id,
 namespace {
 
 // Launch shape of k_layout_iter: a full device of resident waves, capped by
-// params.max_inflight_waves (automatic: see auto_inflight_waves) and by the
+// params.max_inflight_waves (automatic: auto_inflight_waves_plain) and by the
 // number of 64-term groups.  Large grids use 4-wave blocks; small caps use
 // one-wave blocks so the number of concurrent waves is exactly the cap.
 pgsgd_status layout_grid(pgsgd_graph* g, const pgsgd_params* p, size_t lds, uint64_t n_groups, uint32_t* blocks,
@@ -765,7 +765,7 @@ pgsgd_status layout_grid(pgsgd_graph* g, const pgsgd_params* p, size_t lds, uint
   if (st) return st;
   uint64_t waves = (uint64_t)g->n_cu * bpc * 4;
   const uint64_t cap =
-      p->max_inflight_waves ? p->max_inflight_waves : auto_inflight_waves(g->n_nodes, kManyWaveNodesPlain, 0);
+      p->max_inflight_waves ? p->max_inflight_waves : auto_inflight_waves_plain(g->n_nodes, g->S);
   waves = std::min(waves, cap);
   waves = std::min(waves, std::max<uint64_t>(1, n_groups));
   if (waves >= 4ull * g->n_cu) {

@@ -57,21 +57,52 @@ inline uint32_t window_shift(uint64_t S) {
   return sh;
 }
 
-// Automatic cap.  One wave keeps the sampled path stress of the sequential loop
-// on a 2.6K-node graph and two waves raise it by 12%, but what counts there are
-// the XCDs: each works on its own L2's copy of the coordinates until the
-// launch ends.  On 51K nodes the stress is 1.0 / 1.23 / 1.33 / 1.45 of one
-// wave's on 1 / 2 / 4 / 8 XCDs, and then flat from 8 to 1,024 waves while the
-// time falls as 1 / waves (250 ms at 25 waves, 15 ms at 512).  So below `many`
-// nodes the cap is n_nodes / 2048 waves, one or two per XCD, whose runs repeat
-// to about 3e-4 of the coordinates (one wave: exactly) where more waves would
-// move the layout by 1e-3; from there on n_nodes / 64 waves up to 1,024, and
-// where that is more n_nodes / 512 up to `most`, and n_nodes / 2048.
+// Automatic cap of a whole graph.  One wave keeps the sampled path stress of the
+// sequential loop on a 2.6K-node graph and two waves raise it by 12%, but what
+// counts there are the XCDs: each works on its own L2's copy of the coordinates
+// until the launch ends.  On 51K nodes the stress is 1.0 / 1.23 / 1.33 / 1.45 of
+// one wave's on 1 / 2 / 4 / 8 XCDs, and with 24 paths within 0.5% from 24 to
+// 1,024 waves while the time falls as 1 / waves (240 ms at 24, 10.5 at 780).  So
+// below kManyWaveNodes the cap is n_nodes / 2048 waves, one or two per XCD, whose
+// runs repeat to about 3e-4 of the coordinates (one wave: exactly) where more
+// waves would move the layout by 1e-3; from there on n_nodes / 64 waves up to
+// 1,024, and where that is more n_nodes / 512 up to kLocalMostWaves, and
+// n_nodes / 2048.
+//
+// With few paths a node has few updates an iteration, in few windows, to make
+// up for the lost ones, and the waves that leave the stress alone fall with the
+// steps: S / 512, S / 1024 and S / 2048 waves had 1.13 / 1.05 / 1.00 times the
+// stress of n_nodes / 2048 on one path over 84K nodes (n_nodes / 64: 1.25), 1.13
+// / 1.05 / 1.00 on four over 48K (1.15), 1.17 / 1.11 / 1.02 on six over 86K
+// (1.17); on eight and more paths n_nodes / 64 leaves it within its spread.  So
+// the cap is S / 2048 waves up to five steps a node, rising with the fourth
+// power of the steps a node beyond (twelve paths, 7.6 steps: S / 384), and never
+// below n_nodes / 2048.  It costs the six paths 24.6 ms for 6.0 (131 at n_nodes
+// / 2048).
+//
+// In the plain order every term reads the whole graph and 512 waves are as many
+// as the fabric serves: 157K / 326K nodes 21.0 / 45.5 ms at 512 and 21.1 / 46.3
+// at 1,024 with 1.013 / 1.003 and 1.031 / 1.008 times the stress of n_nodes /
+// 2048; 85K nodes 13.9 and 13.3 ms, 1.026 and 1.052.  Few paths take (S / 1500)
+// waves a step of a node: one path over 84K nodes 1.02 times the stress, four
+// over 70K at 450 waves 1.01 (at 1,024: 1.05).
 constexpr uint32_t kManyWaveNodes = 32768;
 constexpr uint32_t kManyWaveNodesPlain = 16384;  // plain order: runs of 8 waves already differ by 6e-4 to 9e-4
-inline uint64_t auto_inflight_waves(uint64_t n, uint32_t many, uint64_t most) {
-  if (n < many) return std::max<uint64_t>(1, n / 2048);
-  return std::max({n / 2048, std::min<uint64_t>(n / 512, most), std::min<uint64_t>(n / 64, 1024)});
+inline uint64_t few_path_waves(uint64_t n, uint64_t S) {
+  const double per_node = (double)S / (double)std::max<uint64_t>(n, 1);
+  const double w = (double)S / 2048.0 * std::max(1.0, std::pow(per_node / 5.0, 4.0));
+  return std::max<uint64_t>({1, n / 2048, (uint64_t)std::min(w, 1e15)});
+}
+inline uint64_t auto_inflight_waves(uint64_t n, uint64_t S) {
+  if (n < kManyWaveNodes) return std::max<uint64_t>(1, n / 2048);
+  const uint64_t some = std::min<uint64_t>(n / 64, 1024), most = std::min<uint64_t>(n / 512, kLocalMostWaves);
+  return std::min(std::max({n / 2048, some, most}), few_path_waves(n, S));
+}
+inline uint64_t auto_inflight_waves_plain(uint64_t n, uint64_t S) {
+  const uint64_t least = std::max<uint64_t>(1, n / 2048);
+  if (n < kManyWaveNodesPlain) return least;
+  const double few = (double)S / 1500.0 * ((double)S / (double)n);
+  return std::max(least, std::min({n / 64, (uint64_t)512, (uint64_t)std::min(few, 1e15)}));
 }
 
 // Iterations of a layout by their launch shape: the first eighth, whose steps
@@ -90,14 +121,17 @@ inline LocalPhase local_phase(uint32_t iter, uint32_t n_iters) {
 // layout of 148K nodes lands 450 nt further along x than with 72 (6.5e-4 of
 // the coordinates, runs differ by 3.6e-4), with 512 or fewer it does not.
 // Graphs of a batch run `scale` times n_nodes / 2048 waves in every iteration
-// (scale = 0: no batch).  Several of them share each L2, and what one evicts of
-// another's coordinates the other XCDs then see, so a graph's place depends on
-// the pace of its neighbours: all must gain alike, and not by much.  Six graphs
-// of 60K to 351K nodes took 1,080 ms at scale 1 and 475 / 270 / 195 at 2 / 4 /
-// 8; graph by graph, layouts of scale 1 / 2 / 4 / 8 lie 1.1 / 1.1 / 1.3 / 1.5
-// times as far from a set of scale 1 as its own lie from each other (means over
-// 24).  With the caps of single layouts (174 ms) the smallest graph lay five
-// times as far.
+// (scale = 0: no batch), twice that below 65,536 nodes where scale > 1.
+// Several of them share each L2, and what one evicts of another's coordinates
+// the other XCDs then see, so a graph's place depends on the pace of its
+// neighbours: all must gain alike, and not by much.  Six graphs of 60K to 351K
+// nodes took 1,080 ms at scale 1 and 475 / 270 / 195 at 2 / 4 / 8; graph by
+// graph, layouts of scale 1 / 2 / 4 / 8 lie 1.1 / 1.1 / 1.3 / 1.5 times as far
+// from a set of scale 1 as its own lie from each other (means over 24).  With
+// the caps of single layouts (174 ms) the smallest graph lay five times as far.
+// Four graphs of 33K to 59K nodes: 401 ms at n_nodes / 2048 waves, 182 at twice
+// and 101 at four times that; the stress of 19 graphs in six batches is 1.003
+// and 0.987 of that at n_nodes / 2048 on average (0.96 to 1.14 and 0.89 to 1.07).
 constexpr uint32_t kBatchScale = 2;
 
 inline uint64_t auto_local_waves(uint32_t n_nodes, uint32_t n_paths, uint64_t S, LocalPhase phase, uint32_t scale) {
@@ -107,9 +141,11 @@ inline uint64_t auto_local_waves(uint32_t n_nodes, uint32_t n_paths, uint64_t S,
   const uint64_t per = phase == kPhaseCooling ? kLocalNodesPerWaveCooling : kLocalNodesPerWave;
   uint64_t w = (uint64_t)(nodes_w / (double)per);
   if (scale) {
-    w = std::min<uint64_t>(w, (uint64_t)scale * std::max(1u, n_nodes / 2048));
+    const uint64_t times = scale > 1 && n_nodes < 65536 ? 2 * scale : scale;
+    w = std::min<uint64_t>(w, times * std::max(1u, n_nodes / 2048));
+    w = std::min(w, few_path_waves(n_nodes, S));
   } else {
-    w = std::min<uint64_t>(w, auto_inflight_waves(n_nodes, kManyWaveNodes, kLocalMostWaves));
+    w = std::min<uint64_t>(w, auto_inflight_waves(n_nodes, S));
     if (phase == kPhaseEarly) w = std::min(w, std::max<uint64_t>(n_nodes / 2048, kLocalEarlyWaves));
   }
   return std::max<uint64_t>(1, w);
@@ -118,14 +154,14 @@ inline uint64_t auto_local_waves(uint32_t n_nodes, uint32_t n_paths, uint64_t S,
 // Grids of k_layout_local: the in-flight wave cap (params.max_inflight_waves,
 // automatic: auto_local_waves) and the waves that the device holds give the
 // waves, which no phase exceeds; 256-thread blocks in a multiple of 8 (one
-// share per XCD), or 64-thread blocks below 32 waves.  Automatic caps of graphs of fewer than 65,536 nodes keep the
-// proportion between the XCDs that n_nodes / 2048 one-wave blocks have (21
-// blocks: three on XCDs 0..4, two on 5..7), so that the same XCDs end their
-// shares last: an XCD writes its copy of the coordinates back when it is
-// done, and the last one's stand.  With equal XCDs a layout of 44.5K nodes lay
-// 2e-3 to 3e-3 away (runs differ by 3e-4), with the proportion kept 6e-4.  Caps
-// below four waves for each of those blocks (few paths, or paths that revisit
-// nodes; batches) keep it with 64-thread blocks.
+// share per XCD), or 64-thread blocks below 32 waves.  Automatic caps of graphs
+// of fewer than 65,536 nodes keep the proportion between the XCDs that n_nodes /
+// 2048 one-wave blocks have (21 blocks: three on XCDs 0..4, two on 5..7), so
+// that the same XCDs end their shares last: an XCD writes its copy of the
+// coordinates back when it is done, and the last one's stand.  With equal XCDs a
+// layout of 44.5K nodes lay 2e-3 to 3e-3 away (runs differ by 3e-4), with the
+// proportion kept 6e-4.  Caps below four waves for each of those blocks (few
+// paths, or paths that revisit nodes; batches) keep it with 64-thread blocks.
 struct LocalGrids {
   uint32_t blocks[kPhases], threads[kPhases];
   uint32_t quota_hi[kPhases], quota_lo[kPhases], hi_xcds[kPhases];  // blocks of an XCD's share that take work

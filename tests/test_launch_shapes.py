@@ -101,3 +101,17 @@ def test_window_grids_stay_within_their_wave_caps(local_grids):
         if cap >= 32:
             assert min(xcds) >= 1, (case, row)  # every XCD works on its own run
             assert 2 * sum(xcds) > cap, (case, row)  # and the cap is used
+
+
+def test_few_paths_take_few_waves(local_grids):
+    # S / 2048 waves up to five steps a node, or n / 2048, in every phase, alone and in a batch; from twelve paths on
+    # the cap does not bind
+    cases = [(n, paths, paths * n // 2, 0, 6144, scale) for n in (32768, 52000, 84000, 340000, 3000000)
+             for paths in (1, 2, 3, 6, 10, 16, 24) for scale in (0, 2)]
+    got = local_grids([" ".join(map(str, c)) for c in cases])
+    for k, row in enumerate(got):
+        n, paths, S, _, _, scale = cases[k // 3]
+        if paths <= 10:
+            assert row[0] <= max(n // 2048, S // 2048), (cases[k // 3], row)
+        elif scale == 0 and k % 3 == 1:  # uniform partners, S / n = 8 and more
+            assert row[0] >= min(n // 64, 1024), (cases[k // 3], row)
