@@ -1868,7 +1868,8 @@ pgsgd_status pgsgd_path_stress_exact(pgsgd_graph* g, const float* coords, double
   *mean_out = 0.0;
   if (pairs_out) *pairs_out = 0;
   if (g->S == 0) return ok();
-  if ((size_t)g->path_slots * 8 > g->lds_limit) return fail(PGSGD_ERR_UNSUPPORTED, "too many paths for LDS");
+  if ((size_t)g->path_slots * 8 + kExactStaticLds > g->lds_limit)
+    return fail(PGSGD_ERR_UNSUPPORTED, "too many paths for LDS");
   DeviceGuard guard(g->device);
   hipStream_t s = (hipStream_t)stream;
   StressLaunch P = make_stress_launch(g, coords, kStreamSps, 0, 0);

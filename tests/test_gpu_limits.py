@@ -108,3 +108,20 @@ def test_captured_layout_outlives_the_term_list(P):  # noqa: F811
     P.layout(g, c, **kw)
     torch.cuda.synchronize()
     assert torch.equal(c, ref)
+
+
+def test_exact_path_stress_with_the_most_paths(P):  # noqa: F811
+    # 16,000 paths: their table and the kernel's own tiles together still fit a block's LDS; twice as many do not
+    import torch
+    for n_paths in (16000, 33000):
+        sg = synth.SynthGraph(np.full(100, 5, np.uint32), (2 * np.arange(n_paths + 1)).astype(np.uint64),
+                              (np.arange(2 * n_paths) % 100).astype(np.uint32), {}, "many-paths")
+        og, g = O.Graph.from_synth(sg), P.Graph.from_synth(sg)
+        c = O.init_coords(og) + np.random.default_rng(3).normal(scale=4.0, size=400).astype(np.float32)
+        if n_paths > 16384:
+            with pytest.raises(P.PgsgdError, match="too many paths"):
+                P.path_stress_exact(g, torch.from_numpy(c).cuda())
+            continue
+        mean, pairs = P.path_stress_exact(g, torch.from_numpy(c).cuda())
+        ref = O.path_stress_exact(og, c)
+        assert pairs == ref[1] == n_paths and abs(mean - ref[0]) <= 1e-9 * abs(ref[0])
