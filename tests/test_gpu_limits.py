@@ -125,3 +125,40 @@ def test_exact_path_stress_with_the_most_paths(P):  # noqa: F811
         mean, pairs = P.path_stress_exact(g, torch.from_numpy(c).cuda())
         ref = O.path_stress_exact(og, c)
         assert pairs == ref[1] == n_paths and abs(mean - ref[0]) <= 1e-9 * abs(ref[0])
+
+
+# an infinite coordinate in every form of the tiles (unstaged and staged, the image in double and in float, beyond the
+# tiles) and in the plain order: the loss is infinite where a pair names its endpoint and unmoved where none does; the
+# gradient is NaN where a pair reaches it, as in the oracle's FP64, and the oracle's elsewhere
+@pytest.mark.parametrize("backbone,paths,pairs,window,renumber,schedule", [
+    (300, 3, 40, 1000, "auto", 3), (9000, 5, 200, 1000, "auto", 3), (900, 4, 60000, 1000, "auto", 3),
+    (9000, 5, 300000, 1000, "always", 3), (9000, 5, 100003, 9000, "auto", 3), (5000, 6, 30011, 20000, "auto", 3),
+    (5000, 6, 30011, 30000, "auto", 3), (5000, 6, 30011, 1000, "auto", 1)])
+def test_loss_of_an_infinite_coordinate(P, backbone, paths, pairs, window, renumber, schedule):  # noqa: F811
+    import torch
+    sg = synth.generate(backbone, 0.2, paths, 31)
+    og, g = O.Graph.from_synth(sg), P.Graph.from_synth(sg, renumber=renumber)
+    rng = np.random.default_rng(pairs)
+    c = (O.init_coords(og) + rng.normal(scale=5.0, size=4 * sg.n_nodes)).astype(np.float32)
+    kw = dict(seed=11, zipf_window=window, schedule=schedule)
+    oracle = O.stress_loss_grad_windowed if schedule == 3 else O.stress_loss_grad
+    loss0, nv0, grad0 = oracle(og, c, pairs, seed=11, step=0, window=window)
+    touched = (np.abs(grad0).reshape(2, -1) > 0).any(axis=0)
+    assert touched.any()
+    for k in (int(np.argmax(np.abs(grad0[: touched.size]))), *np.nonzero(~touched)[0][:1]):
+        far = c.copy()
+        far[k] = np.inf
+        t = torch.from_numpy(far).cuda()
+        loss, nv = P.stress_forward(g, t, pairs, 0, **kw)
+        grad = torch.zeros_like(t)
+        P.stress_backward(g, t, pairs, 0, torch.ones(1, device="cuda"), nv, grad, **kw)
+        _, _, ref = oracle(og, far, pairs, seed=11, step=0, window=window)
+        assert int(nv.item()) == nv0
+        if touched[k]:
+            assert loss.item() == float("inf")
+        else:
+            assert abs(loss.item() - loss0) <= 1e-5 * abs(loss0)
+        got, nan = grad.cpu().numpy().astype(np.float64), np.isnan(ref)
+        assert np.array_equal(np.isnan(got), nan) and nan[k] == touched[k]
+        err = np.abs(got[~nan] - ref[~nan])
+        assert np.all(err <= 1e-4 * np.abs(ref[~nan]) + 1e-6 * np.abs(ref[~nan]).max())
