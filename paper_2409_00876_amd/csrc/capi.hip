@@ -1875,8 +1875,9 @@ pgsgd_status pgsgd_path_stress_exact(pgsgd_graph* g, const float* coords, double
   StressLaunch P = make_stress_launch(g, coords, kStreamSps, 0, 0);
   P.work = g->d_work;
   HIP_TRY(launch_to_work(coords, g->d_work, g->n_nodes, g->d_inv, s));
-  HIP_TRY(launch_path_stress_exact(P, g->max_path_steps, g->d_max, g->d_part_f, g->d_part_n, s));
-  HIP_TRY(launch_reduce_parts(g->d_part_f, g->d_part_n, kStressBlocks, g->d_out_f, g->d_out_n, nullptr, nullptr, s));
+  uint32_t parts = 0;
+  HIP_TRY(launch_path_stress_exact(P, g->max_path_steps, g->d_max, g->d_part_f, g->d_part_n, &parts, s));
+  HIP_TRY(launch_reduce_parts(g->d_part_f, g->d_part_n, parts, g->d_out_f, g->d_out_n, nullptr, nullptr, s));
   double f = 0.0;
   uint64_t n = 0;
   HIP_TRY(hipMemcpyAsync(&f, g->d_out_f, sizeof(f), hipMemcpyDeviceToHost, s));

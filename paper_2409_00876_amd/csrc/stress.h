@@ -177,7 +177,7 @@ hipError_t launch_segment_min_node(const StepRec* rec, const uint64_t* start, ui
                                    hipStream_t s);
 // max_path_steps, d_max: the graph's longest path in steps and in nucleotides
 hipError_t launch_path_stress_exact(const StressLaunch& P, uint64_t max_path_steps, int64_t d_max, double* part_f,
-                                    uint64_t* part_n, hipStream_t s);
+                                    uint64_t* part_n, uint32_t* n_parts, hipStream_t s);
 // Static LDS of k_path_stress_exact, rounded up.
 constexpr size_t kExactStaticLds = 25 * 1024;
 hipError_t launch_stress_fwd(const StressLaunch& P, double* part_f, uint64_t* part_n, hipStream_t s);

@@ -1269,16 +1269,19 @@ hipError_t launch_sps_win(const SpsWinLaunch& W, double* part_f, uint64_t* part_
 }
 
 hipError_t launch_path_stress_exact(const StressLaunch& P, uint64_t max_path_steps, int64_t d_max, double* part_f,
-                                    uint64_t* part_n, hipStream_t s) {
+                                    uint64_t* part_n, uint32_t* n_parts, hipStream_t s) {
   const uint32_t chunks = (uint32_t)((max_path_steps + kExactRows + kExactCols - 1) / kExactCols);
   const size_t lds = (size_t)P.path_slots * 8;
+  // a block for every unit at most: each fills its path table before it looks for one
+  const uint64_t units = (P.S + kExactRows - 1) / kExactRows * chunks;
+  *n_parts = (uint32_t)std::min<uint64_t>(kStressBlocks, std::max<uint64_t>(1, units));
   // any line up to 2^53 is exact; 2^40 leaves genomes a factor of 100 and lets a path of 256 long nodes cross it
   if (d_max < (1ll << 40))
-    hipLaunchKernelGGL(k_path_stress_exact<double>, dim3(kStressBlocks), dim3(kExactRows), lds, s, P, chunks, part_f,
+    hipLaunchKernelGGL(k_path_stress_exact<double>, dim3(*n_parts), dim3(kExactRows), lds, s, P, chunks, part_f,
                        part_n);
   else
-    hipLaunchKernelGGL(k_path_stress_exact<int64_t>, dim3(kStressBlocks), dim3(kExactRows), lds, s, P, chunks,
-                       part_f, part_n);
+    hipLaunchKernelGGL(k_path_stress_exact<int64_t>, dim3(*n_parts), dim3(kExactRows), lds, s, P, chunks, part_f,
+                       part_n);
   return hipGetLastError();
 }
 
