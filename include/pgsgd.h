@@ -295,19 +295,18 @@ enum { PGSGD_FLAG_COUNT_AHEAD = 1, PGSGD_FLAG_COUNT_IN_ORDER = 2 };
  *            2^h * n_nodes * n_paths / S the nodes a window visits, and
  *            nodes_w / 32 in the iterations t >= n_iters / 2, whose partners
  *            all lie in the active window; both at most n_nodes / 2048 below
- *            32,768 nodes and the largest of n_nodes / 2048,
+ *            36,864 nodes and the largest of n_nodes / 2048,
  *            min(n_nodes / 512, 3584, few) and min(n_nodes / 64, 1024, few)
- *            from there on, few = S / 2048 * max(1, (S / n_nodes / 5)^4), and
+ *            from there on, few = S / 2048 * max(1, (S / n_nodes / 7)^4), and
  *            the first eighth of the iterations at most
  *            max(n_nodes / 2048, 512); in a batch n_nodes / 2048, or, if every
  *            graph has 32,768 nodes or more, twice that (four times for graphs
  *            below 65,536 nodes), at most max(n_nodes / 2048, few)).  The time
- *            has a step at 32,768 nodes (24 paths: 31K nodes 354 ms, 38K nodes
- *            10.4 ms): graphs below it run one or two waves on each XCD and
- *            repeat almost exactly, which more waves would not.  84 graphs of
- *            33K to 500K nodes and 1 to 24 paths have 1.015 times the path
- *            stress of n_nodes / 2048 waves on average, 0.94 to 1.21 times, the
- *            ends at few paths below 65,536 nodes.  A layout of one
+ *            has a step at 36,864 nodes (24 paths: 34K nodes 241 ms, 38K nodes
+ *            10.4 ms): below it the path stress at more waves was 1.055 times
+ *            that of n_nodes / 2048 on average, from it on it is 1.009 times
+ *            (111 graphs of up to 500K nodes and 1 to 24 paths, single ones
+ *            0.93 to 1.10 times, the ends at few paths).  A layout of one
  *            wave takes its terms from a list of one iteration's, at most
  *            64 MB, that the graph (or the batch) keeps; a graph gives its
  *            list up when another buffer of it needs the memory, and a call
@@ -388,8 +387,10 @@ pgsgd_status pgsgd_layout(pgsgd_graph *g, const pgsgd_params *p, float *coords, 
 /*
  * pgsgd_layout for callers that cannot allocate device memory (code under
  * HIP graph capture, tight serving loops, harnesses that forbid hipMalloc):
- * the same layout, the same kernels and the same sampled terms, but the
- * window tables of the WINDOWED schedule live in a device array of the
+ * the same layout and the same sampled terms, with the same kernels except
+ * that a layout of one wave has no term list (see PGSGD_SCHEDULE_WINDOWED) and
+ * takes about seven times as long for the same coordinates, but the window
+ * tables of the WINDOWED schedule live in a device array of the
  * library (4 MiB per device, held until the process ends; enough for the
  * 32,768 windows the schedule allows) instead of buffers the graph allocates
  * on first use, and every iteration counts its windows in order on `stream`.
@@ -434,9 +435,10 @@ typedef struct {
 } pgsgd_stress_result;
 
 /*
- * Sampled path stress with its 95% confidence interval (Eq. 2).  Path p receives exactly pairs_per_step * |p| pairs; pair
- * q of path p (q in [m*off[p], m*off[p+1])) draws Philox stream 1 at counter
- * q: i = start + floor(u64 * |p| / 2^64), j = start + floor(r2 * |p| / 2^32),
+ * Sampled path stress with its 95% confidence interval (Eq. 2).  Path p
+ * receives exactly pairs_per_step * |p| pairs; pair q of path p (q in
+ * [m*off[p], m*off[p+1])) draws Philox stream 1 at counter q:
+ * i = start + floor(u64 * |p| / 2^64), j = start + floor(r2 * |p| / 2^32),
  * e_i = bit 0, e_j = bit 1 of r3.  All paths are pooled.  Stress terms are
  * computed in FP64 from the float32 coordinates.  coords: device; out: host.
  * Synchronises the stream.  Errors: INVALID_ARG, DEVICE.
@@ -566,8 +568,9 @@ pgsgd_status pgsgd_stress_forward(pgsgd_graph *g, const pgsgd_params *p, const f
  * the forward of the same step, n_pairs, seed and graph_id reuses that
  * forward's segment offsets.  The order of the float32 additions (not their
  * terms) varies from run to run.
- * Forward and backward read the graph's interleaved working copy of coords,
- * so calls on one graph must be ordered on one stream.  Async.
+ * Forward and backward read coords itself or the graph's interleaved working
+ * copy of it and share the graph's tables, so calls on one graph must be
+ * ordered on one stream.  Async.
  */
 pgsgd_status pgsgd_stress_backward(pgsgd_graph *g, const pgsgd_params *p, const float *coords, uint64_t n_pairs,
                                    uint32_t step, const float *grad_out_dev, const uint64_t *n_valid_dev,

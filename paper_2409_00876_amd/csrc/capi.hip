@@ -1019,7 +1019,7 @@ pgsgd_status ensure_loss_tiles(pgsgd_graph* g, hipStream_t s) {
 
 uint32_t batch_scale(pgsgd_graph* const* graphs, uint32_t n) {
   for (uint32_t k = 0; k < n; ++k)
-    if (graphs[k]->n_nodes < kManyWaveNodes) return 1;  // such a graph keeps its waves, so all do
+    if (graphs[k]->n_nodes < kBatchNodes) return 1;  // such a graph keeps its waves, so all do
   return kBatchScale;
 }
 
@@ -1949,7 +1949,7 @@ pgsgd_status pgsgd_stress_backward(pgsgd_graph* g, const pgsgd_params* p, const 
   auto copy_in = [&] { return launch_to_work(coords, g->d_work, g->n_nodes, g->d_inv, s); };
   if (resolve_schedule(p) == PGSGD_SCHEDULE_WINDOWED) {
     SpsWinLaunch W;
-    // by tiles when their LDS image fits a block (it does for every window W up to ~10^4)
+    // by tiles when their LDS image fits a block (it does for every window W up to about 21,000)
     const bool tiles = tiles_fit(g, p->zipf_window);
     if ((st = loss_win_prepare(g, p, P, n_pairs, s, &W, tiles))) return st;
     if (tiles) {

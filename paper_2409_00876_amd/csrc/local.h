@@ -42,7 +42,7 @@ constexpr uint64_t kLocalMostWaves = 3584;
 // iterations on 51K / 342K / 985K nodes took 5.9 / 42.8 / 70.8 ms without and
 // 4.8 / 35.0 / 60.7 with (500 to 1,900 waves); from about 3,500 waves on their
 // far lines fill the fabric and it is slower (2.7M nodes: 167.9 and 173.0 ms,
-// 7.2M: 437 and 448).  Graphs below 32,768 nodes keep their pace.
+// 7.2M: 437 and 448).  Graphs below kManyWaveNodes keep their pace.
 constexpr uint64_t kLocalAheadWaves = 3072;
 constexpr uint64_t kLocalEarlyWaves = 512;    // cap of the first eighth of the iterations below 1M nodes
 
@@ -65,7 +65,10 @@ inline uint32_t window_shift(uint64_t S) {
 // 1,024 waves while the time falls as 1 / waves (240 ms at 24, 10.5 at 780).  So
 // below kManyWaveNodes the cap is n_nodes / 2048 waves, one or two per XCD, whose
 // runs repeat to about 3e-4 of the coordinates (one wave: exactly) where more
-// waves would move the layout by 1e-3; from there on n_nodes / 64 waves up to
+// waves would move the layout by 1e-3, and at 16 and 17 blocks, whose XCDs share
+// evenly, raise the stress: to 1.055 times on average over nine graphs of 33K to
+// 36.6K nodes and 8 to 40 paths (1.00 to 1.17; 240 ms at 16 waves, 8.7 at 520),
+// against 1.015 over seven of 37K to 41K.  From there on n_nodes / 64 waves up to
 // 1,024, and where that is more n_nodes / 512 up to kLocalMostWaves, and
 // n_nodes / 2048.
 //
@@ -74,11 +77,11 @@ inline uint32_t window_shift(uint64_t S) {
 // steps: S / 512, S / 1024 and S / 2048 waves had 1.13 / 1.05 / 1.00 times the
 // stress of n_nodes / 2048 on one path over 84K nodes (n_nodes / 64: 1.25), 1.13
 // / 1.05 / 1.00 on four over 48K (1.15), 1.17 / 1.11 / 1.02 on six over 86K
-// (1.17); on eight and more paths n_nodes / 64 leaves it within its spread.  So
-// the cap is S / 2048 waves up to five steps a node, rising with the fourth
-// power of the steps a node beyond (twelve paths, 7.6 steps: S / 384), and never
-// below n_nodes / 2048.  It costs the six paths 24.6 ms for 6.0 (131 at n_nodes
-// / 2048).
+// (1.17), and n_nodes / 64 had 1.00 to 1.04 on twelve over 83K in four runs.  So
+// the cap is S / 2048 waves up to seven steps a node (eleven paths), rising with
+// the fourth power of the steps a node beyond (sixteen paths: S / 560), and
+// never below n_nodes / 2048.  It costs the six paths 24.6 ms for 6.0 (131 at
+// n_nodes / 2048).
 //
 // In the plain order every term reads the whole graph and 512 waves are as many
 // as the fabric serves: 157K / 326K nodes 21.0 / 45.5 ms at 512 and 21.1 / 46.3
@@ -86,11 +89,11 @@ inline uint32_t window_shift(uint64_t S) {
 // 2048; 85K nodes 13.9 and 13.3 ms, 1.026 and 1.052.  Few paths take (S / 1500)
 // waves a step of a node: one path over 84K nodes 1.02 times the stress, four
 // over 70K at 450 waves 1.01 (at 1,024: 1.05).
-constexpr uint32_t kManyWaveNodes = 32768;
+constexpr uint32_t kManyWaveNodes = 36864;
 constexpr uint32_t kManyWaveNodesPlain = 16384;  // plain order: runs of 8 waves already differ by 6e-4 to 9e-4
 inline uint64_t few_path_waves(uint64_t n, uint64_t S) {
   const double per_node = (double)S / (double)std::max<uint64_t>(n, 1);
-  const double w = (double)S / 2048.0 * std::max(1.0, std::pow(per_node / 5.0, 4.0));
+  const double w = (double)S / 2048.0 * std::max(1.0, std::pow(per_node / 7.0, 4.0));
   return std::max<uint64_t>({1, n / 2048, (uint64_t)std::min(w, 1e15)});
 }
 inline uint64_t auto_inflight_waves(uint64_t n, uint64_t S) {
@@ -133,6 +136,7 @@ inline LocalPhase local_phase(uint32_t iter, uint32_t n_iters) {
 // and 101 at four times that; the stress of 19 graphs in six batches is 1.003
 // and 0.987 of that at n_nodes / 2048 on average (0.96 to 1.14 and 0.89 to 1.07).
 constexpr uint32_t kBatchScale = 2;
+constexpr uint32_t kBatchNodes = 32768;  // a batch with a smaller graph runs at scale 1
 
 inline uint64_t auto_local_waves(uint32_t n_nodes, uint32_t n_paths, uint64_t S, LocalPhase phase, uint32_t scale) {
   const uint32_t sh = window_shift(S);
@@ -176,7 +180,8 @@ inline LocalGrids local_grids(uint32_t n_nodes, uint32_t n_paths, uint64_t S, ui
     const uint64_t cap =
         max_inflight_waves ? max_inflight_waves : auto_local_waves(n_nodes, n_paths, S, (LocalPhase)ph, scale);
     const uint64_t waves = std::max<uint64_t>(1, std::min(resident_waves, cap));
-    out.ahead[ph] = !max_inflight_waves && scale != 1 && n_nodes >= kManyWaveNodes && waves <= kLocalAheadWaves;
+    out.ahead[ph] = !max_inflight_waves && scale != 1 && waves <= kLocalAheadWaves &&
+                    n_nodes >= (scale ? kBatchNodes : kManyWaveNodes);
     out.quota_hi[ph] = out.quota_lo[ph] = 0xFFFFFFFFu;
     out.hi_xcds[ph] = kXcds;
     const bool wide = waves >= 4ull * kXcds;

@@ -368,11 +368,12 @@ __global__ __launch_bounds__(256) void k_ordered_terms(LocalLaunch P) {
 // mu (mag - d) / (2 mag), mag = sqrt(mag2), each operation correctly rounded as
 // by sqrtf and /.  The chain of these operations and the LDS round trip bound
 // k_layout_ordered (0.24 us an item with the compiler's sequences and a wait
-// for the stores, 0.19 so).  The reciprocal square root y serves both: y mag2 with one correction by the residual is the root,
-// and y / 2, Newton's step, two corrections by the residual the quotient
-// (Markstein, IBM J. Res. Dev. 34, 1990).  Items with a live lane outside the
-// ranges in which no intermediate result leaves FP32's normal numbers take the
-// compiler's sequences; a lane with mag2 = 0 has no step.
+// for the stores, 0.19 so).  The reciprocal square root y serves both: y mag2
+// with one correction by the residual is the root, and y / 2, Newton's step, two
+// corrections by the residual the quotient (Markstein, IBM J. Res. Dev. 34,
+// 1990).  Items with a live lane outside the ranges in which no intermediate
+// result leaves FP32's normal numbers take the compiler's sequences; a lane with
+// mag2 = 0 has no step.
 __device__ __forceinline__ float step_ratio(float mag2, float d, float mu, bool live) {
 #pragma clang fp contract(off)
   const float y = __builtin_amdgcn_rsqf(mag2);

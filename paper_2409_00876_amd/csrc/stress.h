@@ -118,7 +118,8 @@ hipError_t launch_loss_win_bwd(const SpsWinLaunch& W, const float* grad_out, con
 // base[t] on, and keeps the endpoints of up to kTileRange ids from base[t] on in
 // LDS: their coordinates, and in the adjoint an image of their gradient, flushed
 // with one atomic add per touched entry; other endpoints are read and added
-// directly.  Block b starts with unit b and takes the others from *queue.  The pairs are the window-major loss pairs of W, the same slots as
+// directly.  Block b starts with unit b and takes the others from *queue.  The
+// pairs are the window-major loss pairs of W, the same slots as
 // launch_loss_win_bwd.
 //
 // A segment's steps climb through up to ~2,000 ids, so what lies above the range

@@ -424,9 +424,10 @@ __device__ __forceinline__ uint64_t wave_total(uint32_t n, F f) {
 // One block of 1024 threads: seg_off = exclusive prefix of the counts and, with
 // `runs`, the per-run item prefixes and zeroed item counters (the passes by
 // tiles read seg_off alone).  The histogram is read into LDS (and cleared for
-// the next use); each of the 16 waves then scans a contiguous part, 64
-// neighbours at a time, and each half of a run's items the same way, so loads
-// and stores are coalesced (a chunk per thread stored 64 lines a wave): 24 us
+// the next use); each of the 16 waves then scans a contiguous part, 256
+// neighbours at a time (four a lane), and each half of a run's items the same
+// way, so loads and stores are coalesced (a chunk per thread stored 64 lines a
+// wave): 24 us
 // for the 1e7 loss pairs of a million backbone nodes, now 13.
 __global__ __launch_bounds__(1024) void k_sps_win_scan(SpsWinLaunch W, uint32_t runs) {
   extern __shared__ __align__(16) char lds[];
@@ -544,7 +545,7 @@ __global__ __launch_bounds__(kPair ? 1024 : 512) void k_sps_win(SpsWinLaunch W, 
 // lengths below 2^63 cannot reach: the same rounding, fewer instructions.  A
 // sum that is not finite (infinite or NaN coordinates) is taken again the
 // general way.  1.3e9 pairs: 19.3 ms with one row per thread and the
-// compiler's sequences, now 5.6 ms (four combinations a pair: 9.4e11 a second).
+// compiler's sequences, now 5.9 ms (four combinations a pair: 8.9e11 a second).
 // part_f: per-block sum of the pair means; part_n: per-block pair count.
 // ---------------------------------------------------------------------------
 constexpr uint32_t kExactRows = 256, kExactCols = 512;
