@@ -20,9 +20,10 @@ def _check(label, many, few):
     assert many.mean() <= 1.03 * few.mean() + 3 * error, label
 
 
-# the first sizes with many waves in the plain order and in the windowed one and the last below it, sizes whose XCDs share unequally (below
-# 65,536 nodes) and equally, one path (few updates a node), and where n_nodes / 64 waves are the most.  Two to six
-# paths are left out: which XCD ends last puts their layouts in one of several states, a few percent apart
+# the first sizes with many waves in the plain order and in the windowed one, one below it, sizes whose XCDs share
+# unequally (below 65,536 nodes) and equally, one path (few updates a node), and where n_nodes / 64 waves are the
+# most.  Two to six paths are left out: which XCD ends last puts their layouts in one of several states, a few percent
+# apart
 @pytest.mark.parametrize("schedule,nodes,paths", [(1, 20000, 8), (1, 85000, 12), (1, 84000, 1), (3, 34500, 24),
                                                   (3, 38500, 24), (3, 49000, 24), (3, 52000, 1), (3, 85000, 12),
                                                   (3, 84000, 1), (3, 200000, 8), (3, 330000, 1)])
