@@ -25,7 +25,7 @@ def _check(label, many, few):
 # most.  Two to six paths are left out: which XCD ends last puts their layouts in one of several states, a few percent
 # apart
 @pytest.mark.parametrize("schedule,nodes,paths", [(1, 20000, 8), (1, 85000, 12), (1, 84000, 1), (3, 34500, 24),
-                                                  (3, 38500, 24), (3, 49000, 24), (3, 52000, 1), (3, 85000, 12),
+                                                  (3, 38500, 24), (3, 49000, 24), (3, 52000, 1), (3, 125000, 12),
                                                   (3, 84000, 1), (3, 200000, 8), (3, 330000, 1)])
 def test_automatic_wave_caps_keep_the_stress(P, schedule, nodes, paths):  # noqa: F811
     sg = synth.generate(int(nodes / (2.0 - 0.95 ** paths)), 0.2, paths, 13)
